@@ -308,6 +308,11 @@ void launch_simp_filter(const double* rho, const double* dc, int N, double rmin,
 void launch_oc_eval(const double* rho, const double* dc, size_t n, double lam, double move, double eta, double lo,
                     double* out, double* partial, double* total, hipStream_t s);
 void launch_random(double* x, size_t n, uint64_t seed, hipStream_t s);
+// inverse of the pinned coarsest operator (coarse.hip)
+size_t coarse_scratch_doubles(int n);
+void launch_coarse_inverse(const int* node_lin, const int* node_map, const int* elem_map, int N, int n_n, int D,
+                           const double* Kel, double* scratch, double* c64, float* c32, double* status,
+                           hipStream_t s);
 void launch_expand_elem_matrices(const LevelView<double>& L, int kind, int n_e, int D,
                                  const int* elem_lin, double* out, hipStream_t s);
 template <typename T>

@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <array>
 #include <chrono>
 #include <cstdlib>
 #include <cmath>
@@ -428,103 +429,25 @@ struct EventSet {
   }
 };
 
-// The coarsest level's element matrices and connectivity on the host.
-struct CoarseHost {
-  std::vector<double> Ke;
-  std::vector<int> en;
-  double* dK = nullptr;
-  int* dEN = nullptr;
-  hipEvent_t ready = nullptr;
-};
-
-// Queues the copies of the coarsest level's element matrices and connectivity
-// to the host on s; c.ready marks their completion.
-static void coarse_fetch(Hier& h, hipStream_t s, CoarseHost& c, EventSet& evs) {
+// Queues the assembly, pinning and inversion of the coarsest operator on s; the
+// pivot check's outcome lands in status (3 doubles, read by check_coarse).
+// Returns the scratch buffers to release once s has been waited for.
+static std::array<void*, 2> coarse_factor(Hier& h, hipStream_t s, double* status) {
   const int l = h.L - 1;
   LevelData& d = h.lv[l];
   const int D = h.D, M = 8 * D;
   const int n = d.n_n * D;
-  if (n > 2048) fail(GMT_E_INVAL, "coarsest level has %d DOFs (> 2048): use more levels", n);
-  h.cn = n;
-  c.dK = h.alloc<double>((size_t)d.n_e * M * M);
-  c.dEN = h.alloc<int>((size_t)d.n_e * 8);
-  launch_expand_elem_matrices(h.view<double>(l), d.kind, d.n_e, D, d.elem_lin, c.dK, s);
-  launch_elem_nodes(d.elem_lin, d.n_e, d.node_map, d.N, c.dEN, s);
-  c.Ke.resize((size_t)d.n_e * M * M);
-  c.en.resize((size_t)d.n_e * 8);
-  GMT_HIP(hipMemcpyAsync(c.Ke.data(), c.dK, c.Ke.size() * sizeof(double), hipMemcpyDeviceToHost, s));
-  GMT_HIP(hipMemcpyAsync(c.en.data(), c.dEN, c.en.size() * sizeof(int), hipMemcpyDeviceToHost, s));
-  c.ready = evs.make();
-  GMT_HIP(hipEventRecord(c.ready, s));
-}
-
-// Assembles, pins and inverts the coarsest operator on the host once the
-// copies of coarse_fetch have landed (work queued on s after them keeps
-// running meanwhile), then uploads the inverse on s and waits for s.
-static void coarse_factor(Hier& h, hipStream_t s, CoarseHost& c) {
-  const int l = h.L - 1;
-  LevelData& d = h.lv[l];
-  const int D = h.D, M = 8 * D;
-  const int n = h.cn;
-  GMT_HIP(hipEventSynchronize(c.ready));
-  const std::vector<double>& Ke = c.Ke;
-  const std::vector<int>& en = c.en;
-  std::vector<double> A((size_t)n * n, 0.0);
-  for (int e = 0; e < d.n_e; ++e)
-    for (int a = 0; a < 8; ++a)
-      for (int i = 0; i < D; ++i)
-        for (int b = 0; b < 8; ++b)
-          for (int j = 0; j < D; ++j)
-            A[(size_t)(en[e * 8 + a] * D + i) * n + en[e * 8 + b] * D + j] +=
-                Ke[(size_t)e * M * M + (a * D + i) * M + b * D + j];
-  // pin node 0: identity rows / columns
-  for (int i = 0; i < D; ++i) {
-    for (int j = 0; j < n; ++j) A[(size_t)i * n + j] = A[(size_t)j * n + i] = 0.0;
-    A[(size_t)i * n + i] = 1.0;
-  }
-  double dmax = 0;
-  for (int i = 0; i < n; ++i) dmax = std::max(dmax, A[(size_t)i * n + i]);
-  // in-place lower Cholesky
-  for (int j = 0; j < n; ++j) {
-    double sjj = A[(size_t)j * n + j];
-    for (int k = 0; k < j; ++k) sjj -= A[(size_t)j * n + k] * A[(size_t)j * n + k];
-    if (!(sjj > 1e-13 * dmax)) fail(GMT_E_SINGULAR, "coarsest Cholesky: pivot %d is %g", j, sjj);
-    const double ljj = std::sqrt(sjj);
-    A[(size_t)j * n + j] = ljj;
-    for (int i = j + 1; i < n; ++i) {
-      double sij = A[(size_t)i * n + j];
-      const double* ri = &A[(size_t)i * n];
-      const double* rj = &A[(size_t)j * n];
-      for (int k = 0; k < j; ++k) sij -= ri[k] * rj[k];
-      A[(size_t)i * n + j] = sij / ljj;
-    }
-  }
-  // W = L^-1 (lower), then inv = W^T W
-  std::vector<double> W((size_t)n * n, 0.0);
-  for (int c = 0; c < n; ++c) {
-    W[(size_t)c * n + c] = 1.0 / A[(size_t)c * n + c];
-    for (int i = c + 1; i < n; ++i) {
-      double sacc = 0;
-      for (int k = c; k < i; ++k) sacc += A[(size_t)i * n + k] * W[(size_t)k * n + c];
-      W[(size_t)i * n + c] = -sacc / A[(size_t)i * n + i];
-    }
-  }
-  std::vector<double> inv((size_t)n * n, 0.0);
-  for (int i = 0; i < n; ++i)
-    for (int j = 0; j <= i; ++j) {
-      double sacc = 0;
-      for (int k = i; k < n; ++k) sacc += W[(size_t)k * n + i] * W[(size_t)k * n + j];
-      inv[(size_t)i * n + j] = inv[(size_t)j * n + i] = sacc;
-    }
-  for (int i = 0; i < D; ++i)
-    for (int j = 0; j < n; ++j) inv[(size_t)i * n + j] = inv[(size_t)j * n + i] = 0.0;
+  double* K = h.alloc<double>((size_t)d.n_e * M * M);
+  double* scratch = h.alloc<double>(coarse_scratch_doubles(n));
   h.cinv64 = h.alloc<double>((size_t)n * n);
   h.cinv32 = h.alloc<float>((size_t)n * n);
-  GMT_HIP(hipMemcpyAsync(h.cinv64, inv.data(), inv.size() * sizeof(double), hipMemcpyHostToDevice, s));
-  launch_convert<double, float>(h.cinv64, h.cinv32, inv.size(), s);
-  GMT_HIP(hipStreamSynchronize(s));
-  h.release(c.dK);
-  h.release(c.dEN);
+  launch_expand_elem_matrices(h.view<double>(l), d.kind, d.n_e, D, d.elem_lin, K, s);
+  launch_coarse_inverse(d.node_lin, d.node_map, d.elem_map, d.N, d.n_n, D, K, scratch, h.cinv64, h.cinv32, status, s);
+  return {K, scratch};
+}
+
+static void check_coarse(const double* status) {
+  if (status[0] != 0.0) fail(GMT_E_SINGULAR, "coarsest Cholesky: pivot %d is %g", (int)status[0] - 1, status[1]);
 }
 
 // ================================================================ building blocks
@@ -1594,10 +1517,10 @@ static void build(Hier& h, const uint8_t* vox, hipStream_t s, const double* rho 
   launch_load_vector(h.lv[0].node_lin, h.lv[0].occ8, h.lv[0].oscale64, h.lv[0].n_n, D, h.C, h.fe64, h.f64, s);
 
   timer.mark("diag+load");
+  h.cn = h.lv[h.L - 1].n_n * D;
+  if (h.cn > 2048) fail(GMT_E_INVAL, "coarsest level has %d DOFs (> 2048): use more levels", h.cn);
   EventSet evs;
-  CoarseHost ch;
-  coarse_fetch(h, s, ch, evs);
-  void* pw[7] = {};
+  void* pw[9] = {};
   // lambda_max(D^-1 K) per level by power iteration. The iterate only has to
   // point at the top of the spectrum, so the iterations run in FP32 (half the
   // operator bytes); the Rayleigh quotient that becomes the estimate is taken in
@@ -1618,15 +1541,23 @@ static void build(Hier& h, const uint8_t* vox, hipStream_t s, const double* rho 
     double* T64 = h.alloc<double>(off[h.L]);
     double* part = h.alloc<double>((size_t)h.L * kRedBlocks);
     pw[0] = X32, pw[1] = Y32, pw[2] = T32, pw[3] = X64, pw[4] = Y64, pw[5] = T64, pw[6] = part;
-    double* o = h.red_out + 64;  // [4 + 2l, 5 + 2l]: quotient of level l; [40 + l]: its norm
+    double* o = h.red_out + 64;  // [4 + 2l, 5 + 2l]: quotient of level l; [40 + l]: its norm; [56..58]: coarsest pivots
     // One vector: on level 1 the class-assembled boundary sweep (cb 7, or 9
     // with the staged interior) costs in proportion to the number of cases,
     // the masked-stencil one (cb 0, the default before the autotuner runs)
     // does not.
     const int cb_keep = h.lv[0].cb32, cb_keep64 = h.lv[0].cb64;
     if (h.lv[0].kind == KIND_SHARED) h.lv[0].cb32 = h.lv[0].cb64 = h.lv[0].n_st_blk32 > 0 ? 9 : 7;
-    hipEvent_t fork = evs.make();
+    hipEvent_t fork = evs.make(), coarse_done = evs.make();
     GMT_HIP(hipEventRecord(fork, s));
+    {
+      // the coarsest operator is inverted beside the iterations
+      hipStream_t sc = aux_stream(h.L - 1);
+      GMT_HIP(hipStreamWaitEvent(sc, fork, 0));
+      const std::array<void*, 2> tmp = coarse_factor(h, sc, o + 56);
+      pw[7] = tmp[0], pw[8] = tmp[1];
+      GMT_HIP(hipEventRecord(coarse_done, sc));
+    }
     for (int l = 0; l < h.L; ++l) {
       LevelData& d = h.lv[l];
       const int n = d.n_n;
@@ -1673,11 +1604,12 @@ static void build(Hier& h, const uint8_t* vox, hipStream_t s, const double* rho 
     }
     h.lv[0].cb32 = cb_keep;
     h.lv[0].cb64 = cb_keep64;
-    // the host factors the coarsest operator while the iterations run
-    coarse_factor(h, s, ch);
-    // one host round trip for the quotients of all levels
-    double hv[2 * 12];
-    host_dot(h, o + 4, 2 * h.L, hv, s);
+    GMT_HIP(hipStreamWaitEvent(s, coarse_done, 0));
+    // one host round trip for the coarsest pivots and the quotients of all levels
+    double hw[59];
+    host_dot(h, o, 59, hw, s);
+    check_coarse(hw + 56);
+    const double* hv = hw + 4;
     for (int l = 0; l < h.L; ++l) {
       const double lam = hv[2 * l + 1] > 0 ? hv[2 * l] / hv[2 * l + 1] : 0.0;
       if (!(lam > 0) || !std::isfinite(lam)) fail(GMT_E_SINGULAR, "lambda_max estimate failed on level %d", l + 1);

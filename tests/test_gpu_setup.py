@@ -1,0 +1,86 @@
+"""GPU parity of the hierarchy build's kernels at the sizes where they can go wrong: the inverse of
+the pinned coarsest operator (tile and panel remainders, the smallest and largest matrices)."""
+
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from gmt_inputs import gyroid_sheet, uniform  # noqa: E402
+from oracle import solve as osolve  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda"
+
+
+def _gmt():
+    from paper_2604_26518_amd import binding
+    return binding
+
+
+# rows: 8 (padded to one 32-row tile), 81, 375 and 1029 (remainders of tile and panel), 1536 (none),
+# 1728, and 2048 - the largest accepted; levels 1 (shared K_e), 2 (mask table) and 3 (per element)
+COARSE = {
+    "thermal2": (lambda: uniform(2), 1, "thermal"),
+    "elastic3": (lambda: uniform(3), 1, "elastic"),
+    "elastic5": (lambda: uniform(5), 1, "elastic"),
+    "elastic8": (lambda: uniform(8), 1, "elastic"),
+    "thermal12": (lambda: uniform(12), 1, "thermal"),
+    "gyroid14": (lambda: gyroid_sheet(14, 1, 0.5), 2, "elastic"),
+    "gyroid28": (lambda: gyroid_sheet(28, 4, 0.35), 3, "elastic"),
+    "gyroid40_th": (lambda: gyroid_sheet(40, 2, 0.3), 3, "thermal"),
+}
+
+
+@pytest.mark.parametrize("case", sorted(COARSE))
+def test_coarsest_inverse(case):
+    """coarse_solve against a direct solve of the oracle's matrix.  Either side's solution is within
+    n eps cond(K) of exact (Cholesky factor and its inverse), hence the bound."""
+    make, L, phys = COARSE[case]
+    vox = make()
+    P = osolve.Problem(vox, L, phys)
+    H = _gmt().Hierarchy(vox, L, phys)
+    n = P.levels[-1].n_n
+    f = np.random.default_rng(7).standard_normal((n, H.c, H.d))
+    u = H.coarse_solve(torch.as_tensor(f, device=DEV)).cpu().numpy()
+    ref = osolve.coarse_solve(P, f)
+    assert np.all(u[0] == 0)
+    A = _pinned(H, L)
+    w = np.linalg.eigvalsh(A)
+    bound = 4 * A.shape[0] * np.finfo(float).eps * w[-1] / w[0]
+    err = np.linalg.norm(u - ref) / np.linalg.norm(ref)
+    print(f"[{case}] rows {n * H.d} error {err:.1e} bound {bound:.1e}", flush=True)
+    assert err <= bound
+    # the inverse is symmetric bit for bit: x . (inv y) for unit vectors
+    if n * H.d <= 400:
+        inv = np.stack([_column(H, j) for j in range(n * H.d)], 1)
+        assert np.array_equal(inv, inv.T)
+
+
+def _pinned(H, L):
+    m = H.export_maps(L)
+    K = H.export_element_matrices(L).cpu().numpy()
+    en = m["elem_nodes"].cpu().numpy()
+    D, n = H.d, H.n_n(L)
+    dof = (en[:, :, None] * D + np.arange(D)).reshape(en.shape[0], -1)
+    A = np.zeros((n * D, n * D))
+    np.add.at(A, (dof[:, :, None], dof[:, None, :]), K)
+    return A[D:, D:]
+
+
+def _column(H, j):
+    n = H.n_n(H.L)
+    f = np.zeros((n, H.c, H.d))
+    f[j // H.d, 0, j % H.d] = 1.0
+    return H.coarse_solve(torch.as_tensor(f, device=DEV)).cpu().numpy()[:, 0, :].reshape(-1)
+
+
+def test_coarsest_size_limit():
+    """2048 rows are accepted, more are refused before any work on them."""
+    B = _gmt()
+    vox = np.zeros((13, 13, 13), dtype=np.uint8)
+    vox[:, :, :12] = 1  # 13^3 = 2197 nodes
+    with pytest.raises(B.GmtError) as ei:
+        B.Hierarchy(vox, 1, "thermal")
+    assert ei.value.status == B.GMT_E_INVAL and "2197 DOFs" in str(ei.value)
