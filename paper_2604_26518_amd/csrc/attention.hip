@@ -449,8 +449,9 @@ void attention_serialize(const int* node_map, int N, int n, int view, int* order
   hipLaunchKernelGGL(k_morton_flags, dim3(blocks(ncode)), dim3(kThreads), 0, s, ncode, view, bits, N, node_map,
                      flags);
   GMT_LAUNCH_CHECK();
-  const int64_t cnt = scan_compact(flags, ncode, map, codes, scr, total, s);
+  const int64_t cnt = scan_count(flags, ncode, scr, total, s);
   if (cnt != n) fail(GMT_E_STATE, "serialization found %lld of %d nodes", (long long)cnt, n);
+  scan_write(flags, ncode, map, codes, scr, s);
   hipLaunchKernelGGL(k_morton_order, dim3(blocks(n)), dim3(kThreads), 0, s, n, codes, view, bits, N, node_map, order,
                      inv, ser_lin);
   GMT_LAUNCH_CHECK();

@@ -257,8 +257,10 @@ void launch_voxel_elem_flags(const uint8_t* vox, size_t n, int* flags, hipStream
 void launch_node_flags(const int* elem_map_or_flags, int N, int* node_flags, hipStream_t s);
 void launch_coarsen_flags(const int* fine_elem_map, int Nf, int* coarse_flags, uint8_t* dense_cmask,
                           hipStream_t s);
-int64_t scan_compact(const int* flags, size_t n, int* map_out, int* lin_out, int* scratch_blocks,
-                     int* d_total, hipStream_t s);
+// number of flagged items (synchronizes s), then the map (id or -1) and list (id ->
+// index, nullable) of the same flags from the scratch scan_count left
+int64_t scan_count(const int* flags, size_t n, int* scratch_blocks, int* d_total, hipStream_t s);
+void scan_write(const int* flags, size_t n, int* map_out, int* lin_out, const int* scratch_blocks, hipStream_t s);
 size_t scan_scratch_ints(size_t n);
 void launch_occ8(const int* node_lin, int n_n, const int* elem_map, int N, uint8_t* occ8,
                  hipStream_t s);
@@ -267,10 +269,10 @@ void launch_run_flags(const int* interior, int n_int, const int* node_lin, int N
 // Tables of the staged interior sweep of level 1 (see LevelView::st_*): pass 0
 // writes the distinct-id count of every group of nb interior nodes to
 // cnt, pass 1 (for the n_blk groups blk[], offsets per group) the ids and the
-// slot table.
+// slot table.  route: an int of scratch per group, kept from pass 0 to pass 1.
 void launch_stage_tables(const int* interior, int n_int, const int* node_lin, const int* node_map, int N, int nb,
                          int pass, const int* blk, int n_blk, int* cnt, const long long* off, int* ids, uint16_t* slot,
-                         hipStream_t s);
+                         int* route, hipStream_t s);
 // out = the interior ids of the groups (nb positions each) blk[0 .. n_blk)
 void launch_gather_blocks(const int* interior, int n_int, int nb, const int* blk, int n_blk, int* out, hipStream_t s);
 void launch_boundary_nbrs(const int* boundary, int n_bnd, const int* node_lin, const int* node_map, int N, int* table,

@@ -1242,11 +1242,11 @@ static void build(Hier& h, const uint8_t* vox, hipStream_t s, const double* rho 
     } else {
       launch_coarsen_flags(h.lv[l - 1].elem_map, h.lv[l - 1].N, flags, dmask, s);
     }
-    const int64_t ne = scan_compact(flags, nl3, nullptr, nullptr, scr, d_total, s);
+    const int64_t ne = scan_count(flags, nl3, scr, d_total, s);
     if (ne == 0) fail(GMT_E_INVAL, "empty active set");
     d.n_e = (int)ne;
     d.elem_lin = h.alloc<int>(ne);
-    scan_compact(flags, nl3, d.elem_map, d.elem_lin, scr, d_total, s);
+    scan_write(flags, nl3, d.elem_map, d.elem_lin, scr, s);
     if (l == 0) {
       // one rigid body: every solid voxel reachable through shared nodes (the
       // flags buffer holds the union-find parents of the n_e elements)
@@ -1259,10 +1259,10 @@ static void build(Hier& h, const uint8_t* vox, hipStream_t s, const double* rho 
              ncomp);
     }
     launch_node_flags(d.elem_map, d.N, flags, s);
-    const int64_t nn = scan_compact(flags, nl3, nullptr, nullptr, scr, d_total, s);
+    const int64_t nn = scan_count(flags, nl3, scr, d_total, s);
     d.n_n = (int)nn;
     d.node_lin = h.alloc<int>(nn);
-    scan_compact(flags, nl3, d.node_map, d.node_lin, scr, d_total, s);
+    scan_write(flags, nl3, d.node_map, d.node_lin, scr, s);
     d.occ8 = h.alloc<uint8_t>(nn);
     launch_occ8(d.node_lin, d.n_n, d.elem_map, d.N, d.occ8, s);
     if (l >= 1) {
@@ -1300,9 +1300,9 @@ static void build(Hier& h, const uint8_t* vox, hipStream_t s, const double* rho 
     }
     for (int full = 1; full >= 0 && !h.density; --full) {
       launch_occ_flags(d.occ8, d.n_n, full, flags, s);
-      const int64_t cnt = scan_compact(flags, d.n_n, nullptr, nullptr, scr, d_total, s);
+      const int64_t cnt = scan_count(flags, d.n_n, scr, d_total, s);
       int* list = cnt > 0 ? h.alloc<int>(cnt) : nullptr;
-      if (cnt > 0) scan_compact(flags, d.n_n, tmpmap, list, scr, d_total, s);
+      if (cnt > 0) scan_write(flags, d.n_n, tmpmap, list, scr, s);
       if (full) {
         d.interior = list;
         d.n_int = (int)cnt;
@@ -1314,9 +1314,9 @@ static void build(Hier& h, const uint8_t* vox, hipStream_t s, const double* rho 
     // runs of consecutive interior nodes along x (chunks of at most kRun)
     if (d.n_int > 0) {
       launch_run_flags(d.interior, d.n_int, d.node_lin, d.N, flags, s);
-      const int64_t nr = scan_compact(flags, d.n_int, nullptr, nullptr, scr, d_total, s);
+      const int64_t nr = scan_count(flags, d.n_int, scr, d_total, s);
       d.runs = h.alloc<int>(nr + 1);
-      scan_compact(flags, d.n_int, tmpmap, d.runs, scr, d_total, s);
+      scan_write(flags, d.n_int, tmpmap, d.runs, scr, s);
       const int sentinel = d.n_int;
       GMT_HIP(hipMemcpyAsync(d.runs + nr, &sentinel, sizeof(int), hipMemcpyHostToDevice, s));
       d.n_runs = (int)nr;
@@ -1341,9 +1341,10 @@ static void build(Hier& h, const uint8_t* vox, hipStream_t s, const double* rho 
         if (*ec && std::atoi(ec) > 0) cap32 = std::min(cap32, std::atoi(ec)), cap64 = std::min(cap64, std::atoi(ec));
       d.st_nodes = nb;
       const int nblk = (d.n_int + nb - 1) / nb;
-      int* cnt = h.alloc<int>(nblk);
+      int* cnt = h.alloc<int>(2 * (size_t)nblk);
+      int* route = cnt + nblk;
       launch_stage_tables(d.interior, d.n_int, d.node_lin, d.node_map, d.N, nb, 0, nullptr, 0, cnt, nullptr, nullptr,
-                          nullptr, s);
+                          nullptr, route, s);
       std::vector<int> hc(nblk);
       GMT_HIP(hipMemcpyAsync(hc.data(), cnt, nblk * sizeof(int), hipMemcpyDeviceToHost, s));
       GMT_HIP(hipStreamSynchronize(s));
@@ -1363,7 +1364,7 @@ static void build(Hier& h, const uint8_t* vox, hipStream_t s, const double* rho 
         GMT_HIP(hipMemcpyAsync(g32, good[0].data(), good[0].size() * sizeof(int), hipMemcpyHostToDevice, s));
         GMT_HIP(hipMemcpyAsync(d.st_off, ho.data(), ho.size() * sizeof(long long), hipMemcpyHostToDevice, s));
         launch_stage_tables(d.interior, d.n_int, d.node_lin, d.node_map, d.N, nb, 1, g32, (int)good[0].size(), cnt,
-                            d.st_off, d.st_ids, d.st_slot, s);
+                            d.st_off, d.st_ids, d.st_slot, route, s);
         d.st_blk32 = g32;
         d.n_st_blk32 = (int)good[0].size();
         if (!good[1].empty()) {

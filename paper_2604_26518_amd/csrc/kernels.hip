@@ -1585,203 +1585,6 @@ __global__ void k_coarsen(const int* __restrict__ femap, int Nf, int* __restrict
   dcmask[i] = (uint8_t)m;
 }
 
-// --- scan: 256 threads x 16 items per block
-constexpr int kScanItems = 16;
-constexpr int kScanTile = kBlock * kScanItems;
-
-// The same for NT threads, with the NT / 64 wave sums in the caller's LDS
-// (free at the call; it is free again when the function returns).
-template <int NT>
-__device__ int block_exclusive_scan_n(int v, int* total, int* wsum) {
-  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  int incl = v;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    int tt = __shfl_up(incl, o, 64);
-    if (lane >= o) incl += tt;
-  }
-  if (lane == 63) wsum[wid] = incl;
-  __syncthreads();
-  int off = 0, tot = 0;
-#pragma unroll
-  for (int w = 0; w < NT / 64; ++w) {
-    if (w < wid) off += wsum[w];
-    tot += wsum[w];
-  }
-  __syncthreads();
-  *total = tot;
-  return off + incl - v;
-}
-
-__device__ int block_exclusive_scan(int v, int* total) {
-  __shared__ int wsum[kBlock / 64];
-  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  int incl = v;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    int tt = __shfl_up(incl, o, 64);
-    if (lane >= o) incl += tt;
-  }
-  if (lane == 63) wsum[wid] = incl;
-  __syncthreads();
-  int off = 0, tot = 0;
-#pragma unroll
-  for (int w = 0; w < kBlock / 64; ++w) {
-    if (w < wid) off += wsum[w];
-    tot += wsum[w];
-  }
-  __syncthreads();
-  *total = tot;
-  return off + incl - v;
-}
-
-__global__ void k_scan_reduce(const int* __restrict__ flags, size_t n, int* __restrict__ bsum) {
-  const size_t base = (size_t)blockIdx.x * kScanTile;
-  int s = 0;
-#pragma unroll
-  for (int k = 0; k < kScanItems; ++k) {
-    size_t i = base + (size_t)k * kBlock + threadIdx.x;
-    if (i < n) s += flags[i];
-  }
-  int tot;
-  block_exclusive_scan(s, &tot);
-  if (threadIdx.x == 0) bsum[blockIdx.x] = tot;
-}
-
-// exclusive scan of nb block sums by one block; total -> *d_total
-__global__ void k_scan_top(int* __restrict__ bsum, int nb, int* __restrict__ d_total) {
-  __shared__ int carry;
-  if (threadIdx.x == 0) carry = 0;
-  __syncthreads();
-  for (int base = 0; base < nb; base += kBlock) {
-    const int i = base + threadIdx.x;
-    const int v = i < nb ? bsum[i] : 0;
-    int tot;
-    const int ex = block_exclusive_scan(v, &tot);
-    const int c0 = carry;
-    if (i < nb) bsum[i] = c0 + ex;
-    __syncthreads();
-    if (threadIdx.x == 0) carry = c0 + tot;
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) *d_total = carry;
-}
-
-// Tables of the staged interior sweep, one workgroup per 256 interior nodes:
-// the 27 x 256 neighbour ids are sorted in LDS (bitonic), the distinct ones
-// counted (pass 0, every workgroup b: cnt[b]) or, for the workgroups
-// b = blk[g] the staged sweep takes, written out ascending at off[g] together
-// with each node's 27 positions among them (pass 1: binary search).
-template <int NB>
-__global__ __launch_bounds__(NB) void k_stage_tables(const int* __restrict__ interior, int n_int,
-                                                         const int* __restrict__ node_lin,
-                                                         const int* __restrict__ node_map, int N, int pass,
-                                                         const int* __restrict__ blk, int* __restrict__ cnt,
-                                                         const long long* __restrict__ off, int* __restrict__ ids,
-                                                         uint16_t* __restrict__ slot) {
-  constexpr int kStageNodes = NB;
-  constexpr int kStageSort = NB == 256 ? 8192 : 16384;  // >= 27 * NB, a power of two
-  constexpr int kStageItems = kStageSort / NB;
-  static_assert(27 * NB <= kStageSort, "sort buffer too small");
-  __shared__ int s[kStageSort];
-  const int g = blockIdx.x;
-  const int b = pass == 0 ? g : blk[g];
-  const int t = b * kStageNodes + (int)threadIdx.x;
-  const bool valid = t < n_int;
-  int nb[27];
-  if (valid) {
-    const int lin = node_lin[interior[t]];
-    neighbour_ids<true>(node_map, N, lin % N, (lin / N) % N, lin / (N * N), nb);
-  }
-#pragma unroll
-  for (int j = 0; j < 27; ++j) s[(int)threadIdx.x * 27 + j] = valid ? nb[j] : INT_MAX;
-  for (int k = 27 * kStageNodes + (int)threadIdx.x; k < kStageSort; k += kStageNodes) s[k] = INT_MAX;
-  __syncthreads();
-  for (int size = 2; size <= kStageSort; size <<= 1) {
-    for (int stride = size >> 1; stride > 0; stride >>= 1) {
-      for (int p = (int)threadIdx.x; p < kStageSort / 2; p += kStageNodes) {
-        const int lo = 2 * p - (p & (stride - 1));  // the partner index lo + stride has that bit set
-        const int hi = lo + stride;
-        const int a = s[lo], c = s[hi];
-        if ((a > c) == ((lo & size) == 0)) {
-          s[lo] = c;
-          s[hi] = a;
-        }
-      }
-      __syncthreads();
-    }
-  }
-  // distinct values: thread k owns the sorted entries k * kStageItems ..
-  int v[kStageItems];
-  int m = 0;
-  const int base = (int)threadIdx.x * kStageItems;
-#pragma unroll
-  for (int k = 0; k < kStageItems; ++k) {
-    v[k] = s[base + k];
-    const int prev = base + k > 0 ? s[base + k - 1] : INT_MIN;
-    if (v[k] == INT_MAX || v[k] == prev) v[k] = -1;  // not the first of its value
-    m += v[k] >= 0;
-  }
-  int total;
-  __syncthreads();  // every read of s above is done: its first words hold the wave sums
-  int pos = block_exclusive_scan_n<kStageNodes>(m, &total, s);
-  if (pass == 0) {
-    if (threadIdx.x == 0) cnt[b] = total;
-    return;
-  }
-  const long long o0 = off[b];
-#pragma unroll
-  for (int k = 0; k < kStageItems; ++k)
-    if (v[k] >= 0) {
-      s[pos] = v[k];
-      ids[o0 + pos] = v[k];
-      ++pos;
-    }
-  __syncthreads();
-  if (!valid) return;
-  uint16_t* row = slot + (size_t)t * kSlotStride;
-#pragma unroll
-  for (int j = 0; j < 27; ++j) {
-    int lo = 0, hi = total;  // first position with s[pos] >= nb[j]
-    while (lo < hi) {
-      const int mid = (lo + hi) >> 1;
-      if (s[mid] < nb[j]) lo = mid + 1;
-      else hi = mid;
-    }
-    row[j] = (uint16_t)lo;
-  }
-  row[27] = 0;
-}
-
-// per block: ids of the flagged items in linear order; map (id or -1), lin (id -> index)
-__global__ void k_scan_compact(const int* __restrict__ flags, size_t n, const int* __restrict__ boff,
-                               int* __restrict__ map, int* __restrict__ lin) {
-  const size_t base = (size_t)blockIdx.x * kScanTile + (size_t)threadIdx.x * kScanItems;
-  int v[kScanItems];
-  int s = 0;
-#pragma unroll
-  for (int k = 0; k < kScanItems; ++k) {
-    size_t i = base + k;
-    v[k] = i < n ? flags[i] : 0;
-    s += v[k];
-  }
-  int tot;
-  int off = block_exclusive_scan(s, &tot) + boff[blockIdx.x];
-#pragma unroll
-  for (int k = 0; k < kScanItems; ++k) {
-    size_t i = base + k;
-    if (i < n) {
-      if (v[k]) {
-        map[i] = off;
-        if (lin) lin[off] = (int)i;
-        ++off;
-      } else {
-        map[i] = -1;
-      }
-    }
-  }
-}
-
 __global__ void k_occ8(const int* __restrict__ node_lin, int n_n, const int* __restrict__ emap, int N,
                        uint8_t* __restrict__ occ8) {
   const int i = blockIdx.x * kBlock + threadIdx.x;
@@ -2149,71 +1952,6 @@ __global__ void k_gs_update(const int* __restrict__ list, int n_list, int n, int
   u[idx] += omega * dinv[(size_t)i * D + q] * r[idx];
 }
 
-// ---------------------------------------------------------------- connected components
-// Union-find over the active elements of level 1 with lock-free hooking (the
-// scheme of Jaiganesh and Burtscher's ECL-CC): every element points to an
-// element of smaller id in its set (parent[v] <= v), a root to itself; a union
-// hooks the larger of the two roots under the smaller one by compare-and-swap
-// and retries from the value it found when another thread hooked that root
-// first.  Ids only decrease along every chain, so each loop ends.
-__device__ __forceinline__ int cc_load(const int* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// root of v's set, shortening the chain on the way (each element is pointed
-// past its parent to its grandparent, which is also in the set)
-__device__ int cc_root(int* parent, int v) {
-  int cur = cc_load(parent + v);
-  if (cur != v) {
-    int prev = v, next;
-    while (cur > (next = cc_load(parent + cur))) {
-      __hip_atomic_store(parent + prev, next, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      prev = cur;
-      cur = next;
-    }
-  }
-  return cur;
-}
-
-__global__ void k_cc_init(int* __restrict__ parent, int n_e) {
-  const int v = blockIdx.x * kBlock + threadIdx.x;
-  if (v < n_e) parent[v] = v;
-}
-
-// element v is joined to every active element among its 26 periodic
-// neighbours (all of them share at least one node with v)
-__global__ void k_cc_hook(const int* __restrict__ elem_lin, int n_e, const int* __restrict__ elem_map, int N,
-                          int* parent) {
-  const int v = blockIdx.x * kBlock + threadIdx.x;
-  if (v >= n_e) return;
-  const int lin = elem_lin[v];
-  const int x = lin % N, y = (lin / N) % N, z = lin / (N * N);
-  for (int j = 0; j < 27; ++j) {
-    if (j == 13) continue;
-    const int w = elem_map[wrapm(x + j % 3 - 1, N) + N * (wrapm(y + (j / 3) % 3 - 1, N) + N * wrapm(z + j / 9 - 1, N))];
-    if (w < 0 || w == v) continue;
-    int a = cc_root(parent, v), b = cc_root(parent, w);
-    while (a != b) {
-      if (a < b) {
-        const int got = atomicCAS(parent + b, b, a);
-        if (got == b) break;
-        b = got;  // b was hooked meanwhile: continue from its new parent (smaller)
-      } else {
-        const int got = atomicCAS(parent + a, a, b);
-        if (got == a) break;
-        a = got;
-      }
-    }
-  }
-}
-
-__global__ void k_cc_count(const int* __restrict__ parent, int n_e, int* __restrict__ count) {
-  const int v = blockIdx.x * kBlock + threadIdx.x;
-  const bool root = v < n_e && parent[v] == v;
-  const unsigned long long m = __ballot(root);
-  if ((threadIdx.x & 63) == 0 && m) atomicAdd(count, __popcll(m));
-}
-
 }  // namespace
 
 // ================================================================ launchers
@@ -2428,23 +2166,6 @@ void launch_gs_update(const int* list, int n_list, int n, int D, int C, const T*
   hipLaunchKernelGGL(k_gs_update<T>, dim3(blocks_for((size_t)n_list * D), C), dim3(kBlock), 0, s, list, n_list, n, D,
                      dinv, r, u, omega);
   GMT_LAUNCH_CHECK();
-}
-
-int count_components(const int* elem_lin, int n_e, const int* elem_map, int N, int* parent, int* d_count,
-                     hipStream_t s) {
-  if (n_e <= 0) return 0;
-  const unsigned g = blocks_for(n_e);
-  hipLaunchKernelGGL(k_cc_init, dim3(g), dim3(kBlock), 0, s, parent, n_e);
-  GMT_LAUNCH_CHECK();
-  hipLaunchKernelGGL(k_cc_hook, dim3(g), dim3(kBlock), 0, s, elem_lin, n_e, elem_map, N, parent);
-  GMT_LAUNCH_CHECK();
-  GMT_HIP(hipMemsetAsync(d_count, 0, sizeof(int), s));
-  hipLaunchKernelGGL(k_cc_count, dim3(g), dim3(kBlock), 0, s, parent, n_e, d_count);
-  GMT_LAUNCH_CHECK();
-  int h = 0;
-  GMT_HIP(hipMemcpyAsync(&h, d_count, sizeof(int), hipMemcpyDeviceToHost, s));
-  GMT_HIP(hipStreamSynchronize(s));
-  return h;
 }
 
 static unsigned red_grid(int n) {
@@ -2665,25 +2386,6 @@ void launch_coarsen_flags(const int* femap, int Nf, int* cflags, uint8_t* dcmask
   GMT_LAUNCH_CHECK();
 }
 
-size_t scan_scratch_ints(size_t n) { return (n + kScanTile - 1) / kScanTile + 1; }
-
-int64_t scan_compact(const int* flags, size_t n, int* map_out, int* lin_out, int* scratch, int* d_total,
-                     hipStream_t s) {
-  const unsigned nb = (unsigned)((n + kScanTile - 1) / kScanTile);
-  hipLaunchKernelGGL(k_scan_reduce, dim3(nb), dim3(kBlock), 0, s, flags, n, scratch);
-  GMT_LAUNCH_CHECK();
-  hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(kBlock), 0, s, scratch, (int)nb, d_total);
-  GMT_LAUNCH_CHECK();
-  int total = 0;
-  GMT_HIP(hipMemcpyAsync(&total, d_total, sizeof(int), hipMemcpyDeviceToHost, s));
-  GMT_HIP(hipStreamSynchronize(s));
-  if (map_out) {
-    hipLaunchKernelGGL(k_scan_compact, dim3(nb), dim3(kBlock), 0, s, flags, n, scratch, map_out, lin_out);
-    GMT_LAUNCH_CHECK();
-  }
-  return total;
-}
-
 void launch_occ8(const int* node_lin, int n_n, const int* emap, int N, uint8_t* occ8, hipStream_t s) {
   if (!n_n) return;
   hipLaunchKernelGGL(k_occ8, dim3(blocks_for(n_n)), dim3(kBlock), 0, s, node_lin, n_n, emap, N, occ8);
@@ -2701,20 +2403,6 @@ void launch_boundary_nbrs(const int* boundary, int n_bnd, const int* node_lin, c
 void launch_run_flags(const int* interior, int n_int, const int* node_lin, int N, int* flags, hipStream_t s) {
   if (!n_int) return;
   hipLaunchKernelGGL(k_run_flags, dim3(blocks_for(n_int)), dim3(kBlock), 0, s, interior, n_int, node_lin, N, flags);
-  GMT_LAUNCH_CHECK();
-}
-
-void launch_stage_tables(const int* interior, int n_int, const int* node_lin, const int* node_map, int N, int nb,
-                         int pass, const int* blk, int n_blk, int* cnt, const long long* off, int* ids, uint16_t* slot,
-                         hipStream_t s) {
-  const unsigned grid = pass == 0 ? (unsigned)((n_int + nb - 1) / nb) : (unsigned)n_blk;
-  if (!n_int || !grid) return;
-  if (nb == 512)
-    hipLaunchKernelGGL(k_stage_tables<512>, dim3(grid), dim3(512), 0, s, interior, n_int, node_lin, node_map, N, pass,
-                       blk, cnt, off, ids, slot);
-  else
-    hipLaunchKernelGGL(k_stage_tables<256>, dim3(grid), dim3(256), 0, s, interior, n_int, node_lin, node_map, N, pass,
-                       blk, cnt, off, ids, slot);
   GMT_LAUNCH_CHECK();
 }
 

@@ -1,12 +1,14 @@
 """GPU parity of the hierarchy build's kernels at the sizes where they can go wrong: the inverse of
-the pinned coarsest operator (tile and panel remainders, the smallest and largest matrices)."""
+the pinned coarsest operator (tile and panel remainders, the smallest and largest matrices), the
+staged sweep's tables (periodic wraps, both routes), the component count (runs across the period)."""
 
 import numpy as np
 import pytest
 
 torch = pytest.importorskip("torch")
 
-from gmt_inputs import gyroid_sheet, uniform  # noqa: E402
+from gmt_inputs import gyroid_sheet, laminate, uniform  # noqa: E402
+from oracle import hierarchy as ohier  # noqa: E402
 from oracle import solve as osolve  # noqa: E402
 
 pytestmark = pytest.mark.gpu
@@ -84,3 +86,46 @@ def test_coarsest_size_limit():
     with pytest.raises(B.GmtError) as ei:
         B.Hierarchy(vox, 1, "thermal")
     assert ei.value.status == B.GMT_E_INVAL and "2197 DOFs" in str(ei.value)
+
+
+@pytest.mark.parametrize("nodes", [256, 512])
+@pytest.mark.parametrize("case", ["uniform4", "uniform18", "gyroid32", "laminate20"])
+def test_stage_tables_routes(case, nodes, monkeypatch):
+    """The staged sweep's tables from the bitmap and from the sorted groups are the same: the residual
+    is bit for bit the same, with every group on one route, on the other, and with the bitmap too small
+    for some groups only; and it is the plain interior sweep's (same products, same order)."""
+    vox = {"uniform4": uniform(4), "uniform18": uniform(18), "gyroid32": gyroid_sheet(32, 0, 0.5),
+           "laminate20": laminate(20, 7, axis=0)}[case]
+    monkeypatch.setenv("GMT_STAGE_NODES", str(nodes))
+    got = []
+    for words in ("4096", "0", "40"):
+        monkeypatch.setenv("GMT_STAGE_WORDS", words)
+        H = _gmt().Hierarchy(vox, 4 if case == "gyroid32" else 2, "thermal" if case == "uniform18" else "elastic")
+        u = torch.as_tensor(np.random.default_rng(3).standard_normal((H.n_n(), H.c, H.d)), device=DEV)
+        for dt in (torch.float64, torch.float32):
+            monkeypatch.setenv("GMT_FORCE_L1_VARIANT", "9")
+            got.append(H.residual(H.load_vector(dt), u.to(dt)))
+            monkeypatch.setenv("GMT_FORCE_L1_VARIANT", "7")
+            assert torch.equal(got[-1], H.residual(H.load_vector(dt), u.to(dt)))
+    for k in (2, 3, 4, 5):
+        assert torch.equal(got[k], got[k % 2])
+
+
+@pytest.mark.parametrize("N,L,fill", [(2, 1, 0.4), (5, 1, 0.1), (9, 1, 0.06), (18, 2, 0.03), (18, 2, 0.3), (64, 4, 0.04)])
+def test_component_count(N, L, fill):
+    """Random cells, each also with whole x-rows of voxels (runs that close on themselves)."""
+    B = _gmt()
+    for seed in range(4):
+        rng = np.random.default_rng(seed)
+        vox = (rng.random((N, N, N)) < fill).astype(np.uint8)
+        if seed % 2:
+            vox[rng.integers(N), rng.integers(N), :] = 1
+        vox[0, 0, 0] = 1
+        want = ohier.node_components(vox)
+        try:
+            B.Hierarchy(vox, L, "thermal").close()
+            message = ""
+        except B.GmtError as e:
+            message = str(e)
+        assert (f"form {want} node-connected components" in message) == (want != 1), (N, fill, seed, want, message)
+        assert want != 1 or "components" not in message
