@@ -1618,6 +1618,13 @@ static void build(Hier& h, const uint8_t* vox, hipStream_t s, const double* rho 
     }
   }
   timer.mark("lambda+coarse");
+  // Level-1 launch shape until a solve or cycle times the candidates (the operator
+  // entry points never do): the staged interior, or in a density hierarchy all cases
+  // per boundary thread.  Fastest or level with the fastest on every shape timed:
+  // residual of 8.7 M nodes, 6 cases: FP64 2.78 ms (cb 7: 3.55, cb 0: 4.35), FP32 1.84
+  // (2.20, 2.70); of 14.5 k nodes: FP64 36 us (44, 88), FP32 27 us (27, 65); density
+  // K.u at 64^3: FP64 91 us (cb 7: 107), FP32 53 us (61).
+  h.lv[0].cb32 = h.lv[0].cb64 = h.density ? 8 : 9;
   GMT_HIP(hipStreamSynchronize(s));
   for (void* b : pw) h.release(b);
   h.release(flags);

@@ -1195,29 +1195,6 @@ __global__ __launch_bounds__(64 * kCoarseSplit) void k_coarse_solve(const T* __r
   for (int c = 0; c < C; ++c) u[vix(c, n, node, D, q)] = (T)acc[c];
 }
 
-// Layout changes between the ABI's [n][Q] and the solver's [Q][n].
-// ABI [n][C][D] -> solver [C][n][D]
-template <typename Tin, typename Tout>
-__global__ void k_aos_to_soa(const Tin* __restrict__ a, Tout* __restrict__ b, int n, int C, int D) {
-  const size_t idx = (size_t)blockIdx.x * kBlock + threadIdx.x;  // index into b
-  if (idx >= (size_t)n * C * D) return;
-  const int d = (int)(idx % D);
-  const size_t t = idx / D;
-  const size_t i = t % n, c = t / n;
-  b[idx] = (Tout)a[(i * C + c) * D + d];
-}
-
-// solver [C][n][D] -> ABI [n][C][D]
-template <typename Tin, typename Tout>
-__global__ void k_soa_to_aos(const Tin* __restrict__ a, Tout* __restrict__ b, int n, int C, int D) {
-  const size_t idx = (size_t)blockIdx.x * kBlock + threadIdx.x;  // index into b
-  if (idx >= (size_t)n * C * D) return;
-  const int d = (int)(idx % D);
-  const size_t t = idx / D;
-  const size_t c = t % C, i = t / C;
-  b[idx] = (Tout)a[(c * n + i) * D + d];
-}
-
 // ---------------------------------------------------------------- vector kernels
 
 template <typename T>
@@ -2321,22 +2298,6 @@ void launch_pcg_direction(T* p, const T* z, const double* beta, int n, int Q, in
   GMT_LAUNCH_CHECK();
 }
 
-template <typename Tin, typename Tout>
-void launch_aos_to_soa(const Tin* a, Tout* b, int n, int C, int D, hipStream_t s) {
-  const size_t tot = (size_t)n * C * D;
-  if (!tot) return;
-  hipLaunchKernelGGL((k_aos_to_soa<Tin, Tout>), dim3(blocks_for(tot)), dim3(kBlock), 0, s, a, b, n, C, D);
-  GMT_LAUNCH_CHECK();
-}
-
-template <typename Tin, typename Tout>
-void launch_soa_to_aos(const Tin* a, Tout* b, int n, int C, int D, hipStream_t s) {
-  const size_t tot = (size_t)n * C * D;
-  if (!tot) return;
-  hipLaunchKernelGGL((k_soa_to_aos<Tin, Tout>), dim3(blocks_for(tot)), dim3(kBlock), 0, s, a, b, n, C, D);
-  GMT_LAUNCH_CHECK();
-}
-
 void launch_pcg_alpha(const double* rz, const double* pq, double* alpha, int C, hipStream_t s, const double* stop) {
   hipLaunchKernelGGL(k_pcg_alpha, dim3(1), dim3(64), 0, s, rz, pq, alpha, C, stop);
   GMT_LAUNCH_CHECK();
@@ -2597,8 +2558,6 @@ void launch_random(double* x, size_t n, uint64_t seed, hipStream_t s) {
                                         double);                                                               \
   template void launch_dot_centered<T>(const T*, const T*, const double*, double, int, int, int, double*, double*, \
                                        hipStream_t);                                                           \
-  template void launch_aos_to_soa<T, T>(const T*, T*, int, int, int, hipStream_t);                           \
-  template void launch_soa_to_aos<T, T>(const T*, T*, int, int, int, hipStream_t);                           \
   template void launch_gauge_shift<T>(T*, int, int, int, T*, hipStream_t);                                   \
   template void launch_project<T>(T*, int, int, int, double*, double*, hipStream_t);                          \
   template void launch_colsum<T>(const T*, int, int, int, double*, double*, hipStream_t);                     \
@@ -2612,10 +2571,6 @@ void launch_random(double* x, size_t n, uint64_t seed, hipStream_t s) {
 GMT_INST_T(float)
 GMT_INST_T(double)
 template void launch_convert<double, float>(const double*, float*, size_t, hipStream_t);
-template void launch_aos_to_soa<double, float>(const double*, float*, int, int, int, hipStream_t);
-template void launch_aos_to_soa<float, double>(const float*, double*, int, int, int, hipStream_t);
-template void launch_soa_to_aos<double, float>(const double*, float*, int, int, int, hipStream_t);
-template void launch_soa_to_aos<float, double>(const float*, double*, int, int, int, hipStream_t);
 template void launch_convert<float, double>(const float*, double*, size_t, hipStream_t);
 template void launch_gram<double, double>(const double*, const double*, int, int, int, double*, double*,
                                           hipStream_t);
