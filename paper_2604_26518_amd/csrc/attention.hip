@@ -19,10 +19,10 @@
 // integers, (k div 3 + 1) p mod N, so the encoding is exactly periodic.
 //
 // Every tensor of the block is kept in serialization order ("token" i is the
-// node order[i]), so a window is a contiguous run of rows.  One workgroup
-// handles one (window, head) pair; a thread owns kPer queries (forward, dq) or
-// keys (dk, dv) and streams the other side of the window through LDS in chunks
-// of kChunk tokens, so each LDS read serves kPer score evaluations.  The
+// node order[i]), so a window is a contiguous run of rows.  A workgroup takes
+// a (window, head) pair, or one of its `parts`; a thread owns P queries (forward,
+// dq) or keys (dk, dv) and streams the other side of the window through LDS in
+// chunks of kChunk tokens, so each LDS read serves P score evaluations.  The
 // softmax is computed online in base 2 in FP32 against a running offset m that
 // is raised (and the sums rescaled) only when a score exceeds it by more than 8:
 // every term 2^(s - m) stays below 2^8, and the rescaling branch, which a wave
@@ -36,6 +36,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <cstdlib>
 
 #include "common.h"
 
@@ -44,7 +45,7 @@ namespace gmt {
 namespace {
 
 constexpr int kHd = 8;        // head dimension
-constexpr int kPer = 4;       // queries (or keys) per thread
+constexpr int kPer = 4;       // queries (or keys) per thread at most
 constexpr int kChunk = 128;   // tokens of the other side staged in LDS at a time
 constexpr float kSlack = 8.f; // the running offset may trail the maximum score by 2^8
 constexpr int kThreads = 256;
@@ -162,21 +163,24 @@ __global__ void k_morton_order(int n, const int* __restrict__ codes, int view, i
 
 // ---------------------------------------------------------------- forward
 
-// grid (windows, heads), block ceil(W / kPer) threads.  q, k, v, o16: [n][C] BF16,
+// grid (windows * parts, heads), block min(256, ceil(W / P)) threads.  q, k, v, o16: [n][C] BF16,
 // o32 [n][C] FP32, lse [n][C / 8] (base 2, of the scores scaled by log2(e) / sqrt 8).
-__global__ __launch_bounds__(kThreads) void k_attn_fwd(int n, int W, int C, int N, const int* __restrict__ ser_lin,
+template <int P>
+__global__ __launch_bounds__(kThreads) void k_attn_fwd(int n, int W, int C, int N, int parts, const int* __restrict__ ser_lin,
                                                        const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                                                        const uint16_t* __restrict__ v, float* __restrict__ o32,
                                                        uint16_t* __restrict__ o16, float* __restrict__ lse) {
   __shared__ float4 kv[kChunk][4];  // k~ (2 float4), v (2 float4)
   const int h = blockIdx.y, heads = C / kHd;
-  const int w0 = blockIdx.x * W, wn = min(W, n - w0);
+  const int w0 = (int)blockIdx.x / parts * W, wn = min(W, n - w0);
   const int nt = blockDim.x;
+  const int j0 = (int)blockIdx.x % parts * (nt * P);  // first query (or key) of this part
+  if (j0 >= wn) return;
   const float scale = kLog2e * 0.35355339059327373f;  // log2(e) / sqrt(8)
-  float qs[kPer][kHd], acc[kPer][kHd], mx[kPer], l[kPer];
+  float qs[P][kHd], acc[P][kHd], mx[P], l[P];
 #pragma unroll
-  for (int r = 0; r < kPer; ++r) {
-    const int j = threadIdx.x + r * nt;
+  for (int r = 0; r < P; ++r) {
+    const int j = j0 + (int)threadIdx.x + r * nt;
     float c[4], s[4];
     if (j < wn) {
       load_head(q + (size_t)(w0 + j) * C + kHd * h, qs[r]);
@@ -210,28 +214,47 @@ __global__ __launch_bounds__(kThreads) void k_attn_fwd(int n, int W, int C, int 
       kv[j][3] = make_float4(vv[4], vv[5], vv[6], vv[7]);
     }
     __syncthreads();
+    // KB keys' scores first (they do not depend on the running sums), then the
+    // updates key by key: KB P independent dot products in flight per thread
+    constexpr int KB = kPer / P;
+    auto update = [&](int r, float sc, float4 v0, float4 v1) {
+      if (sc > mx[r] + kSlack) {
+        const float f = ex2(mx[r] - sc);
+        l[r] *= f;
+#pragma unroll
+        for (int d = 0; d < kHd; ++d) acc[r][d] *= f;
+        mx[r] = sc;
+      }
+      const float p = ex2(sc - mx[r]);
+      l[r] += p;
+      axpy8(acc[r], p, v0, v1);
+    };
+    int j = 0;
 #pragma unroll 2
-    for (int j = 0; j < cn; ++j) {
+    for (; j + KB <= cn; j += KB) {
+      float sc[KB][P];
+#pragma unroll
+      for (int b = 0; b < KB; ++b) {
+        const float4 k0 = kv[j + b][0], k1 = kv[j + b][1];
+#pragma unroll
+        for (int r = 0; r < P; ++r) sc[b][r] = dot8(qs[r], k0, k1);
+      }
+#pragma unroll
+      for (int b = 0; b < KB; ++b) {
+        const float4 v0 = kv[j + b][2], v1 = kv[j + b][3];
+#pragma unroll
+        for (int r = 0; r < P; ++r) update(r, sc[b][r], v0, v1);
+      }
+    }
+    for (; j < cn; ++j) {
       const float4 k0 = kv[j][0], k1 = kv[j][1], v0 = kv[j][2], v1 = kv[j][3];
 #pragma unroll
-      for (int r = 0; r < kPer; ++r) {
-        const float sc = dot8(qs[r], k0, k1);
-        if (sc > mx[r] + kSlack) {
-          const float f = ex2(mx[r] - sc);
-          l[r] *= f;
-#pragma unroll
-          for (int d = 0; d < kHd; ++d) acc[r][d] *= f;
-          mx[r] = sc;
-        }
-        const float p = ex2(sc - mx[r]);
-        l[r] += p;
-        axpy8(acc[r], p, v0, v1);
-      }
+      for (int r = 0; r < P; ++r) update(r, dot8(qs[r], k0, k1), v0, v1);
     }
   }
 #pragma unroll
-  for (int r = 0; r < kPer; ++r) {
-    const int j = threadIdx.x + r * nt;
+  for (int r = 0; r < P; ++r) {
+    const int j = j0 + (int)threadIdx.x + r * nt;
     if (j >= wn) continue;
     const size_t i = (size_t)(w0 + j);
     const float inv = 1.f / l[r];
@@ -255,8 +278,9 @@ __global__ __launch_bounds__(kThreads) void k_attn_fwd(int n, int W, int C, int 
 //   dk~_j = sum_i dS_ij q~_i,  dv_j = sum_i P_ij go_i,
 // and dq, dk are dq~, dk~ turned back by -theta (the rotation is orthogonal).
 
-// pass A: one thread per kPer queries; keys and values of the window through LDS
-__global__ __launch_bounds__(kThreads) void k_attn_bwd_q(int n, int W, int C, int N, const int* __restrict__ ser_lin,
+// pass A: one thread per P queries; keys and values of the window through LDS
+template <int P>
+__global__ __launch_bounds__(kThreads) void k_attn_bwd_q(int n, int W, int C, int N, int parts, const int* __restrict__ ser_lin,
                                                          const uint16_t* __restrict__ q,
                                                          const uint16_t* __restrict__ k,
                                                          const uint16_t* __restrict__ v,
@@ -265,13 +289,15 @@ __global__ __launch_bounds__(kThreads) void k_attn_bwd_q(int n, int W, int C, in
                                                          const float* __restrict__ go, float* __restrict__ dq) {
   __shared__ float4 kv[kChunk][4];
   const int h = blockIdx.y, heads = C / kHd;
-  const int w0 = blockIdx.x * W, wn = min(W, n - w0);
+  const int w0 = (int)blockIdx.x / parts * W, wn = min(W, n - w0);
   const int nt = blockDim.x;
+  const int j0 = (int)blockIdx.x % parts * (nt * P);  // first query (or key) of this part
+  if (j0 >= wn) return;
   const float scale = kLog2e * 0.35355339059327373f;
-  float qs[kPer][kHd], g[kPer][kHd], acc[kPer][kHd], Dq[kPer], lq[kPer];
+  float qs[P][kHd], g[P][kHd], acc[P][kHd], Dq[P], lq[P];
 #pragma unroll
-  for (int r = 0; r < kPer; ++r) {
-    const int j = threadIdx.x + r * nt;
+  for (int r = 0; r < P; ++r) {
+    const int j = j0 + (int)threadIdx.x + r * nt;
 #pragma unroll
     for (int d = 0; d < kHd; ++d) acc[r][d] = 0.f;
     if (j < wn) {
@@ -316,7 +342,7 @@ __global__ __launch_bounds__(kThreads) void k_attn_bwd_q(int n, int W, int C, in
     for (int j = 0; j < cn; ++j) {
       const float4 k0 = kv[j][0], k1 = kv[j][1], v0 = kv[j][2], v1 = kv[j][3];
 #pragma unroll
-      for (int r = 0; r < kPer; ++r) {
+      for (int r = 0; r < P; ++r) {
         const float p = ex2(dot8(qs[r], k0, k1) - lq[r]);
         const float ds = p * (dot8(g[r], v0, v1) - Dq[r]);
         axpy8(acc[r], ds, k0, k1);
@@ -324,8 +350,8 @@ __global__ __launch_bounds__(kThreads) void k_attn_bwd_q(int n, int W, int C, in
     }
   }
 #pragma unroll
-  for (int r = 0; r < kPer; ++r) {
-    const int j = threadIdx.x + r * nt;
+  for (int r = 0; r < P; ++r) {
+    const int j = j0 + (int)threadIdx.x + r * nt;
     if (j >= wn) continue;
     const size_t i = (size_t)(w0 + j);
     float c[4], s[4];
@@ -337,8 +363,9 @@ __global__ __launch_bounds__(kThreads) void k_attn_bwd_q(int n, int W, int C, in
   }
 }
 
-// pass B: one thread per kPer keys; per query q~ (scaled), go, lse and D through LDS
-__global__ __launch_bounds__(kThreads) void k_attn_bwd_kv(int n, int W, int C, int N,
+// pass B: one thread per P keys; per query q~ (scaled), go, lse and D through LDS
+template <int P>
+__global__ __launch_bounds__(kThreads) void k_attn_bwd_kv(int n, int W, int C, int N, int parts,
                                                           const int* __restrict__ ser_lin,
                                                           const uint16_t* __restrict__ q,
                                                           const uint16_t* __restrict__ k,
@@ -350,13 +377,15 @@ __global__ __launch_bounds__(kThreads) void k_attn_bwd_kv(int n, int W, int C, i
   __shared__ float4 qg[kChunk][4];  // q~ scaled (2 float4), go (2 float4)
   __shared__ float2 ld[kChunk];     // lse, D
   const int h = blockIdx.y, heads = C / kHd;
-  const int w0 = blockIdx.x * W, wn = min(W, n - w0);
+  const int w0 = (int)blockIdx.x / parts * W, wn = min(W, n - w0);
   const int nt = blockDim.x;
+  const int j0 = (int)blockIdx.x % parts * (nt * P);  // first query (or key) of this part
+  if (j0 >= wn) return;
   const float scale = kLog2e * 0.35355339059327373f;
-  float kk[kPer][kHd], vv[kPer][kHd], ak[kPer][kHd], av[kPer][kHd];
+  float kk[P][kHd], vv[P][kHd], ak[P][kHd], av[P][kHd];
 #pragma unroll
-  for (int r = 0; r < kPer; ++r) {
-    const int j = threadIdx.x + r * nt;
+  for (int r = 0; r < P; ++r) {
+    const int j = j0 + (int)threadIdx.x + r * nt;
 #pragma unroll
     for (int d = 0; d < kHd; ++d) ak[r][d] = av[r][d] = 0.f;
     if (j < wn) {
@@ -397,7 +426,7 @@ __global__ __launch_bounds__(kThreads) void k_attn_bwd_kv(int n, int W, int C, i
       const float4 q0 = qg[j][0], q1 = qg[j][1], g0 = qg[j][2], g1 = qg[j][3];
       const float2 lD = ld[j];
 #pragma unroll
-      for (int r = 0; r < kPer; ++r) {
+      for (int r = 0; r < P; ++r) {
         const float p = ex2(dot8(kk[r], q0, q1) - lD.x);
         axpy8(av[r], p, g0, g1);
         const float ds = p * (dot8(vv[r], g0, g1) - lD.y);
@@ -406,8 +435,8 @@ __global__ __launch_bounds__(kThreads) void k_attn_bwd_kv(int n, int W, int C, i
     }
   }
 #pragma unroll
-  for (int r = 0; r < kPer; ++r) {
-    const int j = threadIdx.x + r * nt;
+  for (int r = 0; r < P; ++r) {
+    const int j = j0 + (int)threadIdx.x + r * nt;
     if (j >= wn) continue;
     const size_t i = (size_t)(w0 + j);
     float c[4], s[4];
@@ -463,14 +492,43 @@ void attention_serialize(const int* node_map, int N, int n, int view, int* order
   GMT_HIP(hipFree(total));
 }
 
+// Queries per thread.  A thread with 4 works through its window in 4 W dependent
+// steps, ~200 us for W = 1024 however few windows there are, so levels that would
+// put fewer than two waves on every SIMD that way take 2 or 1 per thread (more
+// LDS reads per score).  Every query's sums keep their order, so the result does
+// not depend on it.  Forward of the six levels of a 128^3 cell: 1.21 ms with 4 on
+// every level, 0.64 ms so.
+struct AttnShape {
+  int per, parts;
+  dim3 grid, block;
+};
+static AttnShape attn_shape(int n, int W, int C) {
+  const long long windows = (n + W - 1) / W, waves = windows * (C / kHd) * ((W + 64 * kPer - 1) / (64 * kPer));
+  AttnShape a;
+  a.per = waves >= 2048 ? 4 : (waves >= 1024 ? 2 : 1);
+  if (const char* e = std::getenv("GMT_ATTN_PER"))  // pins it (tests: the results are the same)
+    if (*e && (std::atoi(e) == 1 || std::atoi(e) == 2 || std::atoi(e) == 4)) a.per = std::atoi(e);
+  const int nt = std::min(kThreads, (W + a.per - 1) / a.per);
+  a.parts = (W + nt * a.per - 1) / (nt * a.per);
+  a.grid = dim3((unsigned)(windows * a.parts), (unsigned)(C / kHd));
+  a.block = dim3((unsigned)nt);
+  return a;
+}
+
+#define GMT_ATTN(kernel, ...)                                                                                       \
+  do {                                                                                                              \
+    const AttnShape a_ = attn_shape(n, W, C);                                                                       \
+    if (a_.per == 4) hipLaunchKernelGGL(kernel<4>, a_.grid, a_.block, 0, s, n, W, C, N, a_.parts, __VA_ARGS__);      \
+    else if (a_.per == 2) hipLaunchKernelGGL(kernel<2>, a_.grid, a_.block, 0, s, n, W, C, N, a_.parts, __VA_ARGS__); \
+    else hipLaunchKernelGGL(kernel<1>, a_.grid, a_.block, 0, s, n, W, C, N, a_.parts, __VA_ARGS__);                  \
+    GMT_LAUNCH_CHECK();                                                                                             \
+  } while (0)
+
 void attention_forward(int n, int W, int C, int N, const int* ser_lin, const uint16_t* q, const uint16_t* k,
                        const uint16_t* v, float* o32, uint16_t* o16, float* lse, hipStream_t s) {
   check_shape(n, W, C);
   if (n == 0) return;
-  const dim3 grid((unsigned)((n + W - 1) / W), (unsigned)(C / kHd));
-  const dim3 block((unsigned)((W + kPer - 1) / kPer));
-  hipLaunchKernelGGL(k_attn_fwd, grid, block, 0, s, n, W, C, N, ser_lin, q, k, v, o32, o16, lse);
-  GMT_LAUNCH_CHECK();
+  GMT_ATTN(k_attn_fwd, ser_lin, q, k, v, o32, o16, lse);
 }
 
 void attention_backward(int n, int W, int C, int N, const int* ser_lin, const uint16_t* q, const uint16_t* k,
@@ -478,12 +536,10 @@ void attention_backward(int n, int W, int C, int N, const int* ser_lin, const ui
                         float* dv, hipStream_t s) {
   check_shape(n, W, C);
   if (n == 0) return;
-  const dim3 grid((unsigned)((n + W - 1) / W), (unsigned)(C / kHd));
-  const dim3 block((unsigned)((W + kPer - 1) / kPer));
-  hipLaunchKernelGGL(k_attn_bwd_q, grid, block, 0, s, n, W, C, N, ser_lin, q, k, v, o32, lse, go, dq);
-  GMT_LAUNCH_CHECK();
-  hipLaunchKernelGGL(k_attn_bwd_kv, grid, block, 0, s, n, W, C, N, ser_lin, q, k, v, o32, lse, go, dk, dv);
-  GMT_LAUNCH_CHECK();
+  GMT_ATTN(k_attn_bwd_q, ser_lin, q, k, v, o32, lse, go, dq);
+  GMT_ATTN(k_attn_bwd_kv, ser_lin, q, k, v, o32, lse, go, dk, dv);
 }
+
+#undef GMT_ATTN
 
 }  // namespace gmt
