@@ -283,6 +283,10 @@ class Hierarchy:
     def vec(self, level: int = 1, dtype=torch.float64, fill=0.0):
         return torch.full((self.n_n(level), self.c, self.d), fill, dtype=dtype, device=self._vox.device)
 
+    def _out(self, level: int = 1, dtype=torch.float64):
+        """A vector that a call writes in full (no fill)."""
+        return torch.empty(self.n_n(level), self.c, self.d, dtype=dtype, device=self._vox.device)
+
     def _v(self, t, level, dtype=None, name="vector"):
         if not isinstance(t, torch.Tensor) or not t.is_cuda:
             raise TypeError(f"{name} must be a CUDA tensor")
@@ -334,7 +338,7 @@ class Hierarchy:
         return D
 
     def load_vector(self, dtype=torch.float64):
-        f = self.vec(1, dtype)
+        f = self._out(1, dtype)
         _check(lib().gmt_load_vector(self._h, _ptr(f), _DT[dtype], _stream()))
         return f
 
@@ -369,7 +373,7 @@ class Hierarchy:
         if level == self.L:
             raise ValueError("no level below the coarsest")
         self._v(rf, level, name="rf")
-        fc = self.vec(level + 1, rf.dtype)
+        fc = self._out(level + 1, rf.dtype)
         _check(lib().gmt_restrict(self._h, level, _ptr(rf), _ptr(fc), _DT[rf.dtype], _stream()))
         return fc
 
@@ -480,7 +484,7 @@ class Hierarchy:
     def nn_forward(self, params):
         """Predictions [u_hat^1, e_hat^2, ..., e_hat^{L-1}] as float32 [n_l][c][d] tensors."""
         self._check_params(params)
-        outs = [self.vec(l, torch.float32) for l in range(1, self.nn_levels)] + [None]
+        outs = [self._out(l, torch.float32) for l in range(1, self.nn_levels)] + [None]
         _check(lib().gmt_nn_forward(self._h, _ptr(params), _ptr_array(outs), _stream()))
         return outs[:-1]
 
@@ -542,7 +546,7 @@ class Hierarchy:
                 self._v(pl[l - 1], l, torch.float32, f"e_hat[{l}]")
         pl[self.L - 1] = None
         o, keep = self._cycle(nu1, nu2, smoother, omega, lo, hi)
-        u1 = self.vec(1, torch.float32) if want_u1 else None
+        u1 = self._out(1, torch.float32) if want_u1 else None
         grads = None
         if want_grad:
             grads = [torch.empty_like(p) if p is not None else None for p in pl[:self.L - 1]] + [None]

@@ -7,14 +7,15 @@
 // node for unpooling; one identity tap for the pointwise head layers).
 // Activations are stored in BF16 (round to nearest even), weights are the BF16
 // rounding of the FP32 master weights, every sum is accumulated in FP32.
-// The backward pass uses the same gather kernel with transposed per-tap
-// weights and the inverse table (mirrored taps on one level, the unpooling
-// table for pooling and vice versa), and a node-chunked reduction for the
-// weight gradients.
+// The backward pass gathers FP32 gradients with transposed per-tap weights and
+// the inverse table (mirrored taps on one level, the unpooling table for pooling
+// and vice versa) on the FP32 matrix cores, and sums the weight gradients over
+// chunks of nodes.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
 #include <cmath>
+#include <cstdlib>
 #include <map>
 #include <mutex>
 #include <vector>
@@ -115,19 +116,28 @@ __global__ __launch_bounds__(kB) void k_gconv(int n, const int* __restrict__ tab
 // accumulators).  Lane l of a 16x16x32 operand holds row/column l % 16 and the
 // 8 consecutive K values 8 (l / 16) .. 8 (l / 16) + 7; the accumulator lane l
 // holds column l % 16 (a node) and rows 4 (l / 16) .. + 3 (four consecutive
-// output channels, one 8-byte store).  A wave computes 4 x 16 nodes, so each
-// weight fragment is loaded once per 64 nodes.
+// output channels, one 8-byte store).
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
-
-constexpr int kMfmaRows = 4;  // 16-node column blocks per wave
 
 __device__ __forceinline__ f32x4_t mfma16(uint4 a, uint4 b, f32x4_t c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b),
                                                  c, 0, 0, 0);
 }
 
-template <typename Tout, int CIN, int COUT, int NTAP, int FLAGS>
+// A wave computes R x 16 nodes and NCW of the 16-channel output blocks
+// (blockIdx.y picks which).  What bounds it is the chain table entry -> gathered
+// row -> matrix instruction, 14 to 54 times in a row with one step in flight: 1.5
+// us a step whatever the level's size.  So the table entries of nine taps (CIN =
+// 16: of all of them) are loaded together, rows and weight fragments are fetched
+// kAhead steps ahead, and every load is unconditional (an absent neighbour reads
+// row 0 and is zeroed by a select), so that the steps of a group are one
+// straight run of code (64 -> 64 layers of a 128^3 cell 80 -> 16 us each, 16 -> 16 on
+// 619 k nodes 154 -> 64 us).  Every accumulator sums the same products in the same
+// order for any R and NCW.
+constexpr int kAhead = 2;
+
+template <typename Tout, int CIN, int COUT, int NTAP, int FLAGS, int R, int NCW>
 __global__ __launch_bounds__(kB) void k_gconv_mfma(int n, const int* __restrict__ tab, const uint16_t* __restrict__ x,
                                                     const uint4* __restrict__ Wm, const float* __restrict__ b,
                                                     const uint16_t* __restrict__ skip, float scale,
@@ -135,32 +145,59 @@ __global__ __launch_bounds__(kB) void k_gconv_mfma(int n, const int* __restrict_
   static_assert(CIN % 16 == 0, "input rows are read 8 channels per lane");
   constexpr int KS = (NTAP * CIN + 31) / 32;  // K steps (the last one zero-padded)
   constexpr int NCB = (COUT + 15) / 16;       // 16-channel output blocks
-  constexpr int R = kMfmaRows;
+  constexpr int GROUPS = NTAP == 27 && CIN > 16 ? 3 : 1;
+  constexpr int SPG = KS / GROUPS;                                // steps per group
+  constexpr int TPL = CIN == 16 ? SPG : (NTAP == 27 ? 9 : 1);     // taps a lane reads per group
+  static_assert(SPG * GROUPS == KS && NCB % NCW == 0, "whole groups and output blocks");
   const int lane = threadIdx.x & 63, col = lane & 15, kb = lane >> 4;
   const int base = (blockIdx.x * (kB / 64) + (threadIdx.x >> 6)) * (16 * R);
+  const int cb0 = blockIdx.y * NCW;
   if (base >= n) return;  // wave-uniform
-  f32x4_t acc[R][NCB];
+  f32x4_t acc[R][NCW];
 #pragma unroll
   for (int r = 0; r < R; ++r)
 #pragma unroll
-    for (int c = 0; c < NCB; ++c) acc[r][c] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    for (int c = 0; c < NCW; ++c) acc[r][c] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll 1
-  for (int s = 0; s < KS; ++s) {
-    const int K0 = 32 * s + 8 * kb;
-    const int t = K0 / CIN, ci0 = K0 % CIN;
-    uint4 xv[R];
+  for (int g = 0; g < GROUPS; ++g) {
+    int src[R][TPL];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
       const int node = base + 16 * r + col;
-      int src = -1;
-      if (node < n && t < NTAP) src = (NTAP == 1 && tab == nullptr) ? node : tab[(size_t)node * NTAP + t];
-      xv[r] = src >= 0 ? *reinterpret_cast<const uint4*>(x + (size_t)src * CIN + ci0) : make_uint4(0u, 0u, 0u, 0u);
+      const int nodec = min(node, n - 1);
+#pragma unroll
+      for (int k = 0; k < TPL; ++k) {
+        const int t = CIN == 16 ? 2 * k + (kb >> 1) : TPL * g + k;
+        int v;
+        if constexpr (NTAP == 1) v = tab ? tab[nodec] : nodec;
+        else v = tab[(size_t)nodec * NTAP + min(t, NTAP - 1)];
+        src[r][k] = node < n && t < NTAP ? v : -1;
+      }
     }
+    uint4 xb[kAhead + 1][R], wb[kAhead + 1][NCW];
+    auto fetch = [&](int s) {  // step s of the group
+      const int ci0 = CIN == 16 ? 8 * (kb & 1) : (CIN == 32 ? 8 * kb : 32 * (s & 1) + 8 * kb);
+      const int k = CIN == 64 ? s / 2 : s;
 #pragma unroll
-    for (int c = 0; c < NCB; ++c) {
-      const uint4 wv = Wm[(size_t)(s * NCB + c) * 64 + lane];
+      for (int r = 0; r < R; ++r)
+        xb[s % (kAhead + 1)][r] = *reinterpret_cast<const uint4*>(x + (size_t)max(src[r][k], 0) * CIN + ci0);
 #pragma unroll
-      for (int r = 0; r < R; ++r) acc[r][c] = mfma16(wv, xv[r], acc[r][c]);
+      for (int c = 0; c < NCW; ++c)
+        wb[s % (kAhead + 1)][c] = Wm[(size_t)((g * SPG + s) * NCB + cb0 + c) * 64 + lane];
+    };
+#pragma unroll
+    for (int s = 0; s < kAhead && s < SPG; ++s) fetch(s);
+#pragma unroll
+    for (int s = 0; s < SPG; ++s) {
+      if (s + kAhead < SPG) fetch(s + kAhead);
+      const int k = CIN == 64 ? s / 2 : s;
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        uint4 v = xb[s % (kAhead + 1)][r];
+        if (src[r][k] < 0) v = make_uint4(0u, 0u, 0u, 0u);
+#pragma unroll
+        for (int c = 0; c < NCW; ++c) acc[r][c] = mfma16(wb[s % (kAhead + 1)][c], v, acc[r][c]);
+      }
     }
   }
 #pragma unroll
@@ -168,8 +205,8 @@ __global__ __launch_bounds__(kB) void k_gconv_mfma(int n, const int* __restrict_
     const int node = base + 16 * r + col;
     if (node >= n) continue;
 #pragma unroll
-    for (int c = 0; c < NCB; ++c) {
-      const int c0 = 16 * c + 4 * kb;
+    for (int c = 0; c < NCW; ++c) {
+      const int c0 = 16 * (cb0 + c) + 4 * kb;
       if (c0 >= COUT) continue;
       float v[4];
 #pragma unroll
@@ -212,8 +249,12 @@ __global__ void k_arrange_mfma(int nlayers, const MfmaLayer* __restrict__ lay, i
                                uint16_t* __restrict__ Wm) {
   const int e = blockIdx.x * kB + threadIdx.x;
   if (e >= total) return;
-  int k = 0;
-  while (k + 1 < nlayers && lay[k + 1].dst <= e) ++k;
+  int k = 0, hi = nlayers;  // the last layer with dst <= e
+  while (hi - k > 1) {
+    const int mid = (k + hi) >> 1;
+    if (lay[mid].dst <= e) k = mid;
+    else hi = mid;
+  }
   const MfmaLayer L = lay[k];
   const int r = e - L.dst;
   const int j = r & 7, lane = (r >> 3) & 63, blk = r >> 9;
@@ -223,6 +264,144 @@ __global__ void k_arrange_mfma(int nlayers, const MfmaLayer* __restrict__ lay, i
   const int t = K / L.cin, ci = K % L.cin;
   const float v = (t < L.ntap && co < L.cout) ? W[L.src + ((size_t)t * L.cin + ci) * L.cout + co] : 0.f;
   Wm[e] = f2bf(v);
+}
+
+// ---------------------------------------------------------------- FP32 MFMA gather convolution (backward)
+__device__ __forceinline__ f32x4_t mfma4(float a, float b, f32x4_t c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+
+// The data gradient y[i][co] = sum_t sum_ci g[tab[i][t]][ci] Wt[t][ci][co] of an FP32
+// gradient, as the same gather-GEMM with v_mfma_f32_16x16x4_f32 (FP32 products and
+// sums).  A lane loads 4 consecutive channels of one neighbour (16 bytes: channels
+// 4 (l / 16) .. + 3 of a 16-channel group) and feeds component j to instruction j,
+// so instruction j sums the channels 4 q + j, q = 0..3; the weights are arranged
+// to match (k_arrange_back: one 16-byte load per 4 instructions).  Loads are
+// unconditional and run kAhead steps ahead, as in the forward kernel.  Bound by the
+// gathered rows on level 1 and by the step latency on the small levels.  The 16 ->
+// 16 layer of 619 k nodes: 370 us on the vector units, 102 us so; the 13 64 -> 64
+// layers of a 128^3 cell: 2.96 ms, 0.40 ms so.
+// Epilogue: D_ACT multiplies by the derivative of the activation stored in ref, D_ADD
+// adds to y.
+enum DFlags { D_ACT = 1, D_ADD = 2 };
+
+template <int CIN, int COUT, int NTAP, int FLAGS, int R, int NCW>
+__global__ __launch_bounds__(kB) void k_dgrad_mfma(int n, const int* __restrict__ tab, const float* __restrict__ g,
+                                                    const float4* __restrict__ Wa, const uint16_t* __restrict__ ref,
+                                                    float* __restrict__ y) {
+  static_assert(CIN % 16 == 0 && COUT % 16 == 0, "channels in groups of 16");
+  constexpr int CG = CIN / 16, NCB = COUT / 16;
+  constexpr int TPG = NTAP == 1 ? 1 : (CIN * NCW * R <= 64 ? 9 : 3);  // taps per group (code size)
+  constexpr int SPG = TPG * CG;                                       // steps per group
+  const int lane = threadIdx.x & 63, col = lane & 15, kb = lane >> 4;
+  const int base = (blockIdx.x * (kB / 64) + (threadIdx.x >> 6)) * (16 * R);
+  const int cb0 = blockIdx.y * NCW;
+  if (base >= n) return;  // wave-uniform
+  f32x4_t acc[R][NCW];
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+#pragma unroll
+    for (int c = 0; c < NCW; ++c) acc[r][c] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+  for (int t0 = 0; t0 < NTAP; t0 += TPG) {
+    int src[R][TPG];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const int node = base + 16 * r + col;
+      const int nodec = min(node, n - 1);
+#pragma unroll
+      for (int k = 0; k < TPG; ++k) {
+        int v;
+        if constexpr (NTAP == 1) v = tab ? tab[nodec] : nodec;
+        else v = tab[(size_t)nodec * NTAP + t0 + k];
+        src[r][k] = node < n ? v : -1;
+      }
+    }
+    float4 xb[kAhead + 1][R], wb[kAhead + 1][NCW];
+    auto fetch = [&](int s) {  // step s of the group: tap t0 + s / CG, channel group s % CG
+      const int k = s / CG, cg = s % CG;
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+        xb[s % (kAhead + 1)][r] =
+            *reinterpret_cast<const float4*>(g + (size_t)max(src[r][k], 0) * CIN + 16 * cg + 4 * kb);
+#pragma unroll
+      for (int c = 0; c < NCW; ++c)
+        wb[s % (kAhead + 1)][c] = Wa[(size_t)((t0 * CG + s) * NCB + cb0 + c) * 64 + lane];
+    };
+#pragma unroll
+    for (int s = 0; s < kAhead && s < SPG; ++s) fetch(s);
+#pragma unroll
+    for (int s = 0; s < SPG; ++s) {
+      if (s + kAhead < SPG) fetch(s + kAhead);
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        float4 v = xb[s % (kAhead + 1)][r];
+        if (src[r][s / CG] < 0) v = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+        for (int c = 0; c < NCW; ++c) {
+          const float4 w = wb[s % (kAhead + 1)][c];
+          acc[r][c] = mfma4(w.x, v.x, acc[r][c]);
+          acc[r][c] = mfma4(w.y, v.y, acc[r][c]);
+          acc[r][c] = mfma4(w.z, v.z, acc[r][c]);
+          acc[r][c] = mfma4(w.w, v.w, acc[r][c]);
+        }
+      }
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int node = base + 16 * r + col;
+    if (node >= n) continue;
+#pragma unroll
+    for (int c = 0; c < NCW; ++c) {
+      const size_t at = (size_t)node * COUT + 16 * (cb0 + c) + 4 * kb;
+      float v[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) v[j] = acc[r][c][j];
+      if constexpr (FLAGS & D_ACT) {
+        const uint2 a = *reinterpret_cast<const uint2*>(ref + at);
+        const uint16_t h[4] = {(uint16_t)a.x, (uint16_t)(a.x >> 16), (uint16_t)a.y, (uint16_t)(a.y >> 16)};
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[j] *= bf2f(h[j]) > 0.f ? 1.f : kSlope;
+      }
+      float4* out = reinterpret_cast<float4*>(y + at);
+      if constexpr (FLAGS & D_ADD) {
+        const float4 o = *out;
+        v[0] = o.x + v[0], v[1] = o.y + v[1], v[2] = o.z + v[2], v[3] = o.w + v[3];
+      }
+      *out = make_float4(v[0], v[1], v[2], v[3]);
+    }
+  }
+}
+
+// The transposed weights of one layer in the A-operand order of k_dgrad_mfma:
+// Wa[(t * cin / 16 + cg) * ncb + cb][lane][j] = W[t'][co][ci] with ci = 16 cg + 4
+// (lane / 16) + j the gradient's channel (the layer's output), co = 16 cb + lane % 16
+// the layer's input channel, and t' = 26 - t where `mirror` (a convolution on one
+// level; the pooling tables are each other's inverse).
+struct BackLayer {
+  int src;  // offset of W [ntap][cout][cin] in the flat parameters
+  int dst;  // offset in the arranged array
+  int ntap, cin, cout, mirror;
+};
+
+__global__ void k_arrange_back(int nlayers, const BackLayer* __restrict__ lay, int total, const float* __restrict__ W,
+                               float* __restrict__ Wa) {
+  const int e = blockIdx.x * kB + threadIdx.x;
+  if (e >= total) return;
+  int k = 0, hi = nlayers;  // the last layer with dst <= e
+  while (hi - k > 1) {
+    const int mid = (k + hi) >> 1;
+    if (lay[mid].dst <= e) k = mid;
+    else hi = mid;
+  }
+  const BackLayer L = lay[k];
+  const int r = e - L.dst;
+  const int j = r & 3, lane = (r >> 2) & 63, blk = r >> 8;
+  const int ncb = L.cout / 16, cgs = L.cin / 16;
+  const int cb = blk % ncb, cg = (blk / ncb) % cgs, t = blk / (ncb * cgs);
+  const int co = 16 * cb + (lane & 15), ci = 16 * cg + 4 * (lane >> 4) + j;
+  Wa[e] = W[L.src + ((size_t)(L.mirror ? L.ntap - 1 - t : t) * L.cout + co) * L.cin + ci];
 }
 
 // Weight gradient dW[t][ci][co] += sum_i x[tab[i][t]][ci] g[i][co] on the FP32
@@ -239,19 +418,27 @@ __global__ void k_arrange_mfma(int nlayers, const MfmaLayer* __restrict__ lay, i
 constexpr int kWgradWaves = 4;                    // waves (chunks) per block
 constexpr int kWgradTargetWaves = 8192;           // waves per launch (8 per SIMD)
 constexpr size_t kPartFloats = (size_t)16 << 20;  // partial sums of one layer (64 MiB)
-
-__device__ __forceinline__ f32x4_t mfma4(float a, float b, f32x4_t c) {
-  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-}
-
-template <int CIN, int COUT, int NTAP, int TPW>
+//
+// GG: the sum runs over the coarse nodes X of an unpooling layer instead, x[X] in
+// place and g gathered through the pooling table (tab[X][t] is the fine node that
+// has X as its tap-t parent): the same products, in n_coarse steps with nearly every
+// tap present instead of n_fine steps with 27 / 8 of the 27 (32 -> 16 over 619 k /
+// 101 k nodes: 292 us, 86 us so).
+// BIAS: the bias gradient db[co] = sum_i g[i][co] comes from the same gradient rows
+// (blockIdx.y = 0), COUT values after the block's weights, as b follows W in the
+// parameters.
+template <int CIN, int COUT, int NTAP, int TPW, bool BIAS, bool GG>
 __global__ __launch_bounds__(kB) void k_wgrad(int n, const int* __restrict__ tab, const uint16_t* __restrict__ x,
                                                const float* __restrict__ g, float* __restrict__ partial,
                                                int nodes_per_chunk) {
   static_assert(CIN % 16 == 0, "input channels in tiles of 16");
   static_assert(NTAP % TPW == 0, "taps in groups of TPW");
+  static_assert(!(BIAS && GG), "the gathered rows are not each node once");
   constexpr int CIT = CIN / 16, COT = (COUT + 15) / 16, TILES = TPW * CIT * COT;
+  constexpr size_t PER = (size_t)NTAP * CIN * COUT + (BIAS ? COUT : 0);
+  constexpr int GT = GG ? TPW : 1, XT = GG ? 1 : TPW;  // gradient / input rows per step
   __shared__ f32x4_t red[TILES][64];
+  __shared__ float redb[kWgradWaves][COT * 16];
   const int lane = threadIdx.x & 63, col = lane & 15, kq = lane >> 4, wave = threadIdx.x >> 6;
   const int chunk = blockIdx.x * kWgradWaves + wave;
   const int t0 = blockIdx.y * TPW;
@@ -264,6 +451,9 @@ __global__ __launch_bounds__(kB) void k_wgrad(int n, const int* __restrict__ tab
     for (int i = 0; i < CIT; ++i)
 #pragma unroll
       for (int j = 0; j < COT; ++j) acc[tt][i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  float bsum[COT];
+#pragma unroll
+  for (int j = 0; j < COT; ++j) bsum[j] = 0.f;
   // Every load is unconditional (indices clamped into range, the value selected
   // away afterwards), so a step's loads issue together, and the table entries of
   // the next step are fetched while the current step's rows are in flight.
@@ -287,20 +477,23 @@ __global__ __launch_bounds__(kB) void k_wgrad(int n, const int* __restrict__ tab
     int src[TPW];
 #pragma unroll
     for (int tt = 0; tt < TPW; ++tt) src[tt] = nxt[tt];
-    float b[COT];
+    float b[GT][COT];
 #pragma unroll
-    for (int j = 0; j < COT; ++j) {
-      const int co = 16 * j + col;
-      const float v = g[(size_t)nodec * COUT + min(co, COUT - 1)];
-      b[j] = (ok && co < COUT) ? v : 0.f;
-    }
-    float a[TPW][CIT];
+    for (int tt = 0; tt < GT; ++tt)
 #pragma unroll
-    for (int tt = 0; tt < TPW; ++tt)
+      for (int j = 0; j < COT; ++j) {
+        const int co = 16 * j + col;
+        const float v = g[(size_t)(GG ? max(src[tt], 0) : nodec) * COUT + min(co, COUT - 1)];
+        b[tt][j] = (ok && co < COUT && (!GG || src[tt] >= 0)) ? v : 0.f;
+        if constexpr (BIAS) bsum[j] += b[tt][j];
+      }
+    float a[XT][CIT];
+#pragma unroll
+    for (int tt = 0; tt < XT; ++tt)
 #pragma unroll
       for (int i = 0; i < CIT; ++i) {
-        const float v = bf2f(x[(size_t)max(src[tt], 0) * CIN + 16 * i + col]);
-        a[tt][i] = (ok && src[tt] >= 0) ? v : 0.f;
+        const float v = bf2f(x[(size_t)(GG ? nodec : max(src[tt], 0)) * CIN + 16 * i + col]);
+        a[tt][i] = (ok && (GG || src[tt] >= 0)) ? v : 0.f;
       }
     if (base + 4 < end) table_row(base + 4, nxt);
 #pragma unroll
@@ -308,9 +501,18 @@ __global__ __launch_bounds__(kB) void k_wgrad(int n, const int* __restrict__ tab
 #pragma unroll
       for (int i = 0; i < CIT; ++i)
 #pragma unroll
-        for (int j = 0; j < COT; ++j) acc[tt][i][j] = mfma4(a[tt][i], b[j], acc[tt][i][j]);
+        for (int j = 0; j < COT; ++j) acc[tt][i][j] = mfma4(a[GG ? 0 : tt][i], b[GG ? tt : 0][j], acc[tt][i][j]);
   }
   // the four waves' sums, added in wave order
+  if constexpr (BIAS) {
+#pragma unroll
+    for (int j = 0; j < COT; ++j) {
+      float v = bsum[j];
+      v += __shfl_xor(v, 16, 64);
+      v += __shfl_xor(v, 32, 64);
+      if (kq == 0) redb[wave][16 * j + col] = v;
+    }
+  }
   for (int w = 0; w < kWgradWaves; ++w) {
     if (wave == w) {
 #pragma unroll
@@ -331,10 +533,19 @@ __global__ __launch_bounds__(kB) void k_wgrad(int n, const int* __restrict__ tab
     const int tt = tile / (CIT * COT), i = (tile / COT) % CIT, j = tile % COT;
     const int co = 16 * j + (ln & 15);
     if (co >= COUT) continue;
-    float* out = partial + ((size_t)blockIdx.x * NTAP + t0 + tt) * CIN * COUT;
+    float* out = partial + (size_t)blockIdx.x * PER + (size_t)(t0 + tt) * CIN * COUT;
     const f32x4_t v = red[tile][ln];
 #pragma unroll
     for (int r = 0; r < 4; ++r) out[(size_t)(16 * i + 4 * (ln >> 4) + r) * COUT + co] = v[r];
+  }
+  if constexpr (BIAS) {
+    const int co = threadIdx.x;
+    if (blockIdx.y == 0 && co < COUT) {
+      float v = redb[0][co];
+#pragma unroll
+      for (int w = 1; w < kWgradWaves; ++w) v += redb[w][co];
+      partial[(size_t)blockIdx.x * PER + (size_t)NTAP * CIN * COUT + co] = v;
+    }
   }
 }
 
@@ -356,43 +567,32 @@ __global__ __launch_bounds__(kB) void k_reduce_partials(size_t per, int chunks, 
 
 inline unsigned reduce_blocks(size_t per) { return (unsigned)((per + 63) / 64); }
 
-// Bias gradient db[co] += sum_i g[i][co]: per-block sums (grid-stride over a
-// fixed grid) into partial[block][co], then k_reduce_partials.
+// Bias gradient of an unpooling layer (k_wgrad's GG form does not see every row once):
+// db[co] += sum_i g[i][co], thread t taking channel t % COUT of every (kB / COUT)-th
+// row; per-block sums (rows strided by the fixed grid) into partial[block][co], then
+// k_reduce_partials.
 template <int COUT>
 __global__ __launch_bounds__(kB) void k_bgrad(int n, const float* __restrict__ g, float* __restrict__ partial) {
-  __shared__ float sh[kB / 64][COUT];
-  float acc[COUT];
-#pragma unroll
-  for (int co = 0; co < COUT; ++co) acc[co] = 0.f;
-  for (int i = blockIdx.x * kB + threadIdx.x; i < n; i += gridDim.x * kB)
-#pragma unroll
-    for (int co = 0; co < COUT; ++co) acc[co] += g[(size_t)i * COUT + co];
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-#pragma unroll
-  for (int co = 0; co < COUT; ++co) {
-    float v = acc[co];
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
-    if (lane == 0) sh[w][co] = v;
-  }
+  static_assert(kB % COUT == 0, "whole rows per pass");
+  __shared__ float sh[kB];
+  constexpr int RB = kB / COUT;
+  const int co = threadIdx.x % COUT, rb = threadIdx.x / COUT;
+  float acc = 0.f;
+  for (int i = blockIdx.x * RB + rb; i < n; i += gridDim.x * RB) acc += g[(size_t)i * COUT + co];
+  sh[threadIdx.x] = acc;
   __syncthreads();
   if (threadIdx.x < COUT) {
     float s = 0.f;
 #pragma unroll
-    for (int k = 0; k < kB / 64; ++k) s += sh[k][threadIdx.x];
+    for (int k = 0; k < RB; ++k) s += sh[k * COUT + threadIdx.x];
     partial[(size_t)blockIdx.x * COUT + threadIdx.x] = s;
   }
 }
 
-// g[i] *= act'(y[i]) from the stored (BF16) activation output
-__global__ void k_act_grad(size_t total, float* __restrict__ g, const uint16_t* __restrict__ y) {
+// out[i] = g[i] act'(y[i]) from the stored (BF16) activation output (out may be g)
+__global__ void k_act_grad(size_t total, const float* g, const uint16_t* __restrict__ y, float* out) {
   const size_t i = (size_t)blockIdx.x * kB + threadIdx.x;
-  if (i < total) g[i] *= bf2f(y[i]) > 0.f ? 1.f : kSlope;
-}
-
-__global__ void k_add(size_t total, float* __restrict__ a, const float* __restrict__ b) {
-  const size_t i = (size_t)blockIdx.x * kB + threadIdx.x;
-  if (i < total) a[i] += b[i];
+  if (i < total) out[i] = g[i] * (bf2f(y[i]) > 0.f ? 1.f : kSlope);
 }
 
 __global__ void k_zero(size_t total, float* __restrict__ a) {
@@ -418,13 +618,18 @@ __global__ void k_transpose_taps(int ntap, int cin, int cout, int mirror, const 
   Wt[e] = W[(size_t)ts * per + (size_t)ci * cout + co];
 }
 
+// 8 channels (16 bytes) per thread; C is a multiple of 16
 __global__ void k_embed(int n, const uint8_t* __restrict__ occ8, const float* __restrict__ E, int C,
                         uint16_t* __restrict__ y) {
   const size_t e = (size_t)blockIdx.x * kB + threadIdx.x;
-  if (e >= (size_t)n * C) return;
-  const size_t i = e / C;
-  const int c = (int)(e % C);
-  y[e] = f2bf(E[(size_t)occ8[i] * C + c]);
+  if (e * 8 >= (size_t)n * C) return;
+  const size_t i = e * 8 / C;
+  const int c = (int)(e * 8 % C);
+  const float* row = E + (size_t)occ8[i] * C + c;
+  uint32_t w[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) w[k] = (uint32_t)f2bf(row[2 * k]) | ((uint32_t)f2bf(row[2 * k + 1]) << 16);
+  *reinterpret_cast<uint4*>(y + e * 8) = make_uint4(w[0], w[1], w[2], w[3]);
 }
 
 // Embedding gradient dE[o][c] += sum of g[i][c] over the nodes i with occupancy o,
@@ -613,7 +818,14 @@ __global__ void k_colmean_final(const double* __restrict__ partial, int nblk, in
   const int q = threadIdx.x;
   if (q >= Q) return;
   double t = 0.0;
-  for (int b = 0; b < nblk; ++b) t += partial[(size_t)b * Q + q];
+  for (int b0 = 0; b0 < nblk; b0 += 32) {  // 32 loads in flight, added in order
+    double v[32];
+#pragma unroll
+    for (int k = 0; k < 32; ++k) v[k] = partial[(size_t)min(b0 + k, nblk - 1) * Q + q];
+#pragma unroll
+    for (int k = 0; k < 32; ++k)
+      if (b0 + k < nblk) t += v[k];
+  }
   mean[q] = n > 0 ? t / n : 0.0;
 }
 
@@ -652,25 +864,40 @@ static void gconv_dispatch(int cin, int cout, int ntap, int n, const int* tab, c
     GMT_LAUNCH_CHECK();                                                                                      \
     return;                                                                                                  \
   }
-  GC(16, 16, 27) GC(32, 32, 27) GC(64, 64, 27) GC(16, 32, 27) GC(32, 64, 27) GC(32, 16, 27) GC(64, 32, 27)
-  GC(16, 32, 1) GC(32, 32, 1) GC(64, 32, 1) GC(32, 18, 1) GC(32, 3, 1)
-  GC(32, 16, 1) GC(32, 64, 1) GC(18, 32, 1) GC(3, 32, 1) GC(16, 16, 1) GC(64, 64, 1)
+  GC(18, 32, 1) GC(3, 32, 1)
 #undef GC
   fail(GMT_E_INVAL, "gather conv (%d -> %d, %d taps) not instantiated", cin, cout, ntap);
 }
 
-// BF16-input layers of the forward on the matrix cores
+// BF16-input layers of the forward on the matrix cores.  Waves of 64 nodes and all
+// output channels load each weight fragment once per 64 nodes; levels with fewer
+// than kWideNodes nodes leave most of the chip idle that way and take a wave
+// per 16 nodes and 16 channels instead.
+constexpr int kWideNodes = 1 << 17;
+
+// GMT_NN_WIDE_NODES=<k> moves that line (tests of both forms on small cells)
+static bool wide_waves(int n) {
+  const char* e = std::getenv("GMT_NN_WIDE_NODES");
+  return n >= (e && *e ? std::atoi(e) : kWideNodes);
+}
+
 template <typename Tout, int FLAGS>
 static void mfma_dispatch(int cin, int cout, int ntap, int n, const int* tab, const uint16_t* x, const uint16_t* Wm,
                           const float* b, const uint16_t* skip, float scale, Tout* y, hipStream_t s) {
   if (n <= 0) return;
-  const int per_block = (kB / 64) * 16 * kMfmaRows;
-  const unsigned g = (unsigned)((n + per_block - 1) / per_block);
+  const bool wide = wide_waves(n);
+  const unsigned per_block = (kB / 64) * 16 * (wide ? 4 : 1);
+  const unsigned g = ((unsigned)n + per_block - 1) / per_block;
   const uint4* w = reinterpret_cast<const uint4*>(Wm);
 #define GM(CI, CO, NT)                                                                                              \
   if (cin == CI && cout == CO && ntap == NT) {                                                                     \
-    hipLaunchKernelGGL((k_gconv_mfma<Tout, CI, CO, NT, FLAGS>), dim3(g), dim3(kB), 0, s, n, tab, x, w, b, skip, scale, \
-                       y);                                                                                          \
+    constexpr int NCB = (CO + 15) / 16;                                                                             \
+    if (wide)                                                                                                       \
+      hipLaunchKernelGGL((k_gconv_mfma<Tout, CI, CO, NT, FLAGS, 4, NCB>), dim3(g), dim3(kB), 0, s, n, tab, x, w, b, \
+                         skip, scale, y);                                                                           \
+    else                                                                                                            \
+      hipLaunchKernelGGL((k_gconv_mfma<Tout, CI, CO, NT, FLAGS, 1, 1>), dim3(g, NCB), dim3(kB), 0, s, n, tab, x, w, \
+                         b, skip, scale, y);                                                                        \
     GMT_LAUNCH_CHECK();                                                                                             \
     return;                                                                                                         \
   }
@@ -684,6 +911,33 @@ static void mfma_dispatch(int cin, int cout, int ntap, int n, const int* tab, co
   fail(GMT_E_INVAL, "MFMA gather conv (%d -> %d, %d taps) not instantiated", cin, cout, ntap);
 }
 
+// FP32 data gradients on the matrix cores (cin: the gradient's channels); waves as
+// in mfma_dispatch
+template <int FLAGS>
+static void dgrad_dispatch(int cin, int cout, int ntap, int n, const int* tab, const float* g, const float* Wa,
+                           const uint16_t* ref, float* y, hipStream_t s) {
+  if (n <= 0) return;
+  const bool wide = wide_waves(n);
+  const unsigned per_block = (kB / 64) * 16 * (wide ? 4 : 1);
+  const unsigned grid = ((unsigned)n + per_block - 1) / per_block;
+  const float4* w = reinterpret_cast<const float4*>(Wa);
+#define GD(CI, CO, NT)                                                                                              \
+  if (cin == CI && cout == CO && ntap == NT) {                                                                     \
+    if (wide)                                                                                                       \
+      hipLaunchKernelGGL((k_dgrad_mfma<CI, CO, NT, FLAGS, 4, CO / 16>), dim3(grid), dim3(kB), 0, s, n, tab, g, w,    \
+                         ref, y);                                                                                   \
+    else                                                                                                            \
+      hipLaunchKernelGGL((k_dgrad_mfma<CI, CO, NT, FLAGS, 1, 1>), dim3(grid, CO / 16), dim3(kB), 0, s, n, tab, g, w, \
+                         ref, y);                                                                                   \
+    GMT_LAUNCH_CHECK();                                                                                             \
+    return;                                                                                                         \
+  }
+  GD(16, 16, 27) GD(32, 32, 27) GD(64, 64, 27) GD(16, 32, 27) GD(32, 64, 27) GD(32, 16, 27) GD(64, 32, 27)
+  GD(32, 32, 1) GD(32, 16, 1) GD(32, 64, 1) GD(16, 16, 1) GD(64, 64, 1)
+#undef GD
+  fail(GMT_E_INVAL, "data gradient (%d -> %d, %d taps) not instantiated", cin, cout, ntap);
+}
+
 // taps per wave: as many as keep at most 12 accumulator tiles (48 registers), so
 // that several waves per SIMD keep enough gathers in flight
 constexpr int wgrad_tpw(int cin, int cout, int ntap) {
@@ -692,10 +946,12 @@ constexpr int wgrad_tpw(int cin, int cout, int ntap) {
   return tiles * 27 <= 12 ? 27 : tiles * 9 <= 12 ? 9 : tiles * 3 <= 12 ? 3 : 1;
 }
 
+// dW (and with BIAS db, which follows it) += the layer's weight gradient; GG: see k_wgrad
+template <bool BIAS, bool GG = false>
 static void wgrad_dispatch(int cin, int cout, int ntap, int n, const int* tab, const uint16_t* x, const float* g,
                            float* dW, float* partial, hipStream_t s) {
   if (n <= 0) return;
-  const size_t per = (size_t)ntap * cin * cout;
+  const size_t per = (size_t)ntap * cin * cout + (BIAS ? cout : 0);
 #define WG(CI, CO, NT)                                                                                      \
   if (cin == CI && cout == CO && ntap == NT) {                                                             \
     constexpr int TPW = wgrad_tpw(CI, CO, NT), GROUPS = NT / TPW;                                          \
@@ -705,15 +961,21 @@ static void wgrad_dispatch(int cin, int cout, int ntap, int n, const int* tab, c
     blocks = (int)std::max<size_t>(1, std::min<size_t>(blocks, kPartFloats / per));                        \
     chunks = blocks * kWgradWaves;                                                                          \
     const int npc = (n + chunks - 1) / chunks;                                                              \
-    hipLaunchKernelGGL((k_wgrad<CI, CO, NT, TPW>), dim3((unsigned)blocks, (unsigned)GROUPS), dim3(kB), 0, s, n, \
-                       tab, x, g, partial, npc);                                                            \
+    hipLaunchKernelGGL((k_wgrad<CI, CO, NT, TPW, BIAS, GG>), dim3((unsigned)blocks, (unsigned)GROUPS), dim3(kB), 0, \
+                       s, n, tab, x, g, partial, npc);                                                      \
     GMT_LAUNCH_CHECK();                                                                                     \
     hipLaunchKernelGGL(k_reduce_partials, dim3(reduce_blocks(per)), dim3(kB), 0, s, per, blocks, partial, dW); \
     GMT_LAUNCH_CHECK();                                                                                     \
     return;                                                                                                 \
   }
-  WG(16, 16, 27) WG(32, 32, 27) WG(64, 64, 27) WG(16, 32, 27) WG(32, 64, 27) WG(32, 16, 27) WG(64, 32, 27)
-  WG(16, 32, 1) WG(32, 32, 1) WG(64, 32, 1) WG(32, 18, 1) WG(32, 3, 1) WG(16, 16, 1) WG(64, 64, 1)
+  if constexpr (GG) {
+    WG(16, 16, 27) WG(32, 32, 27) WG(64, 64, 27) WG(32, 16, 27) WG(64, 32, 27) WG(16, 32, 27) WG(32, 64, 27)
+  } else if constexpr (BIAS) {
+    WG(16, 16, 27) WG(32, 32, 27) WG(64, 64, 27) WG(16, 32, 27) WG(32, 64, 27) WG(32, 16, 27) WG(64, 32, 27)
+    WG(16, 32, 1) WG(32, 32, 1) WG(64, 32, 1) WG(32, 18, 1) WG(32, 3, 1)
+  } else {
+    WG(16, 16, 1) WG(32, 32, 1) WG(64, 64, 1)
+  }
 #undef WG
   fail(GMT_E_INVAL, "weight gradient (%d -> %d, %d taps) not instantiated", cin, cout, ntap);
 }
@@ -731,7 +993,7 @@ static void bgrad_dispatch(int cout, int n, const float* g, float* db, float* pa
     GMT_LAUNCH_CHECK();                                                                          \
     return;                                                                                      \
   }
-  BG(16) BG(32) BG(64) BG(18) BG(3)
+  BG(16) BG(32) BG(64)
 #undef BG
   fail(GMT_E_INVAL, "bias gradient of width %d not instantiated", cout);
 }
@@ -813,7 +1075,11 @@ struct NNState {
   MfmaLayer* mlay = nullptr;                             // their layer table (device)
   int n_mlay = 0, m_total = 0;
   std::map<size_t, int> mdst;                            // parameter offset of a layer -> its Wm offset
-  float* Wt = nullptr;                                   // transposed weights of one layer
+  float* Wt = nullptr;                                   // transposed weights of one W3
+  float* Wa = nullptr;                                   // the other layers' in the order of k_dgrad_mfma
+  BackLayer* blay = nullptr;                             // their layer table (device; built at the first backward)
+  int n_blay = 0, b_total = 0;
+  std::map<size_t, int> bdst;                            // parameter offset of a layer -> its Wa offset
   float *g0 = nullptr, *g1 = nullptr, *g2 = nullptr;     // FP32 gradient scratch (max n_l * max C)
   double* colred = nullptr;                              // column-mean partials + means
   float* part = nullptr;                                 // per-chunk gradient partial sums
@@ -959,9 +1225,7 @@ void nn_setup(Hier& h, const gmt_nn_config& cfg, hipStream_t s) {
     S->mlay = h.alloc<MfmaLayer>(lay.size());
     GMT_HIP(hipMemcpyAsync(S->mlay, lay.data(), lay.size() * sizeof(MfmaLayer), hipMemcpyHostToDevice, s));
   }
-  size_t maxw = 0;
-  for (int l = 0; l < L; ++l) maxw = std::max(maxw, (size_t)27 * 64 * 64);
-  S->Wt = h.alloc<float>(maxw);
+  S->Wt = h.alloc<float>((size_t)S->nl.H * h.Q);
   S->colred = h.alloc<double>((size_t)(kColBlocks + 1) * 32);
   S->g0 = h.alloc<float>(maxnc);
   S->g1 = h.alloc<float>(maxnc);
@@ -1006,7 +1270,7 @@ void nn_forward(Hier& h, const float* params, float* const* out, hipStream_t s) 
   const float* W = S.Wb;
   auto wm = [&](size_t src) { return S.Wm + S.mdst.at(src); };
   const int n0 = h.lv[0].n_n;
-  hipLaunchKernelGGL(k_embed, dim3(nblk((size_t)n0 * N.C[0])), dim3(kB), 0, s, n0, h.lv[0].occ8, W + N.E, N.C[0],
+  hipLaunchKernelGGL(k_embed, dim3(nblk((size_t)n0 * N.C[0] / 8)), dim3(kB), 0, s, n0, h.lv[0].occ8, W + N.E, N.C[0],
                      S.h[0]);
   GMT_LAUNCH_CHECK();
   for (int l = 0; l < L; ++l) {
@@ -1046,21 +1310,10 @@ void nn_forward(Hier& h, const float* params, float* const* out, hipStream_t s) 
   }
 }
 
-static void transpose_taps(NNState& S, const float* W, int ntap, int cin, int cout, bool mirror, hipStream_t s) {
-  const size_t tot = (size_t)ntap * cin * cout;
-  hipLaunchKernelGGL(k_transpose_taps, dim3(nblk(tot)), dim3(kB), 0, s, ntap, cin, cout, mirror ? 1 : 0, W, S.Wt);
-  GMT_LAUNCH_CHECK();
-}
-
-static void act_grad(float* g, const uint16_t* y, size_t tot, hipStream_t s) {
+// out = g act'(y)
+static void act_grad(const float* g, const uint16_t* y, float* out, size_t tot, hipStream_t s) {
   if (!tot) return;
-  hipLaunchKernelGGL(k_act_grad, dim3(nblk(tot)), dim3(kB), 0, s, tot, g, y);
-  GMT_LAUNCH_CHECK();
-}
-
-static void addv(float* a, const float* b, size_t tot, hipStream_t s) {
-  if (!tot) return;
-  hipLaunchKernelGGL(k_add, dim3(nblk(tot)), dim3(kB), 0, s, tot, a, b);
+  hipLaunchKernelGGL(k_act_grad, dim3(nblk(tot)), dim3(kB), 0, s, tot, g, y, out);
   GMT_LAUNCH_CHECK();
 }
 
@@ -1075,10 +1328,41 @@ __global__ void k_scale_copy(size_t total, const float* __restrict__ a, float sc
   if (i < total) b[i] = sc * a[i];
 }
 
-// y = gather-conv of an FP32 gradient with the transposed per-tap weights held in S.Wt
-static void dgrad(NNState& S, int cin, int cout, int ntap, int n_out, const int* tab, const float* g, float* y,
-                  hipStream_t s) {
-  gconv_dispatch<float, float, 0>(cin, cout, ntap, n_out, tab, g, S.Wt, nullptr, nullptr, 1.f, y, s);
+// Every layer's transposed weights for the data gradients, one launch per backward
+// (the layer table is built at the first one: inference never needs it).
+static void arrange_back(Hier& h, NNState& S, hipStream_t s) {
+  const NetLayout& N = S.nl;
+  if (!S.blay) {
+    std::vector<BackLayer> lay;
+    int dst = 0;
+    auto add = [&](size_t src, int ntap, int cin, int cout, bool mirror) {
+      S.bdst[src] = dst;
+      lay.push_back({(int)src, dst, ntap, cin, cout, mirror ? 1 : 0});
+      dst += ntap * cin * cout;
+    };
+    for (int l = 0; l < N.L; ++l) {
+      const int C = N.C[l];
+      add(N.We[l], 27, C, C, true);
+      if (l + 1 < N.L) {
+        add(N.Wp[l], 27, N.C[l + 1], C, false);
+        add(N.Wu[l], 27, C, N.C[l + 1], false);
+        add(N.Wd[l], 27, C, C, true);
+        add(N.W1[l], 1, N.H, C, false);
+        add(N.W2[l], 1, N.H, N.H, false);
+      }
+      if (N.att)
+        for (size_t w : {N.Wq[l], N.Wk[l], N.Wv[l], N.Wo[l]}) add(w, 1, C, C, false);
+    }
+    BackLayer* t = h.alloc<BackLayer>(lay.size());
+    GMT_HIP(hipMemcpyAsync(t, lay.data(), lay.size() * sizeof(BackLayer), hipMemcpyHostToDevice, s));
+    GMT_HIP(hipStreamSynchronize(s));  // the host vector goes out of scope
+    S.Wa = h.alloc<float>((size_t)dst);
+    S.n_blay = (int)lay.size();
+    S.b_total = dst;
+    S.blay = t;
+  }
+  hipLaunchKernelGGL(k_arrange_back, dim3(nblk(S.b_total)), dim3(kB), 0, s, S.n_blay, S.blay, S.b_total, S.Wb, S.Wa);
+  GMT_LAUNCH_CHECK();
 }
 
 // Backward of level l's attention block s = a + bf16(Attn(q, k, v)) Wo with q, k, v = a Wq, a Wk,
@@ -1086,24 +1370,20 @@ static void dgrad(NNState& S, int cin, int cout, int ntap, int n_out, const int*
 // projections); adds the gradients of Wq, Wk, Wv, Wo.
 static void attention_block_backward(Hier& h, NNState& S, int l, float* grad, hipStream_t s) {
   const NetLayout& N = S.nl;
-  const float* W = S.Wb;
   const int n = h.lv[l].n_n, C = N.C[l];
-  const size_t tc = (size_t)n * C;
   float* gs = S.ga[l];
+  auto wa = [&](size_t src) { return S.Wa + S.bdst.at(src); };
   // Wo: rows are nodes, the input o is gathered through inv
-  wgrad_dispatch(C, C, 1, n, S.inv[l], S.o16[l], gs, grad + N.Wo[l], S.part, s);
-  transpose_taps(S, W + N.Wo[l], 1, C, C, false, s);
-  dgrad(S, C, C, 1, n, S.order[l], gs, S.g0, s);  // dL/do in serialization order
+  wgrad_dispatch<false>(C, C, 1, n, S.inv[l], S.o16[l], gs, grad + N.Wo[l], S.part, s);
+  dgrad_dispatch<0>(C, C, 1, n, S.order[l], gs, wa(N.Wo[l]), nullptr, S.g0, s);  // dL/do in serialization order
   attention_backward(n, attention_window(l), C, h.lv[l].N, S.ser_lin[l], S.q[l], S.k[l], S.v[l], S.o32[l],
                      S.lse[l], S.g0, S.g1, S.g2, S.g3, s);
   const size_t Wx[3] = {N.Wq[l], N.Wk[l], N.Wv[l]};
   float* gx[3] = {S.g1, S.g2, S.g3};
   for (int j = 0; j < 3; ++j) {
     // rows in serialization order, the input a gathered through order; dL/da += gathered back through inv
-    wgrad_dispatch(C, C, 1, n, S.order[l], S.a[l], gx[j], grad + Wx[j], S.part, s);
-    transpose_taps(S, W + Wx[j], 1, C, C, false, s);
-    dgrad(S, C, C, 1, n, S.inv[l], gx[j], S.g0, s);
-    addv(gs, S.g0, tc, s);
+    wgrad_dispatch<false>(C, C, 1, n, S.order[l], S.a[l], gx[j], grad + Wx[j], S.part, s);
+    dgrad_dispatch<D_ADD>(C, C, 1, n, S.inv[l], gx[j], wa(Wx[j]), nullptr, gs, s);
   }
 }
 
@@ -1144,6 +1424,8 @@ void nn_backward(Hier& h, const float* const* gout, float* grad, hipStream_t s) 
   const NetLayout& N = S.nl;
   const int L = N.L, H = N.H, q = N.q;
   const float* W = S.Wb;
+  arrange_back(h, S, s);
+  auto wa = [&](size_t src) { return S.Wa + S.bdst.at(src); };
   for (int l = 0; l < L; ++l) zerov(S.gd[l], (size_t)h.lv[l].n_n * N.C[l], s);
   // heads: out = N (z2 W3 + b3), z2 = act(z1 W2 + b2), z1 = act(d W1 + b1)
   for (int l = 0; l + 1 < L; ++l) {
@@ -1153,41 +1435,28 @@ void nn_backward(Hier& h, const float* const* gout, float* grad, hipStream_t s) 
     hipLaunchKernelGGL(k_scale_copy, dim3(nblk(tq)), dim3(kB), 0, s, tq, gout[l], (float)h.N, S.g2);
     GMT_LAUNCH_CHECK();
     center_rows(S, S.g2, n, q, s);
-    wgrad_dispatch(H, q, 1, n, nullptr, S.z2[l], S.g2, grad + N.W3[l], S.part, s);
-    bgrad_dispatch(q, n, S.g2, grad + N.b3[l], S.part, s);
-    transpose_taps(S, W + N.W3[l], 1, H, q, false, s);
-    dgrad(S, q, H, 1, n, nullptr, S.g2, S.g0, s);
-    act_grad(S.g0, S.z2[l], (size_t)n * H, s);
-    wgrad_dispatch(H, H, 1, n, nullptr, S.z1[l], S.g0, grad + N.W2[l], S.part, s);
-    bgrad_dispatch(H, n, S.g0, grad + N.b2[l], S.part, s);
-    transpose_taps(S, W + N.W2[l], 1, H, H, false, s);
-    dgrad(S, H, H, 1, n, nullptr, S.g0, S.g1, s);
-    act_grad(S.g1, S.z1[l], (size_t)n * H, s);
-    wgrad_dispatch(C, H, 1, n, nullptr, S.d[l], S.g1, grad + N.W1[l], S.part, s);
-    bgrad_dispatch(H, n, S.g1, grad + N.b1[l], S.part, s);
-    transpose_taps(S, W + N.W1[l], 1, C, H, false, s);
-    dgrad(S, H, C, 1, n, nullptr, S.g1, S.g2, s);
-    addv(S.gd[l], S.g2, (size_t)n * C, s);
+    wgrad_dispatch<true>(H, q, 1, n, nullptr, S.z2[l], S.g2, grad + N.W3[l], S.part, s);
+    hipLaunchKernelGGL(k_transpose_taps, dim3(nblk((size_t)H * q)), dim3(kB), 0, s, 1, H, q, 0, W + N.W3[l], S.Wt);
+    GMT_LAUNCH_CHECK();
+    gconv_dispatch<float, float, 0>(q, H, 1, n, nullptr, S.g2, S.Wt, nullptr, nullptr, 1.f, S.g0, s);
+    act_grad(S.g0, S.z2[l], S.g0, (size_t)n * H, s);
+    wgrad_dispatch<true>(H, H, 1, n, nullptr, S.z1[l], S.g0, grad + N.W2[l], S.part, s);
+    dgrad_dispatch<D_ACT>(H, H, 1, n, nullptr, S.g0, wa(N.W2[l]), S.z1[l], S.g1, s);
+    wgrad_dispatch<true>(C, H, 1, n, nullptr, S.d[l], S.g1, grad + N.W1[l], S.part, s);
+    dgrad_dispatch<D_ADD>(H, C, 1, n, nullptr, S.g1, wa(N.W1[l]), nullptr, S.gd[l], s);
   }
   // decoder, finest first: d_l = act(conv(t_l) + bd), t_l = act(unpool(d_{l+1}) + bu + a_l)
   for (int l = 0; l + 1 < L; ++l) {
     const int n = h.lv[l].n_n, C = N.C[l], Cn = N.C[l + 1], nn = h.lv[l + 1].n_n;
     const size_t tc = (size_t)n * C;
-    GMT_HIP(hipMemcpyAsync(S.g0, S.gd[l], tc * sizeof(float), hipMemcpyDeviceToDevice, s));
-    act_grad(S.g0, S.d[l], tc, s);
-    wgrad_dispatch(C, C, 27, n, S.conv[l], S.t[l], S.g0, grad + N.Wd[l], S.part, s);
-    bgrad_dispatch(C, n, S.g0, grad + N.bd[l], S.part, s);
-    transpose_taps(S, W + N.Wd[l], 27, C, C, true, s);
-    dgrad(S, C, C, 27, n, S.conv[l], S.g0, S.g1, s);
-    act_grad(S.g1, S.t[l], tc, s);
-    // skip path into a_l, bias bu
-    GMT_HIP(hipMemcpyAsync(S.ga[l], S.g1, tc * sizeof(float), hipMemcpyDeviceToDevice, s));
-    bgrad_dispatch(C, n, S.g1, grad + N.bu[l], S.part, s);
+    act_grad(S.gd[l], S.d[l], S.g0, tc, s);
+    wgrad_dispatch<true>(C, C, 27, n, S.conv[l], S.t[l], S.g0, grad + N.Wd[l], S.part, s);
+    // the gradient at t_l's sum is also that of the skip path into a_l: it starts ga[l]
+    dgrad_dispatch<D_ACT>(C, C, 27, n, S.conv[l], S.g0, wa(N.Wd[l]), S.t[l], S.ga[l], s);
+    bgrad_dispatch(C, n, S.ga[l], grad + N.bu[l], S.part, s);
     const uint16_t* dn = l + 1 == L - 1 ? S.out(L - 1) : S.d[l + 1];
-    wgrad_dispatch(Cn, C, 27, n, S.unpool[l], dn, S.g1, grad + N.Wu[l], S.part, s);
-    transpose_taps(S, W + N.Wu[l], 27, Cn, C, false, s);
-    dgrad(S, C, Cn, 27, nn, S.pool[l], S.g1, S.g2, s);
-    addv(S.gd[l + 1], S.g2, (size_t)nn * Cn, s);
+    wgrad_dispatch<false, true>(Cn, C, 27, nn, S.pool[l], dn, S.ga[l], grad + N.Wu[l], S.part, s);
+    dgrad_dispatch<D_ADD>(C, Cn, 27, nn, S.pool[l], S.ga[l], wa(N.Wu[l]), nullptr, S.gd[l + 1], s);
   }
   // s_{L-1} = d_{L-1}
   GMT_HIP(hipMemcpyAsync(S.ga[L - 1], S.gd[L - 1], (size_t)h.lv[L - 1].n_n * N.C[L - 1] * sizeof(float),
@@ -1198,21 +1467,15 @@ void nn_backward(Hier& h, const float* const* gout, float* grad, hipStream_t s) 
     const int n = h.lv[l].n_n, C = N.C[l];
     const size_t tc = (size_t)n * C;
     if (N.att) attention_block_backward(h, S, l, grad, s);  // ga[l]: dL/ds_l -> dL/da_l
-    GMT_HIP(hipMemcpyAsync(S.g0, S.ga[l], tc * sizeof(float), hipMemcpyDeviceToDevice, s));
-    act_grad(S.g0, S.a[l], tc, s);
-    wgrad_dispatch(C, C, 27, n, S.conv[l], S.h[l], S.g0, grad + N.We[l], S.part, s);
-    bgrad_dispatch(C, n, S.g0, grad + N.be[l], S.part, s);
-    transpose_taps(S, W + N.We[l], 27, C, C, true, s);
-    dgrad(S, C, C, 27, n, S.conv[l], S.g0, S.g1, s);
+    act_grad(S.ga[l], S.a[l], S.g0, tc, s);
+    wgrad_dispatch<true>(C, C, 27, n, S.conv[l], S.h[l], S.g0, grad + N.We[l], S.part, s);
     if (l > 0) {
       const int Cp = N.C[l - 1], np = h.lv[l - 1].n_n;
-      act_grad(S.g1, S.h[l], tc, s);
-      wgrad_dispatch(Cp, C, 27, n, S.pool[l - 1], S.out(l - 1), S.g1, grad + N.Wp[l - 1], S.part, s);
-      bgrad_dispatch(C, n, S.g1, grad + N.bp[l - 1], S.part, s);
-      transpose_taps(S, W + N.Wp[l - 1], 27, Cp, C, false, s);
-      dgrad(S, C, Cp, 27, np, S.unpool[l - 1], S.g1, S.g2, s);
-      addv(S.ga[l - 1], S.g2, (size_t)np * Cp, s);
+      dgrad_dispatch<D_ACT>(C, C, 27, n, S.conv[l], S.g0, wa(N.We[l]), S.h[l], S.g1, s);
+      wgrad_dispatch<true>(Cp, C, 27, n, S.pool[l - 1], S.out(l - 1), S.g1, grad + N.Wp[l - 1], S.part, s);
+      dgrad_dispatch<D_ADD>(C, Cp, 27, np, S.unpool[l - 1], S.g1, wa(N.Wp[l - 1]), nullptr, S.ga[l - 1], s);
     } else {
+      dgrad_dispatch<0>(C, C, 27, n, S.conv[l], S.g0, wa(N.We[l]), nullptr, S.g1, s);
       embed_order(h, S, s);
       if (S.n_emb_chunks > 0) {
         hipLaunchKernelGGL(k_embed_grad, dim3(S.n_emb_chunks), dim3(kB), 0, s, S.emb_nodes, S.emb_chunks, C, S.g1,

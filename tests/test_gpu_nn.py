@@ -432,3 +432,29 @@ def test_norm2_and_ema():
         B.ema(e, _t(x), decay)
         assert np.abs(_np(e) - ref).max() <= 2 * 2.0 ** -24 * np.abs(ref).max()
     assert np.abs(_np(e) - x).max() == 0.0  # decay 0 copies x
+
+
+@pytest.mark.parametrize("attention", [False, True])
+def test_wave_shapes_agree(attention, monkeypatch):
+    """The gather convolutions with 64 nodes or 16 nodes x 16 channels per wave, and the attention
+    kernels with 4, 2 or 1 queries per thread, sum the same products in the same order: predictions
+    and gradients are bit for bit the same (5 levels, from 14 k nodes down to 64: partial waves,
+    fewer nodes than a wave, windows of every size)."""
+    B = _gmt()
+    H = B.Hierarchy(gyroid_sheet(64, 3, 0.25), 5)
+    H.nn_setup([16, 32, 64, 64, 64], attention=attention)
+    rng = np.random.default_rng(2)
+    params = _t(0.1 * rng.standard_normal(H.n_params))
+    ref = None
+    for wide, per in (("0", "4"), ("1000000000", "1"), ("3000", "2")):
+        monkeypatch.setenv("GMT_NN_WIDE_NODES", wide)
+        monkeypatch.setenv("GMT_ATTN_PER", per)
+        outs = H.nn_forward(params)
+        grad = torch.zeros(H.n_params, dtype=torch.float32, device=DEV)
+        H.nn_backward(outs, grad)
+        got = [o.clone() for o in outs] + [grad]
+        if ref is None:
+            ref = got
+        for a, b in zip(ref, got):
+            assert torch.isfinite(a).all() and torch.equal(a, b)
+    H.close()
