@@ -15,7 +15,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libgmt.so")
 SOURCES = ["kernels.hip", "host.hip", "nn.hip", "attention.hip", "coarse.hip",
-           "setup.hip", "layout.hip"]
+           "setup.hip", "layout.hip", "stencil.hip", "simp.hip"]
 
 FLAGS = [
     "-O3",

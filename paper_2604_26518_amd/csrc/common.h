@@ -147,6 +147,10 @@ struct LevelView {
   // workgroup size (64 or 256), cases per thread (1, or all c) -- levels >= 2
   // only -- and XCD-contiguous numbering
   int bs, xcd, cb;
+  // levels >= 2, where they are built: the assembled stencils (stencil.hip), used
+  // when cb is one of kStencil*
+  const T* stc;
+  const int* snbr;
   // levels >= 2: when `list` is set, the sweep covers only the n_list nodes
   // list[0 .. n_list) (one colour class of the Gauss-Seidel smoother)
   const int* list;
@@ -157,12 +161,6 @@ struct LevelView {
 // elements sharing a node are connected); parent: n_e ints of scratch
 int count_components(const int* elem_lin, int n_e, const int* elem_map, int N, int* parent, int* d_count,
                      hipStream_t s);
-// u[c][i][:] += omega D^-1 r[c][i][:] for the n_list nodes i of `list` (one
-// colour of the Gauss-Seidel smoother)
-template <typename T>
-void launch_gs_update(const int* list, int n_list, int n, int D, int C, const T* dinv, const T* r, T* u, T omega,
-                      hipStream_t s);
-
 // Epilogue of a node-centric operator sweep.
 // EPI_CHEB0 is the first Chebyshev step (d = rho2 D^-1 r, the previous d is not read).
 enum Epi { EPI_KU = 0, EPI_RESID = 1, EPI_JACOBI = 2, EPI_CHEB = 3, EPI_CHEB0 = 4 };
@@ -188,9 +186,10 @@ void launch_smooth_zero(int n, int D, int C, const T* f, const T* dinv, T scale,
                         hipStream_t s);
 template <typename T>
 void launch_normalize(const T* src, size_t n, const double* nrm2, T* dst, hipStream_t s);
+// fc = R rf; with u, also the coarse level's first smoothing step from zero, u = scale dinv fc
 template <typename T>
 void launch_restrict(const LevelView<T>& fine, const LevelView<T>& coarse, int Q, int D, const T* rf, T* fc,
-                     hipStream_t s);
+                     hipStream_t s, const T* dinv = nullptr, T scale = T(0), T* u = nullptr);
 template <typename T>
 void launch_prolong_add(const LevelView<T>& fine, const LevelView<T>& coarse, int Q, int D, const T* uc, T* uf,
                         hipStream_t s);
@@ -214,35 +213,35 @@ void launch_dot_centered(const T* a, const T* b, const double* sums, double inv_
 template <typename Ta, typename Tb>
 void launch_gram(const Ta* a, const Tb* b, int n, int C, int D, double* partial, double* out,
                  hipStream_t s);
-// u += alpha[c] p ; r -= alpha[c] q  (vectors [C][n][D]); with qsums, q minus its column
-// means qsums / n
+// Scalars of a PCG step, per case: alpha = rz / pq and beta = rz_new / rz are formed by
+// the kernels that use them (0 where undefined, or once *stop is set; stop nullable).
+// u += alpha p ; r -= alpha q  (vectors [C][n][D]); with qsums, q minus its column
+// means qsums / n; with z, also z = scale dinv r (a first smoothing step from zero)
 template <typename T>
-void launch_pcg_update(T* u, T* r, const T* p, const T* q, const double* alpha, int n, int Q, int D,
-                       hipStream_t s, const double* qsums = nullptr, double inv_n = 0.0);
-// dots[c] = a.b per case and sums[c*D + d] = column sums of b, in one pass
+void launch_pcg_update(T* u, T* r, const T* p, const T* q, const double* rz, const double* pq, const double* stop,
+                       int n, int Q, int D, hipStream_t s, const double* qsums, double inv_n,
+                       const T* dinv = nullptr, T scale = T(0), T* z = nullptr);
+// dots[c] = a.b per case and sums[c*D + d] = column sums of b, in one pass; with cur,
+// prev[c] = cur[c] on the way
 template <typename T>
 void launch_dot_colsum(const T* a, const T* b, int n, int C, int D, double* partial, double* dots, double* sums,
-                       hipStream_t s);
-// rz[c] = r.(z - column means sums / n) and rr[c] = r.r, in one pass
+                       hipStream_t s, const double* cur = nullptr, double* prev = nullptr);
+// rz[c] = r.(z - column means sums / n) and rr[c] = r.r, in one pass; with flags
+// ([0] stop, [1] iterations run, [2 + m] squared residual target of case m) the
+// convergence check of a captured iteration
 template <typename T>
 void launch_dot2_centered(const T* r, const T* z, const double* sums, double inv_n, int n, int C, int D,
-                          double* partial, double* rz, double* rr, hipStream_t s);
-// p = z + beta[c] p (with sums: z with its column means sums / n removed on the fly)
+                          double* partial, double* rz, double* rr, double* flags, hipStream_t s);
+// p = z + beta p, beta = rz_new / rz (0 without rz_new); with sums, z with its column
+// means sums / n removed on the fly
 template <typename T>
-void launch_pcg_direction(T* p, const T* z, const double* beta, int n, int Q, int D, hipStream_t s,
-                          const double* sums = nullptr, double inv_n = 0.0);
+void launch_pcg_direction(T* p, const T* z, const double* rz_new, const double* rz, const double* stop, int n, int Q,
+                          int D, hipStream_t s, const double* sums, double inv_n);
 // layout changes between the ABI's [n][C][D] and the solver's [C][n][D] (with type conversion)
 template <typename Tin, typename Tout>
 void launch_aos_to_soa(const Tin* a, Tout* b, int n, int C, int D, hipStream_t s);
 template <typename Tin, typename Tout>
 void launch_soa_to_aos(const Tin* a, Tout* b, int n, int C, int D, hipStream_t s);
-// stop (nullable): device convergence flag; when set, alpha = beta = 0
-void launch_pcg_alpha(const double* rz, const double* pq, double* alpha, int C, hipStream_t s,
-                      const double* stop = nullptr);
-void launch_pcg_beta(const double* rz_new, double* rz, double* beta, int C, hipStream_t s,
-                     const double* stop = nullptr);
-// flags: [0] stop, [1] iterations run, [2 + m] squared residual target of case m
-void launch_pcg_check(const double* rr, int C, double* flags, hipStream_t s);
 template <typename T>
 void launch_gauge_shift(T* u, int n, int Q, int D, T* tmp, hipStream_t s);
 // v -= column mean over nodes (projection off the rigid translations)
@@ -283,10 +282,13 @@ void launch_elem_nodes(const int* elem_lin, int n_e, const int* node_map, int N,
                        hipStream_t s);
 void launch_prol_maps(const int* node_lin, int n_n, int Nf, const int* coarse_node_map, int Nc,
                       int* idx, double* w, hipStream_t s);
-// fscale (nullable, SHARED source only): per fine element scale of the shared K_e
+// fscale (nullable, SHARED source only): per fine element scale of the shared K_e;
+// terms: galerkin_term_doubles(src_kind, D) of scratch
+size_t galerkin_term_doubles(int src_kind, int D);
 void launch_galerkin(const int* elem_lin_c, int n_e_c, int Nc, const int* elem_map_f,
                      const uint8_t* cmask_f, const double* Ksrc, int src_kind, int D,
-                     const double* Ps, const double* fscale, double* out64, float* out32, hipStream_t s);
+                     const double* Ps, const double* fscale, double* terms, double* out64, float* out32,
+                     hipStream_t s);
 template <typename T>
 void launch_diagonal(const LevelView<T>& L, int kind, int D, T* diag, hipStream_t s);
 // oscale (nullable): per node octant scales of a density hierarchy
@@ -306,10 +308,30 @@ void launch_simp_sensitivity(const int* elem_lin, int n_e, const int* node_map, 
                              const double* G, double* dJ, double* dC, hipStream_t s);
 void launch_simp_filter(const double* rho, const double* dc, int N, double rmin, double gamma, double* out,
                         hipStream_t s);
-// sum over i of the OC update of element i for multiplier lam (and the update itself into out, if set)
-void launch_oc_eval(const double* rho, const double* dc, size_t n, double lam, double move, double eta, double lo,
-                    double* out, double* partial, double* total, hipStream_t s);
+// Optimality-Criteria bisection on the device (simp.hip): launch_oc_begin, then passes of
+// up to three bisection steps each until done is set, then launch_oc_write with the multiplier found
+struct OcState {
+  double lo, hi, lam;
+  int steps, done;
+};
+size_t oc_partial_doubles();
+void launch_oc_begin(OcState* st, hipStream_t s);
+void launch_oc_pass(const double* rho, const double* dc, size_t n, double target, double move, double eta, double lo,
+                    OcState* st, double* partial, hipStream_t s);
+void launch_oc_write(const double* rho, const double* dc, size_t n, double move, double eta, double lo,
+                     const OcState* st, double* out, hipStream_t s);
 void launch_random(double* x, size_t n, uint64_t seed, hipStream_t s);
+// Assembled coarse stencils (stencil.hip): coefficients and neighbour ids of level l >= 2
+// from its element matrices K (the mask table, or one per element), and the sweep.
+constexpr int kStencilAll = 4, kStencilOne = 5, kStencilTwo = 6;  // LevelView::cb: cases per thread
+size_t stencil_values(int n, int D);
+size_t stencil_ids(int n);
+template <typename T>
+void launch_stencil_build(int n, int N, int D, int kind, const int* node_lin, const int* node_map,
+                          const int* elem_map, const uint8_t* cmask, const double* K, T* stc, int* nbr, hipStream_t s);
+template <typename T>
+void launch_apply_stencil(const LevelView<T>& L, int D, int C, int epi, const T* u, const EpiArgs<T>& e,
+                          hipStream_t s);
 // inverse of the pinned coarsest operator (coarse.hip)
 size_t coarse_scratch_doubles(int n);
 void launch_coarse_inverse(const int* node_lin, const int* node_map, const int* elem_map, int N, int n_n, int D,
@@ -353,6 +375,12 @@ struct LevelData {
   float* oscale32 = nullptr;
   double* erho = nullptr;     // level 1 of a density hierarchy: rho and scale per element
   double* escale = nullptr;
+  float* stc32 = nullptr;     // levels >= 2: assembled stencils (LevelView::stc), built before the first solve
+  double* stc64 = nullptr;
+  int* snbr = nullptr;
+  // the solver's choice among their sweeps (kStencil*; 0: the element matrices are faster)
+  int scb32 = 0, sxcd32 = 1, scb64 = 0, sxcd64 = 1;
+  bool stuned32 = false, stuned64 = false, stried32 = false, stried64 = false;
   double* Kel64 = nullptr;    // per element, levels >= 3 (>= 2 for a density hierarchy)
   float* Kel32 = nullptr;
   double* diag64 = nullptr;   // [n_n][d]
@@ -385,6 +413,7 @@ struct Work {
 
 struct Hier {
   gmt_params p{};
+  bool solving = false;  // inside gmt_solve / gmt_solve_batch: the coarse sweeps may use the assembled stencils
   int N = 0, L = 0, C = 0, D = 0, Q = 0;
   std::vector<LevelData> lv;
   double Ke[576] = {0};

@@ -111,7 +111,8 @@ static int forced_l1_variant() {
 }
 
 // GMT_FORCE_COARSE_VARIANT=<cb> pins the sweep variant of levels >= 2 (0..3:
-// all cases or one case per thread, element- or neighbour-major) for tests.
+// all cases or one case per thread, element- or neighbour-major; 4..6 where the
+// level has assembled stencils) for tests.
 static int forced_coarse_variant() {
   const char* e = std::getenv("GMT_FORCE_COARSE_VARIANT");
   return e && *e ? std::atoi(e) : -1;
@@ -162,6 +163,7 @@ LevelView<T> Hier::view(int l) const {
     v.bs = d.bs64;
     v.xcd = d.xcd64;
     v.cb = d.cb64;
+    v.stc = d.stc64;
   } else {
     v.K = d.kind == KIND_SHARED ? Ke32 : (d.kind == KIND_TABLE ? table32 : d.Kel32);
     v.S = S32;
@@ -170,10 +172,18 @@ LevelView<T> Hier::view(int l) const {
     v.bs = d.bs32;
     v.xcd = d.xcd32;
     v.cb = d.cb32;
+    v.stc = d.stc32;
   }
   if (l > 0) {
+    const int scb = std::is_same<T, double>::value ? d.scb64 : d.scb32;
+    if (solving && scb) {
+      v.cb = scb;
+      v.bs = 64;
+      v.xcd = std::is_same<T, double>::value ? d.sxcd64 : d.sxcd32;
+    }
     const int f = forced_coarse_variant();
-    if (f >= 0 && f <= 3) v.cb = f;
+    if (f >= 0 && f <= (v.stc ? kStencilTwo : 3)) v.cb = f;
+    v.snbr = d.snbr;
   }
   if (l == 0) {
     const int f = forced_l1_variant();
@@ -473,7 +483,11 @@ static void apply(Hier& h, int l, int epi, const T* u, const T* f, T* out, int C
   e.omega = omega;
   e.rho1 = rho1;
   e.rho2 = rho2;
-  launch_apply<T>(view ? *view : h.view<T>(l), h.lv[l].kind, h.D, C, epi, u, e, s);
+  const LevelView<T> v = view ? *view : h.view<T>(l);
+  if (l > 0 && v.cb >= kStencilAll)
+    launch_apply_stencil<T>(v, h.D, C, epi, u, e, s);
+  else
+    launch_apply<T>(v, h.lv[l].kind, h.D, C, epi, u, e, s);
 }
 
 struct CycleCfg {
@@ -591,13 +605,26 @@ static CycleCfg make_cycle(const Hier& h, const gmt_cycle_opts* o) {
   return c;
 }
 
+// The first smoothing step from zero is u = scale D^-1 f for Jacobi and Chebyshev
+// smoothing: the kernel that produces f can write u along (launch_restrict,
+// launch_pcg_update), one launch and one pass over f less.  A single Chebyshev step
+// also leaves its direction, which those kernels do not write.
+static bool can_prime(const CycleCfg& c) {
+  return c.smoother == GMT_SMOOTH_JACOBI ? c.nu1 >= 1 : c.smoother == GMT_SMOOTH_CHEBYSHEV && c.nu1 >= 2;
+}
+static double prime_scale(const CycleCfg& c, int l) {
+  return c.smoother == GMT_SMOOTH_JACOBI ? c.omega[l] : 1.0 / (0.5 * (c.hi[l] + c.lo[l]));
+}
+
 // nu smoothing steps on level l; u / ualt are swapped so that u holds the result.
 // Gauss-Seidel (p1 = omega) runs the colours 0..7, or 7..0 when `post` (the
-// adjoint order, for the post-smoother), each colour as the residual at its
-// nodes followed by the in-place update there.
+// adjoint order, for the post-smoother), each colour as a weighted Jacobi step at
+// its nodes in place: no two of them share an element, so a node's neighbours are
+// all of other colours and nothing a sweep reads is written in it.
+// primed: the zero start's first step is in u already.
 template <typename T>
 static void smooth(Hier& h, int l, const T* f, T*& u, T*& ualt, T* dvec, int nu, bool zero_start,
-                   int smoother, double p1, double p2, hipStream_t s, bool post = false) {
+                   int smoother, double p1, double p2, hipStream_t s, bool post = false, bool primed = false) {
   const int n = h.lv[l].n_n;
   if (nu <= 0) {
     if (zero_start) launch_fill<T>(u, (size_t)n * h.Q, T(0), s);
@@ -608,15 +635,12 @@ static void smooth(Hier& h, int l, const T* f, T*& u, T*& ualt, T* dvec, int nu,
     const LevelData& d = h.lv[l];
     if (!d.col_nodes) fail(GMT_E_STATE, "colour classes of level %d are not built", l + 1);
     if (zero_start) launch_fill<T>(u, (size_t)n * h.Q, T(0), s);
-    T* r = h.work<T>().r[l];
     for (int it = 0; it < nu; ++it)
       for (int k = 0; k < 8; ++k) {
         const int c = post ? 7 - k : k;
-        const int cnt = d.col_off[c + 1] - d.col_off[c];
-        if (cnt == 0) continue;
+        if (d.col_off[c + 1] == d.col_off[c]) continue;
         const LevelView<T> v = colour_view<T>(h, l, c);
-        apply<T>(h, l, EPI_RESID, u, f, r, h.C, s, T(0), T(0), T(0), nullptr, &v);
-        launch_gs_update<T>(d.col_nodes + d.col_off[c], cnt, n, h.D, h.C, dinv, r, u, (T)p1, s);
+        apply<T>(h, l, EPI_JACOBI, u, f, u, h.C, s, (T)p1, T(0), T(0), nullptr, &v);
       }
     return;
   }
@@ -624,7 +648,7 @@ static void smooth(Hier& h, int l, const T* f, T*& u, T*& ualt, T* dvec, int nu,
     const T omega = (T)p1;
     for (int it = 0; it < nu; ++it) {
       if (it == 0 && zero_start) {
-        launch_smooth_zero<T>(n, h.D, h.C, f, dinv, omega, u, nullptr, s);
+        if (!primed) launch_smooth_zero<T>(n, h.D, h.C, f, dinv, omega, u, nullptr, s);
       } else {
         apply<T>(h, l, EPI_JACOBI, u, f, ualt, h.C, s, omega);
         std::swap(u, ualt);
@@ -642,7 +666,7 @@ static void smooth(Hier& h, int l, const T* f, T*& u, T*& ualt, T* dvec, int nu,
   bool d_in_u = false;
   if (zero_start) {
     d_in_u = nu > 1;
-    launch_smooth_zero<T>(n, h.D, h.C, f, dinv, (T)(1.0 / theta), u, d_in_u ? nullptr : dvec, s);
+    if (!primed) launch_smooth_zero<T>(n, h.D, h.C, f, dinv, (T)(1.0 / theta), u, d_in_u ? nullptr : dvec, s);
   } else {
     apply<T>(h, l, EPI_CHEB0, u, f, ualt, h.C, s, T(0), T(0), (T)(1.0 / theta), dvec);
     std::swap(u, ualt);
@@ -682,7 +706,7 @@ struct CycleState {
 // from its injected correction e_hat^{l+1} at its first entry in the cycle.
 template <typename T>
 static void cycle_visit(Hier& h, int l, bool zero_start, int sched, CycleState<T>& st, const CycleCfg& cfg,
-                        hipStream_t s) {
+                        hipStream_t s, bool primed = false) {
   Work<T>& W = h.work<T>();
   const int L = h.L;
   if (l == L - 1) {
@@ -691,26 +715,26 @@ static void cycle_visit(Hier& h, int l, bool zero_start, int sched, CycleState<T
   }
   const double p1 = cfg.smoother == GMT_SMOOTH_CHEBYSHEV ? cfg.lo[l] : cfg.omega[l];
   const double p2 = cfg.hi[l];
-  smooth<T>(h, l, st.f[l], st.cur[l], st.alt[l], W.dvec[l], cfg.nu1, zero_start, cfg.smoother, p1, p2, s);
+  smooth<T>(h, l, st.f[l], st.cur[l], st.alt[l], W.dvec[l], cfg.nu1, zero_start, cfg.smoother, p1, p2, s, false,
+            primed);
   apply<T>(h, l, EPI_RESID, st.cur[l], st.f[l], W.r[l], h.C, s);
   const int c = l + 1;
-  launch_restrict<T>(h.view<T>(l), h.view<T>(c), h.Q, h.D, W.r[l], W.f[c], s);
   st.f[c] = W.f[c];
   st.cur[c] = W.u[c];
   st.alt[c] = W.ualt[c];
-  bool zs = true;
-  if (st.e_init && st.e_init[c] && c < L - 1 && !st.entered[c]) {
-    launch_copy<T>(st.e_init[c], st.cur[c], (size_t)h.lv[c].n_n * h.Q, s);
-    zs = false;
-  }
+  const bool zs = !(st.e_init && st.e_init[c] && c < L - 1 && !st.entered[c]);
+  const bool prime = zs && c < L - 1 && can_prime(cfg);
+  launch_restrict<T>(h.view<T>(l), h.view<T>(c), h.Q, h.D, W.r[l], W.f[c], s, prime ? dinv_of<T>(h, c) : nullptr,
+                     prime ? (T)prime_scale(cfg, c) : T(0), prime ? st.cur[c] : nullptr);
+  if (!zs) launch_copy<T>(st.e_init[c], st.cur[c], (size_t)h.lv[c].n_n * h.Q, s);
   st.entered[c] = 1;
   if (sched == GMT_CYCLE_V) {
-    cycle_visit<T>(h, c, zs, GMT_CYCLE_V, st, cfg, s);
+    cycle_visit<T>(h, c, zs, GMT_CYCLE_V, st, cfg, s, prime);
   } else if (sched == GMT_CYCLE_W) {
-    cycle_visit<T>(h, c, zs, GMT_CYCLE_W, st, cfg, s);
+    cycle_visit<T>(h, c, zs, GMT_CYCLE_W, st, cfg, s, prime);
     if (c < L - 1) cycle_visit<T>(h, c, false, GMT_CYCLE_W, st, cfg, s);
   } else {
-    cycle_visit<T>(h, c, zs, GMT_CYCLE_F, st, cfg, s);
+    cycle_visit<T>(h, c, zs, GMT_CYCLE_F, st, cfg, s, prime);
     if (c < L - 1) cycle_visit<T>(h, c, false, GMT_CYCLE_V, st, cfg, s);
   }
   launch_prolong_add<T>(h.view<T>(l), h.view<T>(c), h.Q, h.D, st.cur[c], st.cur[l], s);
@@ -720,9 +744,10 @@ static void cycle_visit(Hier& h, int l, bool zero_start, int sched, CycleState<T
 // One multigrid cycle (Alg. 2; the schedule of cfg) in precision T on caller
 // buffers f0 / u0 of level l0 (the finest level for the solver; l0 > 0 runs the
 // sub-cycle of the coarser levels, used by the adjoint of the learned path).
+// primed: with u0_zero, u0 holds the first smoothing step already.
 template <typename T>
 static void vcycle(Hier& h, const T* f0, T* u0, bool u0_zero, const T* const* e_init, const CycleCfg& cfg,
-                   hipStream_t s, int l0 = 0, const T** result = nullptr) {
+                   hipStream_t s, int l0 = 0, const T** result = nullptr, bool primed = false) {
   h.ensure_work<T>();
   Work<T>& W = h.work<T>();
   const int L = h.L;
@@ -735,7 +760,7 @@ static void vcycle(Hier& h, const T* f0, T* u0, bool u0_zero, const T* const* e_
   st.cur[l0] = u0;
   st.alt[l0] = W.ualt[l0];
   st.f[l0] = f0;
-  cycle_visit<T>(h, l0, u0_zero, cfg.schedule, st, cfg, s);
+  cycle_visit<T>(h, l0, u0_zero, cfg.schedule, st, cfg, s, primed);
   // the smoothers ping-pong between u0 and a work buffer; a caller that passes
   // `result` takes the iterate where it ended (the same buffer for the same
   // cycle configuration) instead of a copy back into u0
@@ -769,11 +794,37 @@ struct Shape {
 static std::mutex g_tune_mu;
 static std::map<std::vector<int>, Shape> g_tune;
 
+// Mean time (ms) of three K.u sweeps of level l in its current launch shape, after two
+// to warm up.
+template <typename T>
+static float time_shape(Hier& h, int l, const T* x, T* y, hipEvent_t e0, hipEvent_t e1, hipStream_t s) {
+  for (int r = 0; r < 5; ++r) {
+    if (r == 2) GMT_HIP(hipEventRecord(e0, s));
+    apply<T>(h, l, EPI_KU, x, nullptr, y, h.C, s);
+  }
+  GMT_HIP(hipEventRecord(e1, s));
+  GMT_HIP(hipEventSynchronize(e1));
+  float ms = 0;
+  GMT_HIP(hipEventElapsedTime(&ms, e0, e1));
+  return ms / 3;
+}
+
+static std::vector<int> tune_key(const Hier& h, const LevelData& d, bool f32) {
+  int nb = 0;
+  while ((1 << (nb + 1)) <= d.n_n) ++nb;
+  const double dens = (double)d.n_n / ((double)d.N * d.N * d.N);
+  return {h.D, h.C, f32 ? 32 : 64, d.kind, nb, (int)(dens * 8.0), h.density ? 1 : 0};
+}
+
+static bool tune_off() {
+  const char* env = std::getenv("GMT_AUTOTUNE");
+  return env && std::string(env) == "0";
+}
+
 template <typename T>
 static void autotune(Hier& h, hipStream_t s) {
   const bool f32 = !std::is_same<T, double>::value;
-  const char* env = std::getenv("GMT_AUTOTUNE");
-  const bool off = env && std::string(env) == "0";
+  const bool off = tune_off();
   h.ensure_work<T>();
   Work<T>& W = h.work<T>();
   hipEvent_t e0 = nullptr, e1 = nullptr;
@@ -786,10 +837,7 @@ static void autotune(Hier& h, hipStream_t s) {
     if (tuned) continue;
     tuned = true;
     if (off || d.n_n == 0) continue;
-    int nb = 0;
-    while ((1 << (nb + 1)) <= d.n_n) ++nb;
-    const double dens = (double)d.n_n / ((double)d.N * d.N * d.N);
-    const std::vector<int> key = {h.D, h.C, f32 ? 32 : 64, d.kind, nb, (int)(dens * 8.0), h.density ? 1 : 0};
+    const std::vector<int> key = tune_key(h, d, f32);
     {
       std::lock_guard<std::mutex> g(g_tune_mu);
       auto it = g_tune.find(key);
@@ -827,17 +875,10 @@ static void autotune(Hier& h, hipStream_t s) {
       bs = c.bs;
       cb = c.cb;
       xcd = c.xcd;
-      for (int r = 0; r < 5; ++r) {
-        if (r == 2) GMT_HIP(hipEventRecord(e0, s));
-        apply<T>(h, l, EPI_KU, x, nullptr, y, h.C, s);
-      }
-      GMT_HIP(hipEventRecord(e1, s));
-      GMT_HIP(hipEventSynchronize(e1));
-      float ms = 0;
-      GMT_HIP(hipEventElapsedTime(&ms, e0, e1));
+      const float ms = time_shape<T>(h, l, x, y, e0, e1, s);
       if (std::getenv("GMT_TIMING"))
         fprintf(stderr, "[gmt tune]   level %d candidate bs %d cb %d xcd %d: %.1f us\n", l + 1, c.bs, c.cb, c.xcd,
-                ms * 1e3 / 3);
+                ms * 1e3);
       if (ms < best) {
         best = ms;
         pick = c;
@@ -848,7 +889,116 @@ static void autotune(Hier& h, hipStream_t s) {
     xcd = pick.xcd;
     if (std::getenv("GMT_TIMING"))
       fprintf(stderr, "[gmt tune] level %d (%s, n_n %d): bs %d cb %d xcd %d, %.1f us\n", l + 1,
-              f32 ? "f32" : "f64", d.n_n, bs, cb, xcd, best * 1e3 / 3);
+              f32 ? "f32" : "f64", d.n_n, bs, cb, xcd, best * 1e3);
+    std::lock_guard<std::mutex> g(g_tune_mu);
+    g_tune[key] = pick;
+  }
+  if (e0) (void)hipEventDestroy(e0);
+  if (e1) (void)hipEventDestroy(e1);
+}
+
+// Level 2 gets assembled stencils below this many nodes only: its element matrices
+// are a 590 KB table, so where the stencils (1.1 KB a node) do not stay in the 256 MB
+// Infinity Cache they cost more bytes than they save (512^3: 4.7 GB a sweep).  The
+// deeper levels replace matrices of twice their size.
+constexpr int kStencilTableNodes = 1 << 18;
+
+// Assembled stencils of the smoothed coarse levels for the solver's sweeps (Hier::solving):
+// in FP32, where the FP64 refinement around the cycle decides the result, and in FP64 for
+// density hierarchies.  FP64 sweeps of binary cells keep the element matrices (CG on thin
+// spinodals amplifies a change of 1e-13 in a sweep to 1e-7 in the solution), and so do the
+// entry points that return a cycle's own result or its gradient, which follow the
+// rounding of every coarse sweep (up to 1e-3 where coarse translations are weakly fixed).
+template <typename T>
+static void ensure_stencils(Hier& h, hipStream_t s) {
+  constexpr bool f32 = !std::is_same<T, double>::value;
+  if (!f32 && !h.density) return;
+  for (int l = 1; l + 1 < h.L; ++l) {
+    LevelData& d = h.lv[l];
+    if ((f32 ? (void*)d.stc32 : (void*)d.stc64) || d.n_n == 0) continue;
+    if (d.kind == KIND_TABLE && d.n_n >= kStencilTableNodes) continue;
+    bool& tried = f32 ? d.stried32 : d.stried64;
+    if (tried) continue;
+    tried = true;
+    T* stc = nullptr;
+    int* nbr = d.snbr;
+    try {
+      stc = h.alloc<T>(stencil_values(d.n_n, h.D));
+      if (!nbr) nbr = h.alloc<int>(stencil_ids(d.n_n));
+    } catch (const Failure& f) {
+      if (f.status != GMT_E_NOMEM) throw;
+    }
+    if (!stc || !nbr || (reinterpret_cast<uintptr_t>(stc) | reinterpret_cast<uintptr_t>(nbr)) % 16 != 0) {
+      // no room, or an allocator callback's memory that 16-byte reads cannot use: the
+      // sweeps keep the element matrices
+      if (stc) h.release(stc);
+      if (nbr && nbr != d.snbr) h.release(nbr);
+      continue;
+    }
+    d.snbr = nbr;
+    launch_stencil_build<T>(d.n_n, d.N, h.D, d.kind, d.node_lin, d.node_map, d.elem_map, d.cmask,
+                            d.kind == KIND_TABLE ? h.table64 : d.Kel64, stc, d.snbr, s);
+    if constexpr (f32) d.stc32 = stc;
+    else d.stc64 = stc;
+  }
+}
+
+// Builds the stencils and takes, per level, the fastest of their sweeps if it beats the
+// tuned element sweep (timed beside it; choices cached like the launch shapes).  Called
+// with a solve's other buffers in place, which have the first claim on the memory.
+template <typename T>
+static void tune_stencils(Hier& h, hipStream_t s) {
+  constexpr bool f32 = !std::is_same<T, double>::value;
+  if (tune_off()) return;
+  ensure_stencils<T>(h, s);
+  h.ensure_work<T>();
+  Work<T>& W = h.work<T>();
+  hipEvent_t e0 = nullptr, e1 = nullptr;
+  for (int l = 1; l + 1 < h.L; ++l) {
+    LevelData& d = h.lv[l];
+    bool& tuned = f32 ? d.stuned32 : d.stuned64;
+    int& cb = f32 ? d.scb32 : d.scb64;
+    int& xcd = f32 ? d.sxcd32 : d.sxcd64;
+    if (tuned || !(f32 ? (void*)d.stc32 : (void*)d.stc64)) continue;
+    tuned = true;
+    std::vector<int> key = tune_key(h, d, f32);
+    key.push_back(1);  // the stencil choice of the class
+    {
+      std::lock_guard<std::mutex> g(g_tune_mu);
+      auto it = g_tune.find(key);
+      if (it != g_tune.end()) {
+        cb = it->second.cb;
+        xcd = it->second.xcd;
+        continue;
+      }
+    }
+    if (!e0) {
+      GMT_HIP(hipEventCreate(&e0));
+      GMT_HIP(hipEventCreate(&e1));
+    }
+    launch_fill<T>(W.u[l], (size_t)d.n_n * h.Q, T(0), s);
+    const bool keep = h.solving;
+    h.solving = true;
+    Shape pick{64, 0, 1};
+    float best = INFINITY;
+    for (int c : {0, kStencilAll, kStencilOne, kStencilTwo}) {
+      if (c == kStencilTwo && h.D != 3) continue;
+      for (int x = 1; x >= (c ? 0 : 1); --x) {
+        cb = c;
+        xcd = x;
+        const float ms = time_shape<T>(h, l, W.u[l], W.r[l], e0, e1, s);
+        if (ms < best) {
+          best = ms;
+          pick = {64, c, x};
+        }
+      }
+    }
+    h.solving = keep;
+    cb = pick.cb;
+    xcd = pick.xcd;
+    if (std::getenv("GMT_TIMING"))
+      fprintf(stderr, "[gmt tune] level %d (%s, n_n %d) stencil: cb %d xcd %d, %.1f us\n", l + 1, f32 ? "f32" : "f64",
+              d.n_n, cb, xcd, best * 1e3);
     std::lock_guard<std::mutex> g(g_tune_mu);
     g_tune[key] = pick;
   }
@@ -922,7 +1072,7 @@ static int pcg(Hier& h, const T* b, T* x, const double* tol, int maxit, int chec
   const int n = h.lv[0].n_n, C = h.C, D = h.D, Q = h.Q;
   const size_t tot = (size_t)n * Q;
   double* sc = h.red_out;
-  double *rz = sc, *pq = sc + 8, *alpha = sc + 16, *beta = sc + 24, *rzn = sc + 32, *rr = sc + 40;
+  double *rz = sc, *pq = sc + 8, *rzn = sc + 32, *rr = sc + 40;  // rzn: r.z of this iteration, rz: of the last
   double* sums = sc + 200;
   double* sums_z = sc + 224;  // column sums of the preconditioned residual
   double* sums_q = sc + 100;  // column sums of K p
@@ -939,7 +1089,12 @@ static int pcg(Hier& h, const T* b, T* x, const double* tol, int maxit, int chec
   // the column sums, then the dot r.z and the direction update read z minus its
   // means (bit for bit what projecting z in place gives)
   const T* z = W.pz;
-  auto vc = [&](hipStream_t st) {
+  // primed: W.pz holds the cycle's first smoothing step (written by the update)
+  const bool prime = !MIXED && h.L > 1 && can_prime(cfg);
+  const T* p_dinv = prime ? dinv_of<T>(h, 0) : nullptr;
+  const T p_scale = prime ? (T)prime_scale(cfg, 0) : T(0);
+  T* p_z = prime ? W.pz : nullptr;
+  auto vc = [&](hipStream_t st, bool primed) {
     if constexpr (MIXED) {
       launch_convert<double, float>(W.pr, W32.pr, tot, st);
       const float* z32 = W32.pz;
@@ -947,22 +1102,14 @@ static int pcg(Hier& h, const T* b, T* x, const double* tol, int maxit, int chec
       launch_convert<float, double>(z32, W.pz, tot, st);
       z = W.pz;
     } else {
-      vcycle<T>(h, W.pr, W.pz, true, nullptr, cfg, st, 0, &z);
+      vcycle<T>(h, W.pr, W.pz, true, nullptr, cfg, st, 0, &z, primed);
     }
   };
-  // rzn = r . Pi z and p = Pi z + beta p
-  auto finish_direction = [&](hipStream_t st, const double* fl) {
-    launch_colsum<T>(z, n, Q, D, h.red_partial, sums_z, st);
-    launch_dot_centered<T>(W.pr, z, sums_z, inv_n, n, C, D, h.red_partial, rzn, st);
-    launch_pcg_beta(rzn, rz, beta, C, st, fl);
-    launch_pcg_direction<T>(W.pp, z, beta, n, Q, D, st, sums_z, inv_n);
-  };
-  vc(s);
+  vc(s, false);
   launch_colsum<T>(z, n, Q, D, h.red_partial, sums_z, s);
-  launch_dot_centered<T>(W.pr, z, sums_z, inv_n, n, C, D, h.red_partial, rz, s);
+  launch_dot_centered<T>(W.pr, z, sums_z, inv_n, n, C, D, h.red_partial, rzn, s);
   launch_fill<T>(W.pp, tot, T(0), s);
-  launch_fill<double>(beta, C, 0.0, s);
-  launch_pcg_direction<T>(W.pp, z, beta, n, Q, D, s, sums_z, inv_n);  // p = Pi z
+  launch_pcg_direction<T>(W.pp, z, nullptr, nullptr, nullptr, n, Q, D, s, sums_z, inv_n);  // p = Pi z
   int it = 0;
   double best = INFINITY;
   int since_best = 0;
@@ -983,7 +1130,7 @@ static int pcg(Hier& h, const T* b, T* x, const double* tol, int maxit, int chec
   if (graph) {
     // Device-side convergence: flags [0] stop, [1] iterations run, [2 + m] the
     // squared target of case m.  Every captured iteration ends with ||r_m||^2 and
-    // k_pcg_check, which sets the stop flag once every case meets its target;
+    // k_reduce_check, which sets the stop flag once every case meets its target;
     // from then on alpha = beta = 0, so the rest of a block (and a block
     // launched ahead) leaves x and r unchanged.
     if (!h.pcg_flags) h.pcg_flags = h.alloc<double>(16);
@@ -1008,15 +1155,12 @@ static int pcg(Hier& h, const T* b, T* x, const double* tol, int maxit, int chec
     // share one pass over r.
     auto step = [&](hipStream_t st) {
       apply<T>(h, 0, EPI_KU, W.pp, nullptr, W.pq, C, st);
-      launch_dot_colsum<T>(W.pp, W.pq, n, C, D, h.red_partial, pq, sums_q, st);
-      launch_pcg_alpha(rz, pq, alpha, C, st, fl);
-      launch_pcg_update<T>(x, W.pr, W.pp, W.pq, alpha, n, Q, D, st, sums_q, inv_n);
-      vc(st);
+      launch_dot_colsum<T>(W.pp, W.pq, n, C, D, h.red_partial, pq, sums_q, st, rzn, rz);
+      launch_pcg_update<T>(x, W.pr, W.pp, W.pq, rz, pq, fl, n, Q, D, st, sums_q, inv_n, p_dinv, p_scale, p_z);
+      vc(st, prime);
       launch_colsum<T>(z, n, Q, D, h.red_partial, sums_z, st);
-      launch_dot2_centered<T>(W.pr, z, sums_z, inv_n, n, C, D, h.red_partial, rzn, rr, st);
-      launch_pcg_beta(rzn, rz, beta, C, st, fl);
-      launch_pcg_direction<T>(W.pp, z, beta, n, Q, D, st, sums_z, inv_n);
-      launch_pcg_check(rr, C, fl, st);
+      launch_dot2_centered<T>(W.pr, z, sums_z, inv_n, n, C, D, h.red_partial, rzn, rr, fl, st);
+      launch_pcg_direction<T>(W.pp, z, rzn, rz, fl, n, Q, D, st, sums_z, inv_n);
     };
     Hier::PcgGraphs& G = MIXED ? h.gmx : graphs_of<T>(h);
     std::vector<double> key = {(double)(uintptr_t)x, (double)cfg.nu1, (double)cfg.nu2, (double)cfg.smoother,
@@ -1114,9 +1258,8 @@ static int pcg(Hier& h, const T* b, T* x, const double* tol, int maxit, int chec
   while (it < maxit) {
     ++it;
     apply<T>(h, 0, EPI_KU, W.pp, nullptr, W.pq, C, s);
-    launch_dot_colsum<T>(W.pp, W.pq, n, C, D, h.red_partial, pq, sums_q, s);
-    launch_pcg_alpha(rz, pq, alpha, C, s);
-    launch_pcg_update<T>(x, W.pr, W.pp, W.pq, alpha, n, Q, D, s, sums_q, inv_n);
+    launch_dot_colsum<T>(W.pp, W.pq, n, C, D, h.red_partial, pq, sums_q, s, rzn, rz);
+    launch_pcg_update<T>(x, W.pr, W.pp, W.pq, rz, pq, nullptr, n, Q, D, s, sums_q, inv_n, p_dinv, p_scale, p_z);
     if (it % check_every == 0 || it == maxit) {
       launch_dot<T>(W.pr, W.pr, n, C, D, h.red_partial, rr, s);
       host_dot(h, rr, C, rr_h, s);
@@ -1131,8 +1274,10 @@ static int pcg(Hier& h, const T* b, T* x, const double* tol, int maxit, int chec
         break;  // stagnation: hand back to the FP64 refinement loop
       }
     }
-    vc(s);
-    finish_direction(s, nullptr);
+    vc(s, prime);
+    launch_colsum<T>(z, n, Q, D, h.red_partial, sums_z, s);
+    launch_dot_centered<T>(W.pr, z, sums_z, inv_n, n, C, D, h.red_partial, rzn, s);
+    launch_pcg_direction<T>(W.pp, z, rzn, rz, nullptr, n, Q, D, s, sums_z, inv_n);
   }
   return it;
 }
@@ -1492,14 +1637,16 @@ static void build(Hier& h, const uint8_t* vox, hipStream_t s, const double* rho 
     launch_convert<double, float>(h.table64, h.table32, tab.size(), s);
     GMT_HIP(hipStreamSynchronize(s));
   }
+  double* terms = nullptr;  // one level at most sums shared terms (the first of the loop)
   for (int l = h.density ? 1 : 2; l < h.L; ++l) {
     LevelData& d = h.lv[l];
     const LevelData& f = h.lv[l - 1];
     d.Kel64 = h.alloc<double>((size_t)d.n_e * M * M);
     d.Kel32 = h.alloc<float>((size_t)d.n_e * M * M);
     const double* src = f.kind == KIND_SHARED ? h.Ke64 : (f.kind == KIND_TABLE ? h.table64 : f.Kel64);
+    if (!terms && galerkin_term_doubles(f.kind, D)) terms = h.alloc<double>(galerkin_term_doubles(f.kind, D));
     launch_galerkin(d.elem_lin, d.n_e, d.N, f.elem_map, f.cmask, src, f.kind, D, h.Ps,
-                    l == 1 ? h.lv[0].escale : nullptr, d.Kel64, d.Kel32, s);
+                    l == 1 ? h.lv[0].escale : nullptr, terms, d.Kel64, d.Kel32, s);
   }
   timer.mark("galerkin");
   // Jacobi diagonals
@@ -1576,6 +1723,10 @@ static void build(Hier& h, const uint8_t* vox, hipStream_t s, const double* rho 
       double* t = T64 + off[l];
       double* pl = part + (size_t)l * kRedBlocks;
       double* nrm = o + 40 + l;
+      // coarse levels: 64-wide workgroups (a wave each), which spread a small level over
+      // more of the chip; the shape does not enter the arithmetic
+      const int bs_keep = d.bs32, bs_keep64 = d.bs64;
+      if (l > 0) d.bs32 = d.bs64 = 64;
       launch_random(x, nd, h.p.seed + 0x1000193ull * (l + 1), sl);
       launch_convert<double, float>(x, x32, nd, sl);
       // x <- D^-1 K x, normalised on the device (no host round trip) every
@@ -1597,6 +1748,8 @@ static void build(Hier& h, const uint8_t* vox, hipStream_t s, const double* rho 
       launch_smooth_zero<double>(n, D, 1, x, d.diag64, 1.0, t, nullptr, sl);  // t = D x
       launch_dot<double>(x, y, n, 1, D, pl, o + 4 + 2 * l, sl);
       launch_dot<double>(x, t, n, 1, D, pl, o + 5 + 2 * l, sl);
+      d.bs32 = bs_keep;
+      d.bs64 = bs_keep64;
       if (l > 0) {
         hipEvent_t done = evs.make();
         GMT_HIP(hipEventRecord(done, sl));
@@ -1627,6 +1780,7 @@ static void build(Hier& h, const uint8_t* vox, hipStream_t s, const double* rho 
   h.lv[0].cb32 = h.lv[0].cb64 = h.density ? 8 : 9;
   GMT_HIP(hipStreamSynchronize(s));
   for (void* b : pw) h.release(b);
+  if (terms) h.release(terms);
   h.release(flags);
   h.release(scr);
   h.release(d_total);
@@ -1657,6 +1811,12 @@ static void borrow_f32_shape(Hier& h) {
   d.xcd64 = d.xcd32;
 }
 
+struct Solving {  // Hier::solving for a scope
+  Hier& h;
+  explicit Solving(Hier& hh) : h(hh) { h.solving = true; }
+  ~Solving() { h.solving = false; }
+};
+
 static void solve(Hier& h, const double* f, double* u, const gmt_solve_opts* o, gmt_solve_report* rep,
                   hipStream_t s, gmt_status* st, bool u_zero = false) {
   const double tol = o && o->tol > 0 ? o->tol : 1e-5;
@@ -1681,6 +1841,7 @@ static void solve(Hier& h, const double* f, double* u, const gmt_solve_opts* o, 
   } else {
     autotune<double>(h, s);
   }
+  const Solving scope(h);
   const int C = h.C;
   const size_t tot = (size_t)h.lv[0].n_n * h.Q;
   gmt_solve_report R{};
@@ -1755,11 +1916,13 @@ static void solve(Hier& h, const double* f, double* u, const gmt_solve_opts* o, 
     if (inner_prec == GMT_F32) {
       if (!h.s_b32) h.s_b32 = h.alloc<float>(tot);
       if (!h.s_x32) h.s_x32 = h.alloc<float>(tot);
+      scratch64(h, &h.s_usave);
+      tune_stencils<float>(h, s);
       launch_convert<double, float>(r64, h.s_b32, tot, s);
       bool reached = false;
       its += pcg<float>(h, h.s_b32, h.s_x32, itol, std::min(max_iter - its, max_inner32), check, graph, cfg, s,
                         &reached);
-      launch_copy<double>(u, scratch64(h, &h.s_usave), tot, s);
+      launch_copy<double>(u, h.s_usave, tot, s);
       launch_accumulate<float>(u, h.s_x32, tot, s, 1.0);
       last_f32 = true;
       // an FP32 inner solve that stalled, or ran into kMaxInner32, short of its
@@ -1775,6 +1938,7 @@ static void solve(Hier& h, const double* f, double* u, const gmt_solve_opts* o, 
     } else {
       if (prec == GMT_F32) autotune<double>(h, s);
       double* x64 = scratch64(h, &h.s_x64);
+      tune_stencils<double>(h, s);
       its += pcg<double>(h, r64, x64, itol, max_iter - its, check, graph, cfg, s);
       launch_accumulate<double>(u, x64, tot, s, 1.0);
       last_f32 = false;
@@ -2292,6 +2456,10 @@ gmt_status gmt_solve_batch(gmt_hier_t const* hs, int32_t n, const void* const* d
     }
     GMT_HIP(hipStreamSynchronize(S(stream)));
     for (int i = 0; i < n; ++i) prepare_solve(hs[i]->h, prec, opts, S(stream));
+    for (int i = 0; i < n; ++i) {
+      if (prec == GMT_F32) tune_stencils<float>(hs[i]->h, S(stream));
+      else tune_stencils<double>(hs[i]->h, S(stream));
+    }
     GMT_HIP(hipStreamSynchronize(S(stream)));
     // Longest-processing-time order balances the workers.  A cell's cost is its
     // unknowns times its iteration count, and the count rises steeply with the
@@ -2526,26 +2694,23 @@ gmt_status gmt_simp_oc(const double* d_rho, const double* d_dc, size_t n, double
     if (d_rho_new == d_rho || d_rho_new == d_dc) fail(GMT_E_INVAL, "d_rho_new must not alias the inputs");
     hipStream_t s = S(stream);
     double* partial = nullptr;
-    double* total = nullptr;
-    GMT_HIP(hipMallocAsync((void**)&partial, (kRedBlocks + 1) * sizeof(double), s));
-    total = partial + kRedBlocks;
-    // bisection on the multiplier: the updated volume decreases with lam
-    double lo = 0.0, hi = 1e9, lam = hi, vol = 0.0;
+    GMT_HIP(hipMallocAsync((void**)&partial, oc_partial_doubles() * sizeof(double) + sizeof(OcState), s));
+    OcState* state = reinterpret_cast<OcState*>(partial + oc_partial_doubles());
+    // bisection on the multiplier: the updated volume decreases with lam.  It takes ~76
+    // steps from [0, 1e9]; passes beyond its end return at once
     const double target = volfrac * (double)n;
-    for (int it = 0; it < 200; ++it) {
-      lam = 0.5 * (lo + hi);
-      launch_oc_eval(d_rho, d_dc, n, lam, move, eta, rho_lo, nullptr, partial, total, s);
-      GMT_HIP(hipMemcpyAsync(&vol, total, sizeof(double), hipMemcpyDeviceToHost, s));
+    OcState end{};
+    launch_oc_begin(state, s);
+    for (int passes = 26; !end.done; passes = 9) {
+      for (int k = 0; k < passes; ++k)
+        launch_oc_pass(d_rho, d_dc, n, target, move, eta, rho_lo, state, partial, s);
+      GMT_HIP(hipMemcpyAsync(&end, state, sizeof(OcState), hipMemcpyDeviceToHost, s));
       GMT_HIP(hipStreamSynchronize(s));
-      if (vol > target)
-        lo = lam;
-      else
-        hi = lam;
-      if (hi - lo <= 1e-10 * std::max(hi, 1e-30)) break;
     }
-    launch_oc_eval(d_rho, d_dc, n, lam, move, eta, rho_lo, d_rho_new, partial, total, s);
+    launch_oc_write(d_rho, d_dc, n, move, eta, rho_lo, state, d_rho_new, s);
     GMT_HIP(hipFreeAsync(partial, s));
     GMT_HIP(hipStreamSynchronize(s));
+    const double lam = end.lam;
     if (h_lambda) *h_lambda = lam;
   });
 }

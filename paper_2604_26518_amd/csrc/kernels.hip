@@ -1046,10 +1046,15 @@ __global__ void k_smooth_zero(int n, int D, int C, const T* __restrict__ f, cons
 // are all loaded before the first FMA (27 gathers in flight instead of one
 // dependent lookup-and-load per neighbour).  The sum runs over the neighbours
 // in the same order either way; absent neighbours are skipped, not added as 0.
-template <typename T, int Q, int D>
+// A thread takes CPT of the C cases (blockIdx.y picks which): all of them, or one
+// on levels too small to fill the chip, where the six cases of a thread are six
+// round trips to memory one after the other (launch_restrict).
+// With u, the coarse level's first smoothing step from zero is taken along: u =
+// scale D^-1 fc, rounded as k_smooth_zero rounds it.
+template <typename T, int Q, int D, int CPT>
 __global__ __launch_bounds__(kBlock) void k_restrict(LevelView<T> F, LevelView<T> Cv, const T* __restrict__ rf,
-                                                     T* __restrict__ fc) {
-  constexpr int C = Q / D;
+                                                     T* __restrict__ fc, const T* __restrict__ dinv, T scale,
+                                                     T* __restrict__ u) {
   const int J = xcd_block() * kBlock + threadIdx.x;
   if (J >= Cv.n_n) return;
   const int Nc = Cv.N, Nf = F.N;
@@ -1065,8 +1070,12 @@ __global__ __launch_bounds__(kBlock) void k_restrict(LevelView<T> F, LevelView<T
     const int dx = k % 3 - 1, dy = (k / 3) % 3 - 1, dz = k / 9 - 1;
     ids[k] = F.node_map[wrapm(2 * X + dx, Nf) + Nf * (wrapm(2 * Y + dy, Nf) + Nf * wrapm(2 * Z + dz, Nf))];
   }
+  T di[D];
+#pragma unroll
+  for (int d = 0; d < D; ++d) di[d] = u ? dinv[(size_t)J * D + d] : T(0);
+  const int c0 = (int)blockIdx.y * CPT;
 #pragma unroll 1
-  for (int c = 0; c < C; ++c) {
+  for (int c = c0; c < c0 + CPT; ++c) {
     T v[27][D];
 #pragma unroll
     for (int k = 0; k < 27; ++k) {
@@ -1087,6 +1096,10 @@ __global__ __launch_bounds__(kBlock) void k_restrict(LevelView<T> F, LevelView<T
     }
 #pragma unroll
     for (int d = 0; d < D; ++d) fc[vix(c, nc, J, D, d)] = acc[d];
+    if (u) {
+#pragma unroll
+      for (int d = 0; d < D; ++d) u[vix(c, nc, J, D, d)] = scale * di[d] * acc[d];
+    }
   }
 }
 
@@ -1094,11 +1107,11 @@ __global__ __launch_bounds__(kBlock) void k_restrict(LevelView<T> F, LevelView<T
 // Per axis an even fine coordinate has one parent (weight 1), an odd one two
 // (1/2 each).  The up to 8 parent ids are looked up first; then, case by case,
 // the parents' values are loaded before the first FMA.  The sum runs over the
-// parents in the same order as a loop over (z, y, x) offsets would.
-template <typename T, int Q, int D>
+// parents in the same order as a loop over (z, y, x) offsets would.  CPT: cases per
+// thread, as in k_restrict.
+template <typename T, int Q, int D, int CPT>
 __global__ __launch_bounds__(kBlock) void k_prolong_add(LevelView<T> F, LevelView<T> Cv, const T* __restrict__ uc,
                                                         T* __restrict__ uf) {
-  constexpr int C = Q / D;
   const int i = xcd_block() * kBlock + threadIdx.x;
   if (i >= F.n_n) return;
   const int Nc = Cv.N, Nf = F.N;
@@ -1119,8 +1132,9 @@ __global__ __launch_bounds__(kBlock) void k_prolong_add(LevelView<T> F, LevelVie
     if (ox < nx && oy < ny && oz < nz)  // (a consistent hierarchy has every such parent)
       pid[k] = Cv.node_map[wrapm(cx0 + ox, Nc) + Nc * (wrapm(cy0 + oy, Nc) + Nc * wrapm(cz0 + oz, Nc))];
   }
+  const int c0 = (int)blockIdx.y * CPT;
 #pragma unroll 1
-  for (int c = 0; c < C; ++c) {
+  for (int c = c0; c < c0 + CPT; ++c) {
     T acc[D], v[8][D];
 #pragma unroll
     for (int d = 0; d < D; ++d) acc[d] = uf[vix(c, nf, i, D, d)];
@@ -1149,50 +1163,49 @@ __global__ __launch_bounds__(kBlock) void k_prolong_add(LevelView<T> F, LevelVie
 // are in flight for the small coarsest systems, and add their FP64 partial
 // sums through LDS at the end.  f (all C cases) is staged in LDS in chunks of
 // kCoarseChunk DOFs, read by broadcast; the Kinv column reads (= rows by
-// symmetry) are coalesced over the 64 rows.
+// symmetry) are coalesced over the 64 rows.  Bound by the latency of those reads:
+// a grid row takes one case, 16 reads in flight per thread, so that the few
+// 64-row groups still put enough loads in flight (the matrix is read from L2 once
+// per case): 1029 rows, 6 cases, FP64: 137 us with all cases in a thread and 4
+// reads in flight, 33 us so; 192 rows, FP32: 17 us, 6.7 us.
 constexpr int kCoarseChunk = 256;
 constexpr int kCoarseSplit = 4;
-template <typename T, int C>
+template <typename T>
 __global__ __launch_bounds__(64 * kCoarseSplit) void k_coarse_solve(const T* __restrict__ Kinv, int cn, int D,
                                                                    const T* __restrict__ f, T* __restrict__ u) {
-  __shared__ T fs[kCoarseChunk * C];
-  __shared__ double part[kCoarseSplit - 1][C][64];
-  const int n = cn / D;
+  __shared__ T fs[kCoarseChunk];
+  __shared__ double part[kCoarseSplit - 1][64];
+  f += (size_t)blockIdx.y * cn;
+  u += (size_t)blockIdx.y * cn;
   const int lane = threadIdx.x & 63, split = threadIdx.x >> 6;
   const int row = blockIdx.x * 64 + lane;
-  double acc[C];
-#pragma unroll
-  for (int c = 0; c < C; ++c) acc[c] = 0.0;
+  double acc = 0.0;
   for (int j0 = 0; j0 < cn; j0 += kCoarseChunk) {
     const int m = min(kCoarseChunk, cn - j0);
     __syncthreads();
-    for (int k = threadIdx.x; k < m * C; k += 64 * kCoarseSplit) {
-      const int j = j0 + k / C, c = k % C;
-      fs[k] = f[vix(c, n, j / D, D, j % D)];
-    }
+    for (int k = threadIdx.x; k < m; k += 64 * kCoarseSplit) fs[k] = f[j0 + k];  // [n][D] of one case is contiguous
     __syncthreads();
-    if (row < cn) {
-#pragma unroll 4
-      for (int jj = split; jj < m; jj += kCoarseSplit) {
-        const double kv = (double)Kinv[(size_t)(j0 + jj) * cn + row];
+    // 16 columns at a time, all loaded before the sum; the last ones repeat a valid
+    // column and are left out of it
+    const int r = min(row, cn - 1);
+#pragma unroll 1
+    for (int jb = split; jb < m; jb += 16 * kCoarseSplit) {
+      T k[16];
 #pragma unroll
-        for (int c = 0; c < C; ++c) acc[c] += kv * (double)fs[jj * C + c];
+      for (int q = 0; q < 16; ++q) k[q] = Kinv[(size_t)(j0 + min(jb + q * kCoarseSplit, m - 1)) * cn + r];
+#pragma unroll
+      for (int q = 0; q < 16; ++q) {
+        const int jj = jb + q * kCoarseSplit;
+        if (jj < m) acc = fma((double)k[q], (double)fs[jj], acc);
       }
     }
   }
-  if (split > 0) {
-#pragma unroll
-    for (int c = 0; c < C; ++c) part[split - 1][c][lane] = acc[c];
-  }
+  if (split > 0) part[split - 1][lane] = acc;
   __syncthreads();
   if (split > 0 || row >= cn) return;
 #pragma unroll
-  for (int s2 = 0; s2 < kCoarseSplit - 1; ++s2)
-#pragma unroll
-    for (int c = 0; c < C; ++c) acc[c] += part[s2][c][lane];
-  const int node = row / D, q = row % D;
-#pragma unroll
-  for (int c = 0; c < C; ++c) u[vix(c, n, node, D, q)] = (T)acc[c];
+  for (int s2 = 0; s2 < kCoarseSplit - 1; ++s2) acc += part[s2][lane];
+  u[row] = (T)acc;
 }
 
 // ---------------------------------------------------------------- vector kernels
@@ -1387,11 +1400,13 @@ __global__ void k_mul_nodewise(T* __restrict__ v, const T* __restrict__ w, int n
   v[i] = divide ? v[i] / ww : v[i] * ww;
 }
 
-// Second stage with the values split over two outputs: k < n1 -> out1[k], else out2[k - n1].
+// Second stage with the values split over two outputs: k < n1 -> out1[k], else out2[k - n1];
+// with cur, the r.z of the last iteration becomes the previous one (prev = cur).
 __global__ void k_reduce_split(const double* __restrict__ partial, int nblocks, int nv, int n1, double* __restrict__ out1,
-                               double* __restrict__ out2) {
+                               double* __restrict__ out2, const double* __restrict__ cur, double* __restrict__ prev) {
   __shared__ double sh[kBlock];
   const int k = blockIdx.x;
+  if (cur && k < n1 && threadIdx.x == 0) prev[k] = cur[k];
   double s = 0.0;
   for (int b = threadIdx.x; b < nblocks; b += kBlock) s += partial[(size_t)b * nv + k];
   sh[threadIdx.x] = s;
@@ -1426,8 +1441,43 @@ __global__ void k_reduce_final(const double* __restrict__ partial, int nblocks, 
   }
 }
 
-// u += alpha p, r -= alpha q; with qsums, q enters with its column means removed,
-// so a residual with zero column means keeps them zero
+// Second stage of an iteration's last reduction (2 C values: r.z, r.r) and its end:
+// one workgroup, a wave per value, in the order of k_reduce_final (thread t of 256
+// sums the partials t, t + 256, .., then a tree over the threads: a lane holds the
+// threads lane + 64 k).  With flags (captured iterations): flags[1] counts the iterations
+// that ran with the flag clear; flags[0] is set once every case meets ||r_m||^2 <=
+// flags[2 + m] (the squared target) or a residual is not finite (the host reports that).
+__global__ void k_reduce_check(const double* __restrict__ partial, int nblocks, int C, double* __restrict__ rz,
+                               double* __restrict__ rr, double* __restrict__ flags) {
+  __shared__ double sh[16];
+  const int lane = threadIdx.x & 63, k = threadIdx.x >> 6, nv = 2 * C;
+  double s[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+    for (int b = lane + 64 * q; b < nblocks; b += kBlock) s[q] += partial[(size_t)b * nv + k];
+  double v = (s[0] + s[2]) + (s[1] + s[3]);
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
+  if (lane == 0) {
+    sh[k] = v;
+    if (k < C) rz[k] = v;
+    else rr[k - C] = v;
+  }
+  if (!flags) return;
+  __syncthreads();
+  if (threadIdx.x != 0 || flags[0] != 0.0) return;
+  flags[1] += 1.0;
+  bool done = true;
+  for (int c = 0; c < C; ++c) {
+    if (!isfinite(sh[C + c])) {
+      done = true;
+      break;
+    }
+    if (!(sh[C + c] <= flags[2 + c])) done = false;
+  }
+  if (done) flags[0] = 1.0;
+}
+
 // the D column means of case row c of a [C][n][D] vector, rounded to T (zero without sums)
 template <typename T, int D>
 __device__ __forceinline__ void case_means(const double* __restrict__ sums, double inv_n, int c, T (&m)[D]) {
@@ -1435,71 +1485,90 @@ __device__ __forceinline__ void case_means(const double* __restrict__ sums, doub
   for (int d = 0; d < D; ++d) m[d] = sums ? (T)(sums[c * D + d] * inv_n) : T(0);
 }
 
+// num[c] / den[c] of a CG step for the whole workgroup (alpha = r.z / p.q, which must
+// be positive, or beta = r.z / the previous r.z): 0 where it is undefined or once the
+// device-side convergence flag (nullable) is set, after which the remaining iterations
+// of a block change nothing.  One lane divides.
+template <bool POSITIVE>
+__device__ __forceinline__ double cg_ratio(const double* __restrict__ num, const double* __restrict__ den, int c,
+                                           const double* __restrict__ stop) {
+  __shared__ double ratio;
+  if (threadIdx.x == 0) {
+    const bool off = stop && *stop != 0.0;
+    const double a = num[c], b = den[c];
+    ratio = !off && (POSITIVE ? b > 0.0 : b != 0.0) && isfinite(a / b) ? a / b : 0.0;
+  }
+  __syncthreads();
+  return ratio;
+}
+
+// u += alpha p, r -= alpha q; with qsums, q enters with its column means removed,
+// so a residual with zero column means keeps them zero.  With z, the V-cycle's first
+// smoothing step from zero is taken along: z = scale D^-1 r, rounded as k_smooth_zero
+// rounds it.
+// Both vector kernels of an iteration are bound by HBM (512^3, 2.4 GB a vector: 4.05 and
+// 1.40 ms, 4.2 and 5.2 TB/s); a thread takes kVecItems values, all read before the ratio's
+// barrier, which otherwise held every workgroup's loads back (4.06 and 1.90 ms with one value).
+constexpr int kVecItems = 4;
 template <typename T, int D>
-__global__ void k_pcg_update(T* __restrict__ u, T* __restrict__ r, const T* __restrict__ p,
-                             const T* __restrict__ q, const double* __restrict__ alpha, int n,
-                             const double* __restrict__ qsums, double inv_n) {
+__global__ __launch_bounds__(kBlock) void k_pcg_update(T* __restrict__ u, T* __restrict__ r, const T* __restrict__ p,
+                                                       const T* __restrict__ q, const double* __restrict__ rz,
+                                                       const double* __restrict__ pq, const double* __restrict__ stop,
+                                                       int n, const double* __restrict__ qsums, double inv_n,
+                                                       const T* __restrict__ dinv, T scale, T* __restrict__ z) {
   // grid row = case
-  const int j = blockIdx.x * kBlock + threadIdx.x;
-  if (j >= n * D) return;
-  const size_t i = (size_t)blockIdx.y * n * D + j;
-  const T a = (T)alpha[blockIdx.y];
+  const unsigned j0 = blockIdx.x * (kVecItems * kBlock) + threadIdx.x, nD = (unsigned)n * D;
+  const size_t row = (size_t)blockIdx.y * nD;
+  T uv[kVecItems], pv[kVecItems], qv[kVecItems], rv[kVecItems], dv[kVecItems];
+#pragma unroll
+  for (int k = 0; k < kVecItems; ++k) {
+    const unsigned j = j0 + k * kBlock < nD ? j0 + k * kBlock : nD - 1;
+    uv[k] = u[row + j];
+    pv[k] = p[row + j];
+    qv[k] = q[row + j];
+    rv[k] = r[row + j];
+    dv[k] = z ? dinv[j] : T(0);
+  }
+  const T a = (T)cg_ratio<true>(rz, pq, blockIdx.y, stop);
   T m[D];
   case_means<T, D>(qsums, inv_n, blockIdx.y, m);
-  u[i] = fma(a, p[i], u[i]);
-  r[i] = fma(-a, q[i] - m[j % D], r[i]);
+#pragma unroll
+  for (int k = 0; k < kVecItems; ++k) {
+    const unsigned j = j0 + k * kBlock;
+    if (j >= nD) break;
+    u[row + j] = fma(a, pv[k], uv[k]);
+    const T rn = fma(-a, qv[k] - m[j % D], rv[k]);
+    r[row + j] = rn;
+    if (z) z[row + j] = scale * dv[k] * rn;
+  }
 }
 
 // p = z + beta p; with sums, z enters with its column means removed (as k_sub_mean
-// would have written it)
+// would have written it); without rz_new, beta = 0
 template <typename T, int D>
-__global__ void k_pcg_direction(T* __restrict__ p, const T* __restrict__ z, const double* __restrict__ beta, int n,
-                                const double* __restrict__ sums, double inv_n) {
+__global__ __launch_bounds__(kBlock) void k_pcg_direction(T* __restrict__ p, const T* __restrict__ z,
+                                                          const double* __restrict__ rz_new,
+                                                          const double* __restrict__ rz,
+                                                          const double* __restrict__ stop, int n,
+                                                          const double* __restrict__ sums, double inv_n) {
   // grid row = case
-  const int j = blockIdx.x * kBlock + threadIdx.x;
-  if (j >= n * D) return;
-  const size_t i = (size_t)blockIdx.y * n * D + j;
-  const T b = (T)beta[blockIdx.y];
+  const unsigned j0 = blockIdx.x * (kVecItems * kBlock) + threadIdx.x, nD = (unsigned)n * D;
+  const size_t row = (size_t)blockIdx.y * nD;
+  T pv[kVecItems], zv[kVecItems];
+#pragma unroll
+  for (int k = 0; k < kVecItems; ++k) {
+    const unsigned j = j0 + k * kBlock < nD ? j0 + k * kBlock : nD - 1;
+    pv[k] = p[row + j];
+    zv[k] = z[row + j];
+  }
+  const T b = rz_new ? (T)cg_ratio<false>(rz_new, rz, blockIdx.y, stop) : T(0);
   T m[D];
   case_means<T, D>(sums, inv_n, blockIdx.y, m);
-  p[i] = fma(b, p[i], z[i] - m[j % D]);
-}
-
-// stop (nullable): the device-side convergence flag of captured PCG blocks; once
-// set, alpha = beta = 0 and the remaining iterations of a block change nothing
-__global__ void k_pcg_alpha(const double* rz, const double* pq, double* alpha, int C, const double* stop) {
-  int c = threadIdx.x;
-  const bool off = stop && *stop != 0.0;
-  if (c < C) alpha[c] = (!off && pq[c] > 0.0 && isfinite(rz[c] / pq[c])) ? rz[c] / pq[c] : 0.0;
-}
-
-__global__ void k_pcg_beta(const double* rz_new, double* rz, double* beta, int C, const double* stop) {
-  int c = threadIdx.x;
-  if (c < C) {
-    if (stop && *stop != 0.0) {
-      beta[c] = 0.0;
-      return;
-    }
-    beta[c] = (rz[c] != 0.0 && isfinite(rz_new[c] / rz[c])) ? rz_new[c] / rz[c] : 0.0;
-    rz[c] = rz_new[c];
+#pragma unroll
+  for (int k = 0; k < kVecItems; ++k) {
+    const unsigned j = j0 + k * kBlock;
+    if (j < nD) p[row + j] = fma(b, pv[k], zv[k] - m[j % D]);
   }
-}
-
-// End of a captured PCG iteration: flags[1] counts the iterations that ran with
-// the flag clear; flags[0] is set once every case meets ||r_m||^2 <= flags[2 + m]
-// (the squared target) or a residual is not finite (the host reports that).
-__global__ void k_pcg_check(const double* rr, int C, double* flags) {
-  if (threadIdx.x != 0 || flags[0] != 0.0) return;
-  flags[1] += 1.0;
-  bool done = true;
-  for (int c = 0; c < C; ++c) {
-    if (!isfinite(rr[c])) {
-      done = true;
-      break;
-    }
-    if (!(rr[c] <= flags[2 + c])) done = false;
-  }
-  if (done) flags[0] = 1.0;
 }
 
 template <typename T>
@@ -1624,65 +1693,6 @@ __global__ void k_prol_maps(const int* __restrict__ node_lin, int n_n, int Nf, c
     }
     if (idx) idx[(size_t)i * 8 + k] = id;
     if (w) w[(size_t)i * 8 + k] = wk;
-  }
-}
-
-// Local Galerkin projection (Sec. 4.6): K_E = sum_{active children c} P_c^T K_c P_c,
-// P_c = Ps_c (8x8 trilinear weights) (x) I_D.  One block per coarse element.
-template <int D>
-__global__ __launch_bounds__(kBlock) void k_galerkin(const int* __restrict__ elem_lin_c, int Nc,
-                                                     const int* __restrict__ emap_f,
-                                                     const uint8_t* __restrict__ cmask_f,
-                                                     const double* __restrict__ Ksrc, int src_kind,
-                                                     const double* __restrict__ Ps,
-                                                     const double* __restrict__ fscale, double* __restrict__ out64,
-                                                     float* __restrict__ out32) {
-  constexpr int M = 8 * D;
-  __shared__ double Kc[M * M];
-  __shared__ double T1[M * M];
-  __shared__ double acc[M * M];
-  __shared__ double P[64];
-  const int e = blockIdx.x;
-  const int Nf = 2 * Nc;
-  const int lin = elem_lin_c[e];
-  const int X = lin % Nc, Y = (lin / Nc) % Nc, Z = lin / (Nc * Nc);
-  for (int t = threadIdx.x; t < M * M; t += kBlock) acc[t] = 0.0;
-  for (int c = 0; c < 8; ++c) {
-    const int fx = 2 * X + (c & 1), fy = 2 * Y + ((c >> 1) & 1), fz = 2 * Z + ((c >> 2) & 1);
-    const int fid = emap_f[fx + Nf * (fy + Nf * fz)];
-    if (fid < 0) continue;  // uniform across the block
-    const double* src = src_kind == KIND_SHARED ? Ksrc
-                        : src_kind == KIND_TABLE ? Ksrc + (size_t)cmask_f[fid] * M * M
-                                                 : Ksrc + (size_t)fid * M * M;
-    const double sc = fscale ? fscale[fid] : 1.0;  // density hierarchy: the child's stiffness scale
-    __syncthreads();
-    for (int t = threadIdx.x; t < M * M; t += kBlock) Kc[t] = sc * src[t];
-    if (threadIdx.x < 64) P[threadIdx.x] = Ps[c * 64 + threadIdx.x];
-    __syncthreads();
-    // T1[(m,i),(p,j)] = sum_n Kc[(m,i),(n,j)] P[n][p]
-    for (int t = threadIdx.x; t < M * M; t += kBlock) {
-      const int row = t / M, col = t % M;
-      const int p = col / D, j = col % D;
-      double s = 0.0;
-#pragma unroll
-      for (int n = 0; n < 8; ++n) s += Kc[row * M + n * D + j] * P[n * 8 + p];
-      T1[t] = s;
-    }
-    __syncthreads();
-    // acc[(o,i),(p,j)] += sum_m P[m][o] T1[(m,i),(p,j)]
-    for (int t = threadIdx.x; t < M * M; t += kBlock) {
-      const int row = t / M, col = t % M;
-      const int o = row / D, i = row % D;
-      double s = 0.0;
-#pragma unroll
-      for (int m = 0; m < 8; ++m) s += P[m * 8 + o] * T1[(m * D + i) * M + col];
-      acc[t] += s;
-    }
-  }
-  __syncthreads();
-  for (int t = threadIdx.x; t < M * M; t += kBlock) {
-    out64[(size_t)e * M * M + t] = acc[t];
-    out32[(size_t)e * M * M + t] = (float)acc[t];
   }
 }
 
@@ -1876,32 +1886,6 @@ __global__ void k_simp_filter(const double* __restrict__ rho, const double* __re
   out[e] = num / (fmax(gamma, rho[e]) * den);
 }
 
-// OC update of element i for multiplier lam, clipped to the move limit and [lo, 1];
-// per-block sums of the updated densities into partial[blockIdx.x]
-__global__ __launch_bounds__(kBlock) void k_oc_eval(const double* __restrict__ rho, const double* __restrict__ dc,
-                                                    size_t n, double lam, double move, double eta, double lo,
-                                                    double* __restrict__ out, double* __restrict__ partial) {
-  __shared__ double sh[kBlock / 64];
-  double acc = 0.0;
-  for (size_t i = (size_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += (size_t)gridDim.x * kBlock) {
-    const double r = rho[i];
-    const double B = fmax(-dc[i], 0.0);
-    const double cand = r * pow(B / lam, eta);
-    const double v = fmin(fmin(1.0, r + move), fmax(cand, fmax(lo, r - move)));
-    if (out) out[i] = v;
-    acc += v;
-  }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) acc += __shfl_down(acc, o, 64);
-  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = acc;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    double t = 0.0;
-    for (int k = 0; k < kBlock / 64; ++k) t += sh[k];
-    partial[blockIdx.x] = t;
-  }
-}
-
 // counter-based uniform(-1,1) values (splitmix64 finaliser of seed + index)
 __global__ void k_random(double* __restrict__ x, size_t n, uint64_t seed) {
   size_t i = (size_t)blockIdx.x * kBlock + threadIdx.x;
@@ -1914,20 +1898,6 @@ __global__ void k_random(double* __restrict__ x, size_t n, uint64_t seed) {
 }
 
 inline unsigned blocks_for(size_t n) { return (unsigned)((n + kBlock - 1) / kBlock); }
-
-// One colour of the Gauss-Seidel smoother (Sec. 4.6): u_i += omega D_i^-1 r_i
-// for the listed nodes, r the residual of the current iterate at those nodes.
-// No two listed nodes share an element, so the updates are independent.
-template <typename T>
-__global__ void k_gs_update(const int* __restrict__ list, int n_list, int n, int D, const T* __restrict__ dinv,
-                            const T* __restrict__ r, T* __restrict__ u, T omega) {
-  const size_t t = (size_t)blockIdx.x * kBlock + threadIdx.x;
-  if (t >= (size_t)n_list * D) return;
-  const int i = list[t / D];
-  const int q = (int)(t % D);
-  const size_t idx = vix((int)blockIdx.y, (size_t)n, (size_t)i, D, q);
-  u[idx] += omega * dinv[(size_t)i * D + q] * r[idx];
-}
 
 }  // namespace
 
@@ -2075,38 +2045,55 @@ void launch_normalize(const T* src, size_t n, const double* nrm2, T* dst, hipStr
   GMT_LAUNCH_CHECK();
 }
 
+// Transfers over fewer threads than this run one case per thread (six times the
+// threads and index lookups, a sixth of the chain): 18 k / 3.5 k nodes, restriction
+// 11 -> 5.6 us, prolongation 12 -> 4.7 us.
+constexpr int kTransferSplit = 1 << 16;
+
 template <typename T>
-void launch_restrict(const LevelView<T>& F, const LevelView<T>& Cv, int Q, int D, const T* rf, T* fc, hipStream_t s) {
+void launch_restrict(const LevelView<T>& F, const LevelView<T>& Cv, int Q, int D, const T* rf, T* fc, hipStream_t s,
+                     const T* dinv, T scale, T* u) {
   const unsigned g = blocks_for(Cv.n_n);
   if (!g) return;
-  if (Q == 18 && D == 3) hipLaunchKernelGGL((k_restrict<T, 18, 3>), dim3(g), dim3(kBlock), 0, s, F, Cv, rf, fc);
-  else if (Q == 3 && D == 1) hipLaunchKernelGGL((k_restrict<T, 3, 1>), dim3(g), dim3(kBlock), 0, s, F, Cv, rf, fc);
-  else if (Q == 3 && D == 3) hipLaunchKernelGGL((k_restrict<T, 3, 3>), dim3(g), dim3(kBlock), 0, s, F, Cv, rf, fc);
-  else if (Q == 1 && D == 1) hipLaunchKernelGGL((k_restrict<T, 1, 1>), dim3(g), dim3(kBlock), 0, s, F, Cv, rf, fc);
-  else fail(GMT_E_INVAL, "unsupported (Q, D) = (%d, %d)", Q, D);
-  GMT_LAUNCH_CHECK();
+  const bool split = Cv.n_n < kTransferSplit;
+#define GMT_RESTRICT(QQ, DD)                                                                                        \
+  if (Q == QQ && D == DD) {                                                                                         \
+    if (split)                                                                                                      \
+      hipLaunchKernelGGL((k_restrict<T, QQ, DD, 1>), dim3(g, QQ / DD), dim3(kBlock), 0, s, F, Cv, rf, fc, dinv,      \
+                         scale, u);                                                                                 \
+    else                                                                                                            \
+      hipLaunchKernelGGL((k_restrict<T, QQ, DD, QQ / DD>), dim3(g), dim3(kBlock), 0, s, F, Cv, rf, fc, dinv, scale, u); \
+    GMT_LAUNCH_CHECK();                                                                                             \
+    return;                                                                                                         \
+  }
+  GMT_RESTRICT(18, 3) GMT_RESTRICT(3, 1)
+#undef GMT_RESTRICT
+  fail(GMT_E_INVAL, "unsupported (Q, D) = (%d, %d)", Q, D);
 }
 
 template <typename T>
 void launch_prolong_add(const LevelView<T>& F, const LevelView<T>& Cv, int Q, int D, const T* uc, T* uf, hipStream_t s) {
   const unsigned g = blocks_for(F.n_n);
   if (!g) return;
-  if (Q == 18 && D == 3) hipLaunchKernelGGL((k_prolong_add<T, 18, 3>), dim3(g), dim3(kBlock), 0, s, F, Cv, uc, uf);
-  else if (Q == 3 && D == 1) hipLaunchKernelGGL((k_prolong_add<T, 3, 1>), dim3(g), dim3(kBlock), 0, s, F, Cv, uc, uf);
-  else if (Q == 3 && D == 3) hipLaunchKernelGGL((k_prolong_add<T, 3, 3>), dim3(g), dim3(kBlock), 0, s, F, Cv, uc, uf);
-  else if (Q == 1 && D == 1) hipLaunchKernelGGL((k_prolong_add<T, 1, 1>), dim3(g), dim3(kBlock), 0, s, F, Cv, uc, uf);
-  else fail(GMT_E_INVAL, "unsupported (Q, D) = (%d, %d)", Q, D);
-  GMT_LAUNCH_CHECK();
+  const bool split = F.n_n < kTransferSplit;
+#define GMT_PROLONG(QQ, DD)                                                                                         \
+  if (Q == QQ && D == DD) {                                                                                         \
+    if (split)                                                                                                      \
+      hipLaunchKernelGGL((k_prolong_add<T, QQ, DD, 1>), dim3(g, QQ / DD), dim3(kBlock), 0, s, F, Cv, uc, uf);        \
+    else                                                                                                            \
+      hipLaunchKernelGGL((k_prolong_add<T, QQ, DD, QQ / DD>), dim3(g), dim3(kBlock), 0, s, F, Cv, uc, uf);           \
+    GMT_LAUNCH_CHECK();                                                                                             \
+    return;                                                                                                         \
+  }
+  GMT_PROLONG(18, 3) GMT_PROLONG(3, 1)
+#undef GMT_PROLONG
+  fail(GMT_E_INVAL, "unsupported (Q, D) = (%d, %d)", Q, D);
 }
 
 template <typename T>
 void launch_coarse_solve(const T* cinv, int cn, int D, int C, const T* f, T* u, hipStream_t s) {
-  const unsigned g = (unsigned)((cn + 63) / 64);
-  const dim3 b(64 * kCoarseSplit);
-  if (C == 6) hipLaunchKernelGGL((k_coarse_solve<T, 6>), dim3(g), b, 0, s, cinv, cn, D, f, u);
-  else if (C == 3) hipLaunchKernelGGL((k_coarse_solve<T, 3>), dim3(g), b, 0, s, cinv, cn, D, f, u);
-  else if (C == 1) hipLaunchKernelGGL((k_coarse_solve<T, 1>), dim3(g), b, 0, s, cinv, cn, D, f, u);
-  else fail(GMT_E_INVAL, "unsupported C=%d", C);
+  const dim3 g((unsigned)((cn + 63) / 64), (unsigned)C);
+  hipLaunchKernelGGL((k_coarse_solve<T>), g, dim3(64 * kCoarseSplit), 0, s, cinv, cn, D, f, u);
   GMT_LAUNCH_CHECK();
 }
 
@@ -2133,15 +2120,6 @@ template <typename T>
 void launch_inv(const T* a, T* b, size_t n, hipStream_t s) {
   if (!n) return;
   hipLaunchKernelGGL(k_inv<T>, dim3(blocks_for(n)), dim3(kBlock), 0, s, a, b, n);
-  GMT_LAUNCH_CHECK();
-}
-
-template <typename T>
-void launch_gs_update(const int* list, int n_list, int n, int D, int C, const T* dinv, const T* r, T* u, T omega,
-                      hipStream_t s) {
-  if (n_list <= 0) return;
-  hipLaunchKernelGGL(k_gs_update<T>, dim3(blocks_for((size_t)n_list * D), C), dim3(kBlock), 0, s, list, n_list, n, D,
-                     dinv, r, u, omega);
   GMT_LAUNCH_CHECK();
 }
 
@@ -2242,15 +2220,18 @@ void launch_project(T* v, int n, int Q, int D, double* partial, double* sums, hi
 }
 
 template <typename T>
-void launch_pcg_update(T* u, T* r, const T* p, const T* q, const double* alpha, int n, int Q, int D,
-                       hipStream_t s, const double* qsums, double inv_n) {
+void launch_pcg_update(T* u, T* r, const T* p, const T* q, const double* rz, const double* pq, const double* stop,
+                       int n, int Q, int D, hipStream_t s, const double* qsums, double inv_n, const T* dinv, T scale,
+                       T* z) {
   const size_t tot = (size_t)n * Q;
   if (!tot) return;
-  const dim3 g(blocks_for((size_t)n * D), Q / D);
+  const dim3 g((unsigned)(((size_t)n * D + kVecItems * kBlock - 1) / (kVecItems * kBlock)), Q / D);
   if (D == 3)
-    hipLaunchKernelGGL((k_pcg_update<T, 3>), g, dim3(kBlock), 0, s, u, r, p, q, alpha, n, qsums, inv_n);
+    hipLaunchKernelGGL((k_pcg_update<T, 3>), g, dim3(kBlock), 0, s, u, r, p, q, rz, pq, stop, n, qsums, inv_n, dinv,
+                       scale, z);
   else if (D == 1)
-    hipLaunchKernelGGL((k_pcg_update<T, 1>), g, dim3(kBlock), 0, s, u, r, p, q, alpha, n, qsums, inv_n);
+    hipLaunchKernelGGL((k_pcg_update<T, 1>), g, dim3(kBlock), 0, s, u, r, p, q, rz, pq, stop, n, qsums, inv_n, dinv,
+                       scale, z);
   else
     fail(GMT_E_INVAL, "unsupported d = %d", D);
   GMT_LAUNCH_CHECK();
@@ -2258,19 +2239,20 @@ void launch_pcg_update(T* u, T* r, const T* p, const T* q, const double* alpha, 
 
 template <typename T>
 void launch_dot_colsum(const T* a, const T* b, int n, int C, int D, double* partial, double* dots, double* sums,
-                       hipStream_t s) {
+                       hipStream_t s, const double* cur, double* prev) {
   const unsigned g = red_grid(n);
   if (C == 6 && D == 3) hipLaunchKernelGGL((k_dot_colsum<T, 6, 3>), dim3(g), dim3(kBlock), 0, s, a, b, n, partial);
   else if (C == 3 && D == 1) hipLaunchKernelGGL((k_dot_colsum<T, 3, 1>), dim3(g), dim3(kBlock), 0, s, a, b, n, partial);
   else fail(GMT_E_INVAL, "unsupported (c, d)");
   GMT_LAUNCH_CHECK();
-  hipLaunchKernelGGL(k_reduce_split, dim3(C + C * D), dim3(kBlock), 0, s, partial, (int)g, C + C * D, C, dots, sums);
+  hipLaunchKernelGGL(k_reduce_split, dim3(C + C * D), dim3(kBlock), 0, s, partial, (int)g, C + C * D, C, dots, sums,
+                     cur, prev);
   GMT_LAUNCH_CHECK();
 }
 
 template <typename T>
 void launch_dot2_centered(const T* r, const T* z, const double* sums, double inv_n, int n, int C, int D,
-                          double* partial, double* rz, double* rr, hipStream_t s) {
+                          double* partial, double* rz, double* rr, double* flags, hipStream_t s) {
   const unsigned g = red_grid(n);
   if (C == 6 && D == 3)
     hipLaunchKernelGGL((k_dot2_centered<T, 6, 3>), dim3(g), dim3(kBlock), 0, s, r, z, n, sums, inv_n, partial);
@@ -2279,37 +2261,22 @@ void launch_dot2_centered(const T* r, const T* z, const double* sums, double inv
   else
     fail(GMT_E_INVAL, "unsupported (c, d)");
   GMT_LAUNCH_CHECK();
-  hipLaunchKernelGGL(k_reduce_split, dim3(2 * C), dim3(kBlock), 0, s, partial, (int)g, 2 * C, C, rz, rr);
+  hipLaunchKernelGGL(k_reduce_check, dim3(1), dim3(64 * 2 * C), 0, s, partial, (int)g, C, rz, rr, flags);
   GMT_LAUNCH_CHECK();
 }
 
 template <typename T>
-void launch_pcg_direction(T* p, const T* z, const double* beta, int n, int Q, int D, hipStream_t s,
-                          const double* sums, double inv_n) {
+void launch_pcg_direction(T* p, const T* z, const double* rz_new, const double* rz, const double* stop, int n, int Q,
+                          int D, hipStream_t s, const double* sums, double inv_n) {
   const size_t tot = (size_t)n * Q;
   if (!tot) return;
-  const dim3 g(blocks_for((size_t)n * D), Q / D);
+  const dim3 g((unsigned)(((size_t)n * D + kVecItems * kBlock - 1) / (kVecItems * kBlock)), Q / D);
   if (D == 3)
-    hipLaunchKernelGGL((k_pcg_direction<T, 3>), g, dim3(kBlock), 0, s, p, z, beta, n, sums, inv_n);
+    hipLaunchKernelGGL((k_pcg_direction<T, 3>), g, dim3(kBlock), 0, s, p, z, rz_new, rz, stop, n, sums, inv_n);
   else if (D == 1)
-    hipLaunchKernelGGL((k_pcg_direction<T, 1>), g, dim3(kBlock), 0, s, p, z, beta, n, sums, inv_n);
+    hipLaunchKernelGGL((k_pcg_direction<T, 1>), g, dim3(kBlock), 0, s, p, z, rz_new, rz, stop, n, sums, inv_n);
   else
     fail(GMT_E_INVAL, "unsupported d = %d", D);
-  GMT_LAUNCH_CHECK();
-}
-
-void launch_pcg_alpha(const double* rz, const double* pq, double* alpha, int C, hipStream_t s, const double* stop) {
-  hipLaunchKernelGGL(k_pcg_alpha, dim3(1), dim3(64), 0, s, rz, pq, alpha, C, stop);
-  GMT_LAUNCH_CHECK();
-}
-
-void launch_pcg_beta(const double* rz_new, double* rz, double* beta, int C, hipStream_t s, const double* stop) {
-  hipLaunchKernelGGL(k_pcg_beta, dim3(1), dim3(64), 0, s, rz_new, rz, beta, C, stop);
-  GMT_LAUNCH_CHECK();
-}
-
-void launch_pcg_check(const double* rr, int C, double* flags, hipStream_t s) {
-  hipLaunchKernelGGL(k_pcg_check, dim3(1), dim3(64), 0, s, rr, C, flags);
   GMT_LAUNCH_CHECK();
 }
 
@@ -2403,19 +2370,6 @@ void launch_prol_maps(const int* node_lin, int n_n, int Nf, const int* cmap, int
                       hipStream_t s) {
   if (!n_n) return;
   hipLaunchKernelGGL(k_prol_maps, dim3(blocks_for(n_n)), dim3(kBlock), 0, s, node_lin, n_n, Nf, cmap, Nc, idx, w);
-  GMT_LAUNCH_CHECK();
-}
-
-void launch_galerkin(const int* elem_lin_c, int n_e_c, int Nc, const int* emap_f, const uint8_t* cmask_f,
-                     const double* Ksrc, int src_kind, int D, const double* Ps, const double* fscale, double* out64,
-                     float* out32, hipStream_t s) {
-  if (!n_e_c) return;
-  if (D == 3)
-    hipLaunchKernelGGL(k_galerkin<3>, dim3(n_e_c), dim3(kBlock), 0, s, elem_lin_c, Nc, emap_f, cmask_f, Ksrc,
-                       src_kind, Ps, fscale, out64, out32);
-  else
-    hipLaunchKernelGGL(k_galerkin<1>, dim3(n_e_c), dim3(kBlock), 0, s, elem_lin_c, Nc, emap_f, cmask_f, Ksrc,
-                       src_kind, Ps, fscale, out64, out32);
   GMT_LAUNCH_CHECK();
 }
 
@@ -2517,16 +2471,6 @@ void launch_simp_filter(const double* rho, const double* dc, int N, double rmin,
   GMT_LAUNCH_CHECK();
 }
 
-void launch_oc_eval(const double* rho, const double* dc, size_t n, double lam, double move, double eta, double lo,
-                    double* out, double* partial, double* total, hipStream_t s) {
-  if (!n) return;
-  const unsigned g = std::min<unsigned>(kRedBlocks, blocks_for(n));
-  hipLaunchKernelGGL(k_oc_eval, dim3(g), dim3(kBlock), 0, s, rho, dc, n, lam, move, eta, lo, out, partial);
-  GMT_LAUNCH_CHECK();
-  hipLaunchKernelGGL(k_reduce_final, dim3(1), dim3(kBlock), 0, s, partial, (int)g, 1, total);
-  GMT_LAUNCH_CHECK();
-}
-
 void launch_random(double* x, size_t n, uint64_t seed, hipStream_t s) {
   if (!n) return;
   hipLaunchKernelGGL(k_random, dim3(blocks_for(n)), dim3(kBlock), 0, s, x, n, seed);
@@ -2540,7 +2484,7 @@ void launch_random(double* x, size_t n, uint64_t seed, hipStream_t s) {
                                 hipStream_t);                                                                \
   template void launch_smooth_zero<T>(int, int, int, const T*, const T*, T, T*, T*, hipStream_t);            \
   template void launch_restrict<T>(const LevelView<T>&, const LevelView<T>&, int, int, const T*, T*,         \
-                                   hipStream_t);                                                              \
+                                   hipStream_t, const T*, T, T*);                                             \
   template void launch_prolong_add<T>(const LevelView<T>&, const LevelView<T>&, int, int, const T*, T*,      \
                                       hipStream_t);                                                          \
   template void launch_coarse_solve<T>(const T*, int, int, int, const T*, T*, hipStream_t);                  \
@@ -2549,13 +2493,14 @@ void launch_random(double* x, size_t n, uint64_t seed, hipStream_t s) {
   template void launch_inv<T>(const T*, T*, size_t, hipStream_t);                                            \
   template void launch_dot<T>(const T*, const T*, int, int, int, double*, double*, hipStream_t);             \
   template void launch_normalize<T>(const T*, size_t, const double*, T*, hipStream_t);                     \
-  template void launch_pcg_update<T>(T*, T*, const T*, const T*, const double*, int, int, int, hipStream_t,     \
-                                     const double*, double);                                                   \
-  template void launch_dot_colsum<T>(const T*, const T*, int, int, int, double*, double*, double*, hipStream_t); \
+  template void launch_pcg_update<T>(T*, T*, const T*, const T*, const double*, const double*, const double*,   \
+                                     int, int, int, hipStream_t, const double*, double, const T*, T, T*);      \
+  template void launch_dot_colsum<T>(const T*, const T*, int, int, int, double*, double*, double*, hipStream_t, \
+                                     const double*, double*);                                                  \
   template void launch_dot2_centered<T>(const T*, const T*, const double*, double, int, int, int, double*, double*, \
-                                        double*, hipStream_t);                                                 \
-  template void launch_pcg_direction<T>(T*, const T*, const double*, int, int, int, hipStream_t, const double*, \
-                                        double);                                                               \
+                                        double*, double*, hipStream_t);                                        \
+  template void launch_pcg_direction<T>(T*, const T*, const double*, const double*, const double*, int, int,    \
+                                        int, hipStream_t, const double*, double);                              \
   template void launch_dot_centered<T>(const T*, const T*, const double*, double, int, int, int, double*, double*, \
                                        hipStream_t);                                                           \
   template void launch_gauge_shift<T>(T*, int, int, int, T*, hipStream_t);                                   \
@@ -2565,8 +2510,7 @@ void launch_random(double* x, size_t n, uint64_t seed, hipStream_t s) {
   template void launch_scale_add_comp<T>(T*, const T*, T, const double*, int, int, int, hipStream_t);         \
   template void launch_mul_nodewise<T>(T*, const T*, int, int, int, int, hipStream_t);                        \
   template void launch_accumulate<T>(double*, const T*, size_t, hipStream_t, double);                                \
-  template void launch_diagonal<T>(const LevelView<T>&, int, int, T*, hipStream_t);                            \
-  template void launch_gs_update<T>(const int*, int, int, int, int, const T*, const T*, T*, T, hipStream_t);
+  template void launch_diagonal<T>(const LevelView<T>&, int, int, T*, hipStream_t);
 
 GMT_INST_T(float)
 GMT_INST_T(double)

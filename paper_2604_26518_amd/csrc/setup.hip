@@ -1,5 +1,5 @@
 // Hierarchy construction: compaction of flag fields, the tables of the staged
-// interior sweep, connected components.
+// interior sweep, connected components, Galerkin element matrices.
 #include <algorithm>
 #include <climits>
 #include <cstdlib>
@@ -126,16 +126,18 @@ __global__ __launch_bounds__(kBlock) void k_scan_write(const int* __restrict__ f
 // written out ascending at off[g] together with each node's 27 positions among
 // them (pass 1).
 //
-// The ids of one z-plane offset lie in a short interval (consecutive interior
+// The neighbours in one z-plane lie in a short interval of ids (consecutive interior
 // nodes have consecutive neighbours, and the x - 1, x, x + 1 neighbours are
-// consecutive ids), so the set is a bitmap over the three intervals: bits set by
-// LDS atomics, positions by popcount against a prefix over the words.  Groups
-// whose intervals need more than kStageBits bits (at 512^3 those that cross a
-// plane or wrap in y or z, ~3 %) are left to the sorting kernel below
-// (route[b] = 1).  Bound by the node-map lookups (9 per node) and the slot rows.
+// consecutive ids), so the set is a bitmap over the intervals of the group's planes:
+// bits set by LDS atomics, positions by popcount against a prefix over the words.
+// Groups whose intervals need more than kStageBits bits (at 512^3 those that wrap
+// in y) are left to the sorting kernel below (route[b] = 1).  Bound by the node-map lookups (9 per node) and the slot rows.
 // 512^3 gyroid, 32.3 M interior nodes: 2 x 29.5 ms with every group sorted,
-// 2 x 1.4 ms so (and 0.1 ms for the groups that are sorted).
+// 2 x 1.4 ms so (and 2 x 0.7 ms for the groups that are sorted).
 constexpr int kStageBits = 1 << 17;
+// planes told apart: those before, of and after the group's first node's plane and on;
+// the last one takes all further planes (small cells)
+constexpr int kStagePlanes = 6;
 
 template <int NB>
 __global__ __launch_bounds__(NB) void k_stage_tables(const int* __restrict__ interior, int n_int,
@@ -148,8 +150,9 @@ __global__ __launch_bounds__(NB) void k_stage_tables(const int* __restrict__ int
   __shared__ unsigned bits[kWords];
   __shared__ uint16_t pre[kWords];
   __shared__ int list[8 * NB];  // pass 1: a staged group has at most 8 NB distinct ids
-  __shared__ int lo3[3], hi3[3], bias3[3];
-  __shared__ int wstart[3], wbias[3], n_words;
+  constexpr int PL = kStagePlanes;
+  __shared__ int lo3[PL], hi3[PL], bias3[PL];
+  __shared__ int wstart[PL], wbias[PL], n_words, z_first;
   __shared__ int wsum[NB / 64];
   const int tid = threadIdx.x;
   const int b = pass == 0 ? (int)blockIdx.x : blk[blockIdx.x];
@@ -157,7 +160,9 @@ __global__ __launch_bounds__(NB) void k_stage_tables(const int* __restrict__ int
   const bool valid = t < n_int;
   int ctr[9], edge[9];
   bool left = false, right = false;  // x - 1 / x + 1 is the id next to ctr (no wrap)
-  if (tid < 3) lo3[tid] = INT_MAX, hi3[tid] = -1;
+  int plane = 0;                     // of z - 1; z and z + 1 follow
+  if (tid < PL) lo3[tid] = INT_MAX, hi3[tid] = -1;
+  if (tid == 0) z_first = node_lin[interior[t]] / (N * N);
   __syncthreads();
   int mn[3] = {INT_MAX, INT_MAX, INT_MAX}, mx[3] = {-1, -1, -1};
   if (valid) {
@@ -165,6 +170,7 @@ __global__ __launch_bounds__(NB) void k_stage_tables(const int* __restrict__ int
     const int x = lin % N, y = (lin / N) % N, z = lin / (N * N);
     left = x > 0;
     right = x < N - 1;
+    plane = z - z_first;
 #pragma unroll
     for (int r = 0; r < 9; ++r) {
       const int row = N * (wrapm(y + r % 3 - 1, N) + N * wrapm(z + r / 3 - 1, N));
@@ -174,28 +180,41 @@ __global__ __launch_bounds__(NB) void k_stage_tables(const int* __restrict__ int
       mx[r / 3] = max(mx[r / 3], max(right ? ctr[r] + 1 : ctr[r], edge[r]));
     }
   }
+  const int p0 = __shfl(plane, 0, 64);
+  if (__all(!valid || plane == p0)) {  // one plane's nodes in the wave: one update per interval
 #pragma unroll
-  for (int k = 0; k < 3; ++k) {
+    for (int k = 0; k < 3; ++k) {
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-      mn[k] = min(mn[k], __shfl_xor(mn[k], o, 64));
-      mx[k] = max(mx[k], __shfl_xor(mx[k], o, 64));
+      for (int o = 32; o > 0; o >>= 1) {
+        mn[k] = min(mn[k], __shfl_xor(mn[k], o, 64));
+        mx[k] = max(mx[k], __shfl_xor(mx[k], o, 64));
+      }
+      if ((tid & 63) == 0) {
+        atomicMin(&lo3[min(p0 + k, PL - 1)], mn[k]);
+        atomicMax(&hi3[min(p0 + k, PL - 1)], mx[k]);
+      }
     }
-    if ((tid & 63) == 0) {
-      atomicMin(&lo3[k], mn[k]);
-      atomicMax(&hi3[k], mx[k]);
+  } else if (valid) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      atomicMin(&lo3[min(plane + k, PL - 1)], mn[k]);
+      atomicMax(&hi3[min(plane + k, PL - 1)], mx[k]);
     }
   }
   __syncthreads();
   if (tid == 0) {
-    // intervals in ascending order; overlapping ones share their bits
-    int o[3] = {0, 1, 2};
-    if (lo3[o[1]] < lo3[o[0]]) { const int q = o[0]; o[0] = o[1]; o[1] = q; }
-    if (lo3[o[2]] < lo3[o[1]]) { const int q = o[1]; o[1] = o[2]; o[2] = q; }
-    if (lo3[o[1]] < lo3[o[0]]) { const int q = o[0]; o[0] = o[1]; o[1] = q; }
+    // intervals in ascending order (empty ones, lo = INT_MAX, last); overlapping ones
+    // share their bits
+    int o[PL];
+    for (int k = 0; k < PL; ++k) {
+      int at = k;
+      for (; at > 0 && lo3[o[at - 1]] > lo3[k]; --at) o[at] = o[at - 1];
+      o[at] = k;
+    }
     int words = 0, nw = 0, end = -1;
-    for (int k = 0; k < 3; ++k) {
+    for (int k = 0; k < PL; ++k) {
       const int w = o[k];
+      if (hi3[w] < 0) break;
       if (nw > 0 && lo3[w] <= end) {
         end = max(end, hi3[w]);
       } else {
@@ -208,7 +227,7 @@ __global__ __launch_bounds__(NB) void k_stage_tables(const int* __restrict__ int
       bias3[w] = wbias[nw - 1];
     }
     words = wstart[nw - 1] + (end - (wbias[nw - 1] + 32 * wstart[nw - 1])) / 32 + 1;
-    for (int k = nw; k < 3; ++k) wstart[k] = INT_MAX;
+    for (int k = nw; k < PL; ++k) wstart[k] = INT_MAX;
     n_words = words;
   }
   __syncthreads();
@@ -222,12 +241,12 @@ __global__ __launch_bounds__(NB) void k_stage_tables(const int* __restrict__ int
   if (valid) {
 #pragma unroll
     for (int r = 0; r < 9; ++r) {
-      const int base = ctr[r] - bias3[r / 3] - (left ? 1 : 0);
+      const int base = ctr[r] - bias3[min(plane + r / 3, PL - 1)] - (left ? 1 : 0);
       const unsigned long long m = (unsigned long long)(left ? (right ? 7u : 3u) : (right ? 3u : 1u)) << (base & 31);
       atomicOr(&bits[base >> 5], (unsigned)m);
       if (m >> 32) atomicOr(&bits[(base >> 5) + 1], (unsigned)(m >> 32));
       if (!left || !right) {
-        const int p = edge[r] - bias3[r / 3];
+        const int p = edge[r] - bias3[min(plane + r / 3, PL - 1)];
         atomicOr(&bits[p >> 5], 1u << (p & 31));
       }
     }
@@ -244,7 +263,8 @@ __global__ __launch_bounds__(NB) void k_stage_tables(const int* __restrict__ int
   }
   for (int w = w0; w < w1; ++w) {
     pre[w] = (uint16_t)pos;
-    const int bias = w >= wstart[2] ? wbias[2] : (w >= wstart[1] ? wbias[1] : wbias[0]);
+    int bias = wbias[0];
+    for (int k = 1; k < PL && w >= wstart[k]; ++k) bias = wbias[k];
     for (unsigned v = bits[w]; v; v &= v - 1) list[pos++] = 32 * w + __ffs((int)v) - 1 + bias;
   }
   __syncthreads();
@@ -258,8 +278,8 @@ __global__ __launch_bounds__(NB) void k_stage_tables(const int* __restrict__ int
   uint16_t row[kSlotStride];
 #pragma unroll
   for (int r = 0; r < 9; ++r) {
-    const unsigned k = rank(ctr[r], bias3[r / 3]);
-    const unsigned e = left && right ? 0 : rank(edge[r], bias3[r / 3]);
+    const unsigned k = rank(ctr[r], bias3[min(plane + r / 3, PL - 1)]);
+    const unsigned e = left && right ? 0 : rank(edge[r], bias3[min(plane + r / 3, PL - 1)]);
     row[3 * r] = (uint16_t)(left ? k - 1 : e);
     row[3 * r + 1] = (uint16_t)k;
     row[3 * r + 2] = (uint16_t)(right ? k + 1 : e);
@@ -465,6 +485,139 @@ __global__ void k_cc_count(const int* __restrict__ parent, int n_e, int* __restr
   if ((threadIdx.x & 63) == 0 && m) atomicAdd(count, __popcll(m));
 }
 
+// ---------------------------------------------------------------- Galerkin operators
+// Local Galerkin projection (Sec. 4.6): K_E = sum_{active children c} P_c^T K_c P_c,
+// P_c = Ps_c (8x8 trilinear weights) (x) I_D.  One block per coarse element.  Bound by
+// the two 8-term products of every entry (LDS), 8 times per element.
+template <int D>
+__global__ __launch_bounds__(kBlock) void k_galerkin(const int* __restrict__ elem_lin_c, int Nc,
+                                                     const int* __restrict__ emap_f,
+                                                     const double* __restrict__ Ksrc,
+                                                     const double* __restrict__ Ps, double* __restrict__ out64,
+                                                     float* __restrict__ out32) {
+  constexpr int M = 8 * D;
+  __shared__ double Kc[M * M];
+  __shared__ double T1[M * M];
+  __shared__ double acc[M * M];
+  __shared__ double P[64];
+  const int e = blockIdx.x;
+  const int Nf = 2 * Nc;
+  const int lin = elem_lin_c[e];
+  const int X = lin % Nc, Y = (lin / Nc) % Nc, Z = lin / (Nc * Nc);
+  for (int t = threadIdx.x; t < M * M; t += kBlock) acc[t] = 0.0;
+  for (int c = 0; c < 8; ++c) {
+    const int fx = 2 * X + (c & 1), fy = 2 * Y + ((c >> 1) & 1), fz = 2 * Z + ((c >> 2) & 1);
+    const int fid = emap_f[fx + Nf * (fy + Nf * fz)];
+    if (fid < 0) continue;  // uniform across the block
+    const double* src = Ksrc + (size_t)fid * M * M;
+    __syncthreads();
+    for (int t = threadIdx.x; t < M * M; t += kBlock) Kc[t] = src[t];
+    if (threadIdx.x < 64) P[threadIdx.x] = Ps[c * 64 + threadIdx.x];
+    __syncthreads();
+    // T1[(m,i),(p,j)] = sum_n Kc[(m,i),(n,j)] P[n][p]
+    for (int t = threadIdx.x; t < M * M; t += kBlock) {
+      const int row = t / M, col = t % M;
+      const int p = col / D, j = col % D;
+      double s = 0.0;
+#pragma unroll
+      for (int n = 0; n < 8; ++n) s += Kc[row * M + n * D + j] * P[n * 8 + p];
+      T1[t] = s;
+    }
+    __syncthreads();
+    // acc[(o,i),(p,j)] += sum_m P[m][o] T1[(m,i),(p,j)]
+    for (int t = threadIdx.x; t < M * M; t += kBlock) {
+      const int row = t / M, col = t % M;
+      const int o = row / D, i = row % D;
+      double s = 0.0;
+#pragma unroll
+      for (int m = 0; m < 8; ++m) s += P[m * 8 + o] * T1[(m * D + i) * M + col];
+      acc[t] += s;
+    }
+  }
+  __syncthreads();
+  for (int t = threadIdx.x; t < M * M; t += kBlock) {
+    out64[(size_t)e * M * M + t] = acc[t];
+    out32[(size_t)e * M * M + t] = (float)acc[t];
+  }
+}
+
+// Where the children's matrices come from a table of nm (the 256 mask matrices of level 2;
+// the voxel's K_e, nm = 1), every term P_c^T K P_c is one of 8 nm: they are formed once
+// (k_galerkin_terms, the arithmetic of k_galerkin) and an element is the sum of its
+// children's terms, in the same order, each times the child's stiffness scale in a
+// density hierarchy.  Bound by reading the terms (37 KB an element, from L2) and writing
+// the matrices.  Level 3 of a 512^3 cell (581 k elements): 11.5 ms element by element,
+// 2.4 ms so.
+template <int D>
+__global__ __launch_bounds__(kBlock) void k_galerkin_terms(int nm, const double* __restrict__ Ksrc,
+                                                           const double* __restrict__ Ps, double* __restrict__ terms) {
+  constexpr int M = 8 * D;
+  __shared__ double Kc[M * M];
+  __shared__ double T1[M * M];
+  __shared__ double P[64];
+  const int m = blockIdx.x, c = blockIdx.y;
+  for (int t = threadIdx.x; t < M * M; t += kBlock) Kc[t] = Ksrc[(size_t)m * M * M + t];
+  if (threadIdx.x < 64) P[threadIdx.x] = Ps[c * 64 + threadIdx.x];
+  __syncthreads();
+  for (int t = threadIdx.x; t < M * M; t += kBlock) {
+    const int row = t / M, col = t % M;
+    const int p = col / D, j = col % D;
+    double s = 0.0;
+#pragma unroll
+    for (int n = 0; n < 8; ++n) s += Kc[row * M + n * D + j] * P[n * 8 + p];
+    T1[t] = s;
+  }
+  __syncthreads();
+  for (int t = threadIdx.x; t < M * M; t += kBlock) {
+    const int row = t / M, col = t % M;
+    const int o = row / D, i = row % D;
+    double s = 0.0;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) s += P[k * 8 + o] * T1[(k * D + i) * M + col];
+    terms[((size_t)c * nm + m) * M * M + t] = s;
+  }
+}
+
+template <int D>
+__global__ __launch_bounds__(D == 3 ? 288 : 256) void k_galerkin_sum(const int* __restrict__ elem_lin_c, int n_e, int Nc,
+                                                                     const int* __restrict__ emap_f,
+                                                                     const uint8_t* __restrict__ mask_f, int nm,
+                                                                     const double* __restrict__ terms,
+                                                                     const double* __restrict__ fscale,
+                                                                     double* __restrict__ out64,
+                                                                     float* __restrict__ out32) {
+  constexpr int M = 8 * D, H = M * M / 2;  // two entries per thread
+  constexpr int EPB = D == 3 ? 1 : 8;      // elements per workgroup
+  const int e = blockIdx.x * EPB + (int)threadIdx.x / H;
+  if (e >= n_e) return;
+  const int t = (int)threadIdx.x % H;
+  const int Nf = 2 * Nc;
+  const int lin = elem_lin_c[e];
+  const int X = lin % Nc, Y = (lin / Nc) % Nc, Z = lin / (Nc * Nc);
+  int fid[8], row[8];
+#pragma unroll
+  for (int c = 0; c < 8; ++c)
+    fid[c] = emap_f[2 * X + (c & 1) + Nf * (2 * Y + ((c >> 1) & 1) + Nf * (2 * Z + (c >> 2)))];
+#pragma unroll
+  for (int c = 0; c < 8; ++c) row[c] = c * nm + (nm > 1 && fid[c] >= 0 ? mask_f[fid[c]] : 0);
+  double a0 = 0.0, a1 = 0.0;
+#pragma unroll
+  for (int c = 0; c < 8; ++c) {
+    if (fid[c] < 0) continue;
+    const double2 v = reinterpret_cast<const double2*>(terms + (size_t)row[c] * M * M)[t];
+    if (fscale) {
+      const double sc = fscale[fid[c]];
+      a0 = fma(sc, v.x, a0);
+      a1 = fma(sc, v.y, a1);
+    } else {
+      a0 += v.x;
+      a1 += v.y;
+    }
+  }
+  reinterpret_cast<double2*>(out64 + (size_t)e * M * M)[t] = make_double2(a0, a1);
+  reinterpret_cast<float2*>(out32 + (size_t)e * M * M)[t] = make_float2((float)a0, (float)a1);
+}
+
 inline unsigned blocks_for(size_t n) { return (unsigned)((n + kBlock - 1) / kBlock); }
 
 }  // namespace
@@ -509,6 +662,32 @@ void launch_stage_tables(const int* interior, int n_int, const int* node_lin, co
     hipLaunchKernelGGL(k_stage_sort<256>, dim3(grid), dim3(256), 0, s, interior, n_int, node_lin, node_map, N, pass,
                        blk, cnt, off, ids, slot, route);
   }
+  GMT_LAUNCH_CHECK();
+}
+
+size_t galerkin_term_doubles(int src_kind, int D) {
+  return src_kind == KIND_PERELEM ? 0 : (size_t)8 * (src_kind == KIND_TABLE ? 256 : 1) * 64 * D * D;
+}
+
+void launch_galerkin(const int* elem_lin_c, int n_e_c, int Nc, const int* emap_f, const uint8_t* cmask_f,
+                     const double* Ksrc, int src_kind, int D, const double* Ps, const double* fscale, double* terms,
+                     double* out64, float* out32, hipStream_t s) {
+  if (!n_e_c) return;
+#define GMT_GALERKIN(DD)                                                                                             \
+  if (D == DD) {                                                                                                     \
+    if (src_kind == KIND_PERELEM) {                                                                                  \
+      hipLaunchKernelGGL(k_galerkin<DD>, dim3(n_e_c), dim3(kBlock), 0, s, elem_lin_c, Nc, emap_f, Ksrc, Ps, out64,    \
+                         out32);                                                                                     \
+    } else {                                                                                                         \
+      const int nm = src_kind == KIND_TABLE ? 256 : 1, epb = DD == 3 ? 1 : 8;                                        \
+      hipLaunchKernelGGL(k_galerkin_terms<DD>, dim3(nm, 8), dim3(kBlock), 0, s, nm, Ksrc, Ps, terms);                 \
+      hipLaunchKernelGGL(k_galerkin_sum<DD>, dim3((unsigned)((n_e_c + epb - 1) / epb)), dim3(DD == 3 ? 288 : 256), 0, \
+                         s, elem_lin_c, n_e_c, Nc, emap_f, cmask_f, nm, terms, fscale, out64, out32);                \
+    }                                                                                                                \
+  }
+  GMT_GALERKIN(3)
+  GMT_GALERKIN(1)
+#undef GMT_GALERKIN
   GMT_LAUNCH_CHECK();
 }
 

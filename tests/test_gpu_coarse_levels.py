@@ -1,0 +1,135 @@
+"""GPU parity of the solver's coarse-level kernels: the assembled-stencil sweeps in every split of the
+cases (remainders of the 64-node workgroups, lists of one colour, density hierarchies in FP64), and the
+transfers on either side of the node count that splits the cases over threads."""
+
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from gmt_inputs import gyroid_sheet, laminate, random_vectors, spinodal, uniform  # noqa: E402
+from oracle import operators as oops  # noqa: E402
+from oracle import simp as osimp  # noqa: E402
+from oracle import solve as osolve  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda"
+
+
+def _gmt():
+    from paper_2604_26518_amd import binding
+    return binding
+
+
+def _t(a, dt=torch.float64):
+    return torch.as_tensor(np.ascontiguousarray(a), dtype=dt, device=DEV)
+
+
+def _np(t):
+    return t.cpu().numpy().astype(np.float64)
+
+
+# a row is a sum of 81 products of coefficients, each a sum of at most 8 element-matrix
+# entries rounded once, plus the epilogue's few operations: n = 100 covers them
+def _gamma(dt, n=100):
+    u = 2.0 ** -24 if dt == torch.float32 else 2.0 ** -53
+    return n * u / (1 - n * u)
+
+
+CELLS = {
+    "uniform8_L3": (lambda: uniform(8), 3, "elastic"),  # level 2: 64 nodes, one full workgroup
+    "gyroid24_L3": (lambda: gyroid_sheet(24, 3, 0.4), 3, "elastic"),
+    "spinodal32_L4": (lambda: spinodal(32, 5, 0.4), 4, "elastic"),
+    "laminate24_th": (lambda: laminate(24, 9, axis=1), 3, "thermal"),
+    "gyroid40_th": (lambda: gyroid_sheet(40, 2, 0.3), 4, "thermal"),
+}
+
+
+@pytest.mark.parametrize("variant", [4, 5, 6])
+@pytest.mark.parametrize("cell", sorted(CELLS) + ["density16", "density16_th"])
+def test_stencil_sweeps(cell, variant, monkeypatch):
+    """K.u and f - K.u within the forward-error bound, the smoothers against the oracle's."""
+    B = _gmt()
+    if cell.startswith("density"):
+        phys = "thermal" if cell.endswith("th") else "elastic"
+        rng = np.random.default_rng(4)
+        rho = np.clip(0.5 + 0.4 * gyroid_sheet(16, 1, 0.5) + 0.1 * rng.standard_normal((16, 16, 16)), 0.0, 1.0)
+        P = osimp.DensityProblem(rho, 3, physics=phys, prune=1e-5)
+        H = B.Hierarchy(None, 3, phys, density=rho, prune=1e-5)
+        dtypes = (torch.float32, torch.float64)
+    else:
+        make, L, phys = CELLS[cell]
+        P, H = osolve.Problem(make(), L, phys), B.Hierarchy(make(), L, phys)
+        dtypes = (torch.float32,)  # the solver's FP64 sweeps of binary cells keep the element matrices
+    if variant == 6 and phys == "thermal":
+        pytest.skip("two cases per thread: elastic cells only")
+    f1 = H.apply_K(_t(random_vectors(P.levels[0].n_n, P.c * P.d, 5).reshape(-1, P.c, P.d)))
+    for dt in dtypes:  # a solve (of a load that is not zero on the full cell either) lays the stencils out
+        H.solve(f1, precision="f32" if dt == torch.float32 else "f64", tol=1e-3)
+    for l in range(2, P.L):
+        n = P.levels[l - 1].n_n
+        mats = P.mats[l - 1]
+        u0 = random_vectors(n, P.c * P.d, 11 + l).reshape(n, P.c, P.d)
+        f0 = random_vectors(n, P.c * P.d, 21 + l).reshape(n, P.c, P.d)
+        ref = oops.apply_K(P.levels[l - 1], mats, u0)
+        mag = oops.apply_K(P.levels[l - 1], np.abs(mats), np.abs(u0))
+        lam = H.level_info(l)["lambda_max"]
+        for dt in dtypes:
+            monkeypatch.delenv("GMT_FORCE_COARSE_VARIANT", raising=False)
+            elem = H.apply_K(_t(u0, dt), l)
+            monkeypatch.setenv("GMT_FORCE_COARSE_VARIANT", str(variant))
+            got = H.apply_K(_t(u0, dt), l)
+            y = _np(got)
+            r = _np(H.residual(_t(f0, dt), _t(u0, dt), l))
+            worst = max(np.max(np.abs(y - ref) / (_gamma(dt) * mag + 1e-300)),
+                        np.max(np.abs(r - (f0 - ref)) / (_gamma(dt) * (mag + np.abs(f0)))))
+            print(f"[{cell}] level {l} ({n} nodes) variant {variant} {dt}: |err| / bound {worst:.3f}", flush=True)
+            assert worst <= 1.0
+            assert n < 64 or not torch.equal(got, elem)  # another order of summation: the stencils ran
+            # a smoother is a few sweeps: 2 Chebyshev or Jacobi steps and one of 8 colours of
+            # Gauss-Seidel amplify a row's relative error by no more than 100
+            tol = 100 * _gamma(dt)
+            lo, hi = lam / 30, 1.1 * lam
+            for name, p1, p2, want in (
+                    ("chebyshev", lo, hi, osolve.chebyshev(P, l - 1, u0, f0, 2, lo, hi)),
+                    ("jacobi", 0.4, 0.0, osolve.jacobi(P, l - 1, u0, f0, 2, 0.4)),
+                    ("gs", 1.0, 0.0, osolve.gauss_seidel(P, l - 1, u0, f0, 2, 1.0))):
+                out = _np(H.smooth(_t(f0, dt), _t(u0, dt), 2, name, p1, p2, level=l))
+                assert np.abs(out - want).max() <= tol * np.abs(want).max(), (l, name, dt)
+    H.close()
+
+
+@pytest.mark.parametrize("N,L,phys", [(96, 5, "elastic"), (96, 4, "thermal"), (88, 4, "thermal"), (80, 5, "elastic")])
+def test_transfers_around_the_split(N, L, phys):
+    """Restriction and prolongation against the maps' weights: levels of 884736 .. 1000 nodes, on both
+    sides of the node count (of the level written) below which each thread takes one case."""
+    H = _gmt().Hierarchy(uniform(N), L, phys)
+    for l in range(1, L):
+        m = H.export_maps(l)
+        idx, w = m["prol_idx"].long(), m["prol_w"].double()
+        ok = idx >= 0
+        w = torch.where(ok, w, torch.zeros_like(w))
+        idx = torch.where(ok, idx, torch.zeros_like(idx))
+        n, nc = H.n_n(l), H.n_n(l + 1)
+        g = torch.Generator(device=DEV).manual_seed(l)
+        uc = torch.randn((nc, H.c, H.d), generator=g, device=DEV, dtype=torch.float64)
+        uf = torch.randn((n, H.c, H.d), generator=g, device=DEV, dtype=torch.float64)
+        up, up_abs = uf.clone(), uf.abs()
+        down, down_abs = torch.zeros_like(uc), torch.zeros_like(uc)
+        for k in range(idx.shape[1]):
+            wk = w[:, k, None, None]
+            up += wk * uc[idx[:, k]]
+            up_abs += wk * uc[idx[:, k]].abs()
+            down.index_add_(0, idx[:, k], wk * uf)
+            down_abs.index_add_(0, idx[:, k], wk * uf.abs())
+        # at most 27 products and as many additions on either side (of the oracle's sums too)
+        for dt in (torch.float64, torch.float32):
+            fc = H.restrict(uf.to(dt), l).double()
+            u1 = H.prolong_add(uc.to(dt), uf.to(dt, copy=True), l).double()
+            bound = _gamma(dt, 64)
+            e = (float(((fc - down).abs() / (bound * down_abs + 1e-300)).max()),
+                 float(((u1 - up).abs() / (bound * up_abs + 1e-300)).max()))
+            print(f"[transfers {N} {phys}] level {l} ({n} -> {nc}) {dt}: |err| / bound {e[0]:.3f} {e[1]:.3f}", flush=True)
+            assert max(e) <= 1.0
+    H.close()
