@@ -14,7 +14,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libgmt.so")
-SOURCES = ["kernels.hip", "host.hip", "nn.hip", "attention.hip", "coarse.hip",
+SOURCES = ["kernels.hip", "host.hip", "nn.hip", "attention.hip", "coarse.hip", "krylov.hip",
            "setup.hip", "layout.hip", "stencil.hip", "simp.hip"]
 
 FLAGS = [

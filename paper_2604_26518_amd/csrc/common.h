@@ -232,6 +232,13 @@ void launch_dot_colsum(const T* a, const T* b, int n, int C, int D, double* part
 template <typename T>
 void launch_dot2_centered(const T* r, const T* z, const double* sums, double inv_n, int n, int C, int D,
                           double* partial, double* rz, double* rr, double* flags, hipStream_t s);
+// The same two of an FP32 iteration (krylov.hip; the templates above serve FP64): per-case partial sums of case_sums_partials(C)
+// doubles; launch_sums_rz forms the sums of z itself.
+size_t case_sums_partials(int C);
+void launch_sums_pq(const float* p, const float* q, int n, int C, int D, double* partial, double* pq, double* sums,
+                    hipStream_t s, const double* cur, double* prev);
+void launch_sums_rz(const float* r, const float* z, double inv_n, int n, int C, int D, double* partial, double* rz,
+                    double* rr, double* sums, double* flags, hipStream_t s);
 // p = z + beta p, beta = rz_new / rz (0 without rz_new); with sums, z with its column
 // means sums / n removed on the fly
 template <typename T>

@@ -569,7 +569,9 @@ static LevelView<T> colour_view(const Hier& h, int l, int c) {
     v.bnd_nbrs = d.col_bnd_nbrs ? d.col_bnd_nbrs + (size_t)d.col_bnd_off[c] * kBndStride : nullptr;
     v.n_runs = 0;
     v.runs = nullptr;
-    if (v.cb < 5 || v.cb > 8) v.cb = 7;  // the list-driven variants
+    // the lists in one launch (the same sums as the other variants; cycle on a 160^3
+    // gyroid: 2.7 ms in variant 7, 3.3 ms as two launches a colour of variant 6)
+    if (!h.density) v.cb = 7;
   } else {
     v.list = d.col_nodes + d.col_off[c];
     v.n_list = d.col_off[c + 1] - d.col_off[c];
@@ -798,15 +800,21 @@ static std::map<std::vector<int>, Shape> g_tune;
 // to warm up.
 template <typename T>
 static float time_shape(Hier& h, int l, const T* x, T* y, hipEvent_t e0, hipEvent_t e1, hipStream_t s) {
-  for (int r = 0; r < 5; ++r) {
-    if (r == 2) GMT_HIP(hipEventRecord(e0, s));
-    apply<T>(h, l, EPI_KU, x, nullptr, y, h.C, s);
+  // coarse levels: the better of two rounds, their launches last a few us and one that
+  // is held up would decide
+  float best = INFINITY;
+  for (int round = 0; round < (l > 0 ? 2 : 1); ++round) {
+    for (int r = round ? 2 : 0; r < 5; ++r) {
+      if (r == 2) GMT_HIP(hipEventRecord(e0, s));
+      apply<T>(h, l, EPI_KU, x, nullptr, y, h.C, s);
+    }
+    GMT_HIP(hipEventRecord(e1, s));
+    GMT_HIP(hipEventSynchronize(e1));
+    float ms = 0;
+    GMT_HIP(hipEventElapsedTime(&ms, e0, e1));
+    best = std::min(best, ms / 3);
   }
-  GMT_HIP(hipEventRecord(e1, s));
-  GMT_HIP(hipEventSynchronize(e1));
-  float ms = 0;
-  GMT_HIP(hipEventElapsedTime(&ms, e0, e1));
-  return ms / 3;
+  return best;
 }
 
 static std::vector<int> tune_key(const Hier& h, const LevelData& d, bool f32) {
@@ -1105,6 +1113,21 @@ static int pcg(Hier& h, const T* b, T* x, const double* tol, int maxit, int chec
       vcycle<T>(h, W.pr, W.pz, true, nullptr, cfg, st, 0, &z, primed);
     }
   };
+  // the sums of an iteration: p.q with those of q; r.z, r.r and those of z
+  auto sums_pq = [&](hipStream_t st) {
+    if constexpr (std::is_same<T, float>::value)
+      launch_sums_pq(W.pp, W.pq, n, C, D, h.red_partial, pq, sums_q, st, rzn, rz);
+    else
+      launch_dot_colsum<T>(W.pp, W.pq, n, C, D, h.red_partial, pq, sums_q, st, rzn, rz);
+  };
+  auto sums_rz = [&](hipStream_t st, double* rr_out, double* fl) {
+    if constexpr (std::is_same<T, float>::value) {
+      launch_sums_rz(W.pr, z, inv_n, n, C, D, h.red_partial, rzn, rr_out, sums_z, fl, st);
+    } else {
+      launch_colsum<T>(z, n, Q, D, h.red_partial, sums_z, st);
+      launch_dot2_centered<T>(W.pr, z, sums_z, inv_n, n, C, D, h.red_partial, rzn, rr_out, fl, st);
+    }
+  };
   vc(s, false);
   launch_colsum<T>(z, n, Q, D, h.red_partial, sums_z, s);
   launch_dot_centered<T>(W.pr, z, sums_z, inv_n, n, C, D, h.red_partial, rzn, s);
@@ -1155,11 +1178,10 @@ static int pcg(Hier& h, const T* b, T* x, const double* tol, int maxit, int chec
     // share one pass over r.
     auto step = [&](hipStream_t st) {
       apply<T>(h, 0, EPI_KU, W.pp, nullptr, W.pq, C, st);
-      launch_dot_colsum<T>(W.pp, W.pq, n, C, D, h.red_partial, pq, sums_q, st, rzn, rz);
+      sums_pq(st);
       launch_pcg_update<T>(x, W.pr, W.pp, W.pq, rz, pq, fl, n, Q, D, st, sums_q, inv_n, p_dinv, p_scale, p_z);
       vc(st, prime);
-      launch_colsum<T>(z, n, Q, D, h.red_partial, sums_z, st);
-      launch_dot2_centered<T>(W.pr, z, sums_z, inv_n, n, C, D, h.red_partial, rzn, rr, fl, st);
+      sums_rz(st, rr, fl);
       launch_pcg_direction<T>(W.pp, z, rzn, rz, fl, n, Q, D, st, sums_z, inv_n);
     };
     Hier::PcgGraphs& G = MIXED ? h.gmx : graphs_of<T>(h);
@@ -1258,7 +1280,7 @@ static int pcg(Hier& h, const T* b, T* x, const double* tol, int maxit, int chec
   while (it < maxit) {
     ++it;
     apply<T>(h, 0, EPI_KU, W.pp, nullptr, W.pq, C, s);
-    launch_dot_colsum<T>(W.pp, W.pq, n, C, D, h.red_partial, pq, sums_q, s, rzn, rz);
+    sums_pq(s);
     launch_pcg_update<T>(x, W.pr, W.pp, W.pq, rz, pq, nullptr, n, Q, D, s, sums_q, inv_n, p_dinv, p_scale, p_z);
     if (it % check_every == 0 || it == maxit) {
       launch_dot<T>(W.pr, W.pr, n, C, D, h.red_partial, rr, s);
@@ -1275,8 +1297,12 @@ static int pcg(Hier& h, const T* b, T* x, const double* tol, int maxit, int chec
       }
     }
     vc(s, prime);
-    launch_colsum<T>(z, n, Q, D, h.red_partial, sums_z, s);
-    launch_dot_centered<T>(W.pr, z, sums_z, inv_n, n, C, D, h.red_partial, rzn, s);
+    if constexpr (std::is_same<T, float>::value) {
+      sums_rz(s, rr, nullptr);
+    } else {
+      launch_colsum<T>(z, n, Q, D, h.red_partial, sums_z, s);
+      launch_dot_centered<T>(W.pr, z, sums_z, inv_n, n, C, D, h.red_partial, rzn, s);
+    }
     launch_pcg_direction<T>(W.pp, z, rzn, rz, nullptr, n, Q, D, s, sums_z, inv_n);
   }
   return it;
@@ -1364,7 +1390,7 @@ static void build(Hier& h, const uint8_t* vox, hipStream_t s, const double* rho 
   local_prolongation(Ps);
   h.Ps = h.alloc<double>(512);
   GMT_HIP(hipMemcpyAsync(h.Ps, Ps, 512 * sizeof(double), hipMemcpyHostToDevice, s));
-  h.red_partial = h.alloc<double>((size_t)kRedBlocks * 64);
+  h.red_partial = h.alloc<double>(std::max((size_t)kRedBlocks * 64, case_sums_partials(h.C)));
   h.red_out = h.alloc<double>(256);
   h.gauge_tmp64 = h.alloc<double>(32);
   h.gauge_tmp32 = h.alloc<float>(32);

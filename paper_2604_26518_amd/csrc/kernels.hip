@@ -15,6 +15,7 @@
 #include <algorithm>
 #include <climits>
 #include <cmath>
+#include <cstdlib>
 #include <type_traits>
 
 #include "common.h"
@@ -198,9 +199,9 @@ __device__ __forceinline__ void neighbour_ids(const int* __restrict__ map, int N
 // 27-point stencil S of the shared K_e, wave-uniform coefficients.
 // PRE: all 27 x D values of a case are loaded before the first FMA, which
 // keeps 27 gathers per wave in flight at the cost of registers (occupancy).
-template <typename T, int D, int EPI, int PRE = 0>
-__global__ __launch_bounds__(kBlock) void k_apply_interior(LevelView<T> L, int C, const T* __restrict__ u, EpiArgs<T> e) {
-  const int t = block_index(L.xcd) * kBlock + threadIdx.x;
+template <typename T, int D, int EPI, int PRE>
+__device__ __forceinline__ void interior_plain(const LevelView<T>& L, int c0, int c1, const T* __restrict__ u,
+                                               const EpiArgs<T>& e, int t) {
   if (t >= L.n_int) return;
   const int i = L.interior[t];
   const int N = L.N;
@@ -214,7 +215,7 @@ __global__ __launch_bounds__(kBlock) void k_apply_interior(LevelView<T> L, int C
   for (int q = 0; q < D; ++q) dv[q] = needs_dinv<EPI>() ? e.dinv[(size_t)i * D + q] : T(0);
   const StencilClasses<T, D> S(L.scls);
 #pragma unroll 1
-  for (int c = 0; c < C; ++c) {
+  for (int c = c0; c < c1; ++c) {
     T acc[D];
 #pragma unroll
     for (int q = 0; q < D; ++q) acc[q] = T(0);
@@ -242,6 +243,10 @@ __global__ __launch_bounds__(kBlock) void k_apply_interior(LevelView<T> L, int C
   }
 }
 
+template <typename T, int D, int EPI, int PRE = 0>
+__global__ __launch_bounds__(kBlock) void k_apply_interior(LevelView<T> L, int C, const T* __restrict__ u, EpiArgs<T> e) {
+  interior_plain<T, D, EPI, PRE>(L, 0, C, u, e, block_index(L.xcd) * kBlock + (int)threadIdx.x);
+}
 
 // Level 1, interior nodes, neighbourhoods staged in LDS.  Workgroup g takes
 // the NB interior nodes of group b = st_blk[g] and, per case, first copies the
@@ -658,12 +663,9 @@ __global__ __launch_bounds__(kBlock) void k_apply_boundary_st(LevelView<T> L, co
 // The grid is 1-D, rows workgroups per block of kBlock nodes, one per group
 // of C cases, adjacent in the launch order: the rows of a node block run
 // together and share its neighbour-id rows and occupancy in L2.
-template <typename T, int D, int C, int EPI, int PRE = 0>
-__global__ __launch_bounds__(kBlock) void k_apply_boundary_cls(LevelView<T> L, const T* __restrict__ u, EpiArgs<T> e,
-                                                               int rows) {
-  const int bi = block_index(L.xcd);
-  const int t = (bi / rows) * kBlock + threadIdx.x;
-  const int c0 = (bi % rows) * C;  // this workgroup's first case
+template <typename T, int D, int C, int EPI, int PRE>
+__device__ __forceinline__ void boundary_cls(const LevelView<T>& L, const T* __restrict__ u, const EpiArgs<T>& e, int t,
+                                             int c0) {
   if (t >= L.n_bnd) return;
   const int i = L.boundary[t];
   const size_t n = (size_t)L.n_n;
@@ -683,6 +685,12 @@ __global__ __launch_bounds__(kBlock) void k_apply_boundary_cls(LevelView<T> L, c
       nb[4 * k + 2] = v.z;
       nb[4 * k + 3] = v.w;
     }
+  }
+  unsigned active = 0;
+#pragma unroll
+  for (int j = 0; j < 27; ++j) {
+    active |= (nb[j] >= 0 ? 1u : 0u) << j;
+    nb[j] = nb[j] >= 0 ? nb[j] : 0;
   }
   T mk[8], mkn[8];
   if (L.oscale) {  // density hierarchy: the octant elements' stiffness scales (0 where inactive)
@@ -704,7 +712,7 @@ __global__ __launch_bounds__(kBlock) void k_apply_boundary_cls(LevelView<T> L, c
   if constexpr (PRE) {
 #pragma unroll
     for (int j = 0; j < 27; ++j) {
-      const size_t id = nb[j] >= 0 ? nb[j] : 0;
+      const size_t id = nb[j];
 #pragma unroll
       for (int c = 0; c < C; ++c)
 #pragma unroll
@@ -731,8 +739,8 @@ __global__ __launch_bounds__(kBlock) void k_apply_boundary_cls(LevelView<T> L, c
         for (int q2 = 0; q2 < D; ++q2)
           cj[q][q2] = fma(kcls_negative<D>(a, q, q2) ? mkn[k] : mk[k], kc[kcls_index<D>(a ^ m, q, q2)], cj[q][q2]);
     }
-    const bool act = nb[j] >= 0;
-    const size_t id = act ? nb[j] : 0;
+    const bool act = (active >> j) & 1u;
+    const size_t id = nb[j];
     T v[C][D];
 #pragma unroll
     for (int c = 0; c < C; ++c)
@@ -750,6 +758,62 @@ __global__ __launch_bounds__(kBlock) void k_apply_boundary_cls(LevelView<T> L, c
         for (int c = 0; c < C; ++c) acc[c][q] = fma(cj[q][q2], v[c][q2], acc[c][q]);
   }
   epilogue_node<T, EPI, C, D>(e, u, n, i, c0, &acc[0][0], nullptr, nullptr);
+}
+
+template <typename T, int D, int C, int EPI, int PRE = 0>
+__global__ __launch_bounds__(kBlock) void k_apply_boundary_cls(LevelView<T> L, const T* __restrict__ u, EpiArgs<T> e,
+                                                               int rows) {
+  const int bi = block_index(L.xcd);
+  boundary_cls<T, D, C, EPI, PRE>(L, u, e, (bi / rows) * kBlock + (int)threadIdx.x, (bi % rows) * C);
+}
+
+// What a workgroup of a sweep over ni interior and nb boundary workgroups does: kind 1,
+// boundary workgroup `index`; 0, interior; 2, nothing (padding).  Both kinds are spread
+// evenly over the launch, in the XCD order each over its contiguous shares.
+struct Share {
+  int kind;
+  unsigned index;
+};
+__device__ __forceinline__ Share level1_share(int xcd, unsigned nb, unsigned ni) {
+  unsigned k = blockIdx.x, cb = nb, ci = ni, fb = 0, fi = 0;
+  if (xcd) {
+    const unsigned x = k & 7u;
+    k >>= 3;
+    cb = nb / 8 + (x < nb % 8 ? 1u : 0u);
+    ci = ni / 8 + (x < ni % 8 ? 1u : 0u);
+    fb = x * (nb / 8) + min(x, nb % 8);
+    fi = x * (ni / 8) + min(x, ni % 8);
+  }
+  if (k >= cb + ci) return {2, 0};
+  const unsigned before = (unsigned)((unsigned long long)k * cb / (cb + ci));
+  const unsigned after = (unsigned)((unsigned long long)(k + 1) * cb / (cb + ci));
+  if (after > before) return {1, fb + before};
+  return {0, fi + k - before};
+}
+
+// Level 1, interior and boundary lists in one launch (small cells, one colour of a level,
+// thermal cells): bound by the latency of the gathers, which two launches after each
+// other pay twice, and by the launches themselves.  32^3 gyroid (9.8 k + 4.7 k nodes),
+// Chebyshev step: 12.1 + 5.6 us as two launches with the interior staged, 8.2 us so;
+// Gauss-Seidel cycle at 160^3: 55 + 23 us a colour as two launches, 69 us so.  On 128^3
+// and larger elastic cells the staged interior (variant 9) in a launch of its own stays
+// ahead (54.7 + 51.4 us); the autotuner times both.
+// The interior takes all cases of a node in a thread (ids and D^-1 read once), or one
+// (ic = 1) where that would make fewer workgroups than half the CUs: 32^3 solve 5.6 ms
+// with all, 5.0 - 5.5 with one; colours of 160^3 (150 k nodes): cycle 2.7 ms with all,
+// 3.0 with one.
+constexpr int kSplitInterior = 1 << 15;
+template <typename T, int D, int C, int EPI>
+__global__ __launch_bounds__(kBlock) void k_apply_lists(LevelView<T> L, const T* __restrict__ u, EpiArgs<T> e, int ic) {
+  const unsigned nb = (unsigned)((L.n_bnd + kBlock - 1) / kBlock) * C;
+  const unsigned rows = C / ic, ni = (unsigned)((L.n_int + kBlock - 1) / kBlock) * rows;
+  const Share w = level1_share(L.xcd, nb, ni);
+  if (w.kind == 1) {
+    boundary_cls<T, D, 1, EPI, 1>(L, u, e, (int)(w.index / C * kBlock + threadIdx.x), (int)(w.index % C));
+  } else if (w.kind == 0) {
+    const int c0 = (int)(w.index % rows) * ic;
+    interior_plain<T, D, EPI, 1>(L, c0, c0 + ic, u, e, (int)(w.index / rows * kBlock + threadIdx.x));
+  }
 }
 
 // Level 1, boundary nodes, all C cases per thread: the masked stencil block
@@ -1927,6 +1991,21 @@ static void launch_coarse(const LevelView<T>& L, int kind, int rows, const T* u,
   }
 }
 
+// workgroups of level1_share
+static unsigned share_grid(int xcd, unsigned nb, unsigned ni) {
+  return xcd ? 8 * ((nb + 7) / 8 + (ni + 7) / 8) : nb + ni;
+}
+
+// variant 7 with both kinds of nodes
+template <typename T, int D, int C, int EPI>
+static void launch_lists(const LevelView<T>& L, const T* u, const EpiArgs<T>& e, hipStream_t s) {
+  const char* env = std::getenv("GMT_SPLIT_INTERIOR");  // another line (tests of both forms on small cells)
+  const int ic = L.n_int < (env && *env ? std::atoi(env) : kSplitInterior) ? 1 : C;
+  hipLaunchKernelGGL((k_apply_lists<T, D, C, EPI>),
+                     dim3(share_grid(L.xcd, blocks_for(L.n_bnd) * C, blocks_for(L.n_int) * (C / ic))), dim3(kBlock), 0,
+                     s, L, u, e, ic);
+}
+
 // staged interior sweep (variant 9): the staged workgroups, then the plain
 // kernel (all 27 neighbours of a case loaded up front) over the rest
 template <typename T, int D, int EPI>
@@ -1950,7 +2029,9 @@ static void launch_interior_stage(const LevelView<T>& L, int C, const T* u, cons
 template <typename T, int D, int C, int EPI>
 static void apply_dispatch_kind(const LevelView<T>& L, int kind, const T* u, const EpiArgs<T>& e, hipStream_t s) {
   if (kind == KIND_SHARED) {
-    if (L.cb >= 5 && L.cb <= 9) {  // boundary as a register-assembled masked stencil
+    if (L.cb == 7 && L.n_int > 0 && L.n_bnd > 0) {
+      launch_lists<T, D, C, EPI>(L, u, e, s);
+    } else if (L.cb >= 5 && L.cb <= 9) {  // boundary as a register-assembled masked stencil
       if (L.n_int > 0) {
         if (L.cb == 9)
           launch_interior_stage<T, D, EPI>(L, C, u, e, s);
@@ -2495,10 +2576,6 @@ void launch_random(double* x, size_t n, uint64_t seed, hipStream_t s) {
   template void launch_normalize<T>(const T*, size_t, const double*, T*, hipStream_t);                     \
   template void launch_pcg_update<T>(T*, T*, const T*, const T*, const double*, const double*, const double*,   \
                                      int, int, int, hipStream_t, const double*, double, const T*, T, T*);      \
-  template void launch_dot_colsum<T>(const T*, const T*, int, int, int, double*, double*, double*, hipStream_t, \
-                                     const double*, double*);                                                  \
-  template void launch_dot2_centered<T>(const T*, const T*, const double*, double, int, int, int, double*, double*, \
-                                        double*, double*, hipStream_t);                                        \
   template void launch_pcg_direction<T>(T*, const T*, const double*, const double*, const double*, int, int,    \
                                         int, hipStream_t, const double*, double);                              \
   template void launch_dot_centered<T>(const T*, const T*, const double*, double, int, int, int, double*, double*, \
@@ -2520,5 +2597,10 @@ template void launch_gram<double, double>(const double*, const double*, int, int
                                           hipStream_t);
 template void launch_gram<float, double>(const float*, const double*, int, int, int, double*, double*,
                                          hipStream_t);
+
+template void launch_dot_colsum<double>(const double*, const double*, int, int, int, double*, double*, double*,
+                                        hipStream_t, const double*, double*);
+template void launch_dot2_centered<double>(const double*, const double*, const double*, double, int, int, int, double*,
+                                           double*, double*, double*, hipStream_t);
 
 }  // namespace gmt

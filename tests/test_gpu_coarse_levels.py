@@ -76,7 +76,7 @@ def test_stencil_sweeps(cell, variant, monkeypatch):
         mag = oops.apply_K(P.levels[l - 1], np.abs(mats), np.abs(u0))
         lam = H.level_info(l)["lambda_max"]
         for dt in dtypes:
-            monkeypatch.delenv("GMT_FORCE_COARSE_VARIANT", raising=False)
+            monkeypatch.setenv("GMT_FORCE_COARSE_VARIANT", "0")  # element-major
             elem = H.apply_K(_t(u0, dt), l)
             monkeypatch.setenv("GMT_FORCE_COARSE_VARIANT", str(variant))
             got = H.apply_K(_t(u0, dt), l)
@@ -97,6 +97,32 @@ def test_stencil_sweeps(cell, variant, monkeypatch):
                     ("gs", 1.0, 0.0, osolve.gauss_seidel(P, l - 1, u0, f0, 2, 1.0))):
                 out = _np(H.smooth(_t(f0, dt), _t(u0, dt), 2, name, p1, p2, level=l))
                 assert np.abs(out - want).max() <= tol * np.abs(want).max(), (l, name, dt)
+    H.close()
+
+
+@pytest.mark.parametrize("split", [0, 1 << 30])
+@pytest.mark.parametrize("cell", sorted(CELLS))
+def test_level1_lists(cell, split, monkeypatch):
+    """Level 1 with both node lists in one launch, all cases of an interior node in a thread (split 0)
+    or one: bit for bit the sweeps of two launches (variant 5), whose sums it forms, and within the
+    forward-error bound of the oracle; so are the Gauss-Seidel colours."""
+    make, L, phys = CELLS[cell]
+    P, H = osolve.Problem(make(), L, phys), _gmt().Hierarchy(make(), L, phys)
+    n = P.levels[0].n_n
+    u0 = random_vectors(n, P.c * P.d, 7).reshape(n, P.c, P.d)
+    ref = oops.apply_K(P.levels[0], P.mats[0], u0)
+    mag = oops.apply_K(P.levels[0], np.abs(P.mats[0]), np.abs(u0))
+    monkeypatch.setenv("GMT_SPLIT_INTERIOR", str(split))
+    for dt in (torch.float32, torch.float64):
+        monkeypatch.setenv("GMT_FORCE_L1_VARIANT", "5")
+        want = H.apply_K(_t(u0, dt), 1)
+        monkeypatch.setenv("GMT_FORCE_L1_VARIANT", "7")
+        got = H.apply_K(_t(u0, dt), 1)
+        assert torch.equal(got, want)
+        assert np.max(np.abs(_np(got) - ref) / (_gamma(dt) * mag + 1e-300)) <= 1.0
+        out = _np(H.smooth(_t(P.f, dt), _t(u0, dt), 2, "gs", 1.0, 0.0))
+        gs = osolve.gauss_seidel(P, 0, u0, P.f, 2, 1.0)
+        assert np.abs(out - gs).max() <= 100 * _gamma(dt) * np.abs(gs).max()
     H.close()
 
 
