@@ -50,7 +50,7 @@ COPY_BYTES = 512 << 20
 # kernel reports null until it is profiled again.
 SWEEP_TRAFFIC_BYTES = {
     # profiles/level1_chebyshev_sweep_gyroid512_hbm_traffic.txt
-    ("gyroid512_seed30001", 9, "64c7445f942b8902"): (22_693_601 + 5_186_849) * 1024,
+    ("gyroid512_seed30001", 9, "b53cd5b5f18eca48"): (22_693_662 + 5_187_202) * 1024,
 }
 SWEEP_KERNELS = {
     0: "k_apply_interior_nc + k_apply_boundary_st",
@@ -59,7 +59,7 @@ SWEEP_KERNELS = {
     3: "k_apply_interior_run + k_apply_boundary",
     5: "k_apply_interior + k_apply_boundary_cls",
     6: "k_apply_interior_nc + k_apply_boundary_cls",
-    7: "k_apply_interior<PRE=1> + k_apply_boundary_cls<PRE=1>",
+    7: "k_apply_lists",
     8: "k_apply_interior<PRE=1> + k_apply_boundary_all",
     9: "k_apply_interior_stage + k_apply_interior<PRE=1> (unstaged rest) + k_apply_boundary_cls<PRE=1>",
 }
