@@ -6,6 +6,7 @@
 #include <cstdint>
 #include <cstdio>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "gmt.h"
@@ -163,7 +164,14 @@ int count_components(const int* elem_lin, int n_e, const int* elem_map, int N, i
                      hipStream_t s);
 // Epilogue of a node-centric operator sweep.
 // EPI_CHEB0 is the first Chebyshev step (d = rho2 D^-1 r, the previous d is not read).
-enum Epi { EPI_KU = 0, EPI_RESID = 1, EPI_JACOBI = 2, EPI_CHEB = 3, EPI_CHEB0 = 4 };
+// EPI_GS is EPI_JACOBI in place (out is u) over one colour of a level: a node reads its own
+// value and those of its neighbours, which are of other colours, and nothing else of u (an
+// absent neighbour's load goes to the node itself), so no thread reads what another writes.
+enum Epi { EPI_KU = 0, EPI_RESID = 1, EPI_JACOBI = 2, EPI_CHEB = 3, EPI_CHEB0 = 4, EPI_GS = 5 };
+
+// the sweeps' input vector: not written in the sweep, except by EPI_GS
+template <typename T, int EPI>
+using sweep_input = std::conditional_t<EPI == EPI_GS, const T*, const T* __restrict__>;
 
 template <typename T>
 struct EpiArgs {

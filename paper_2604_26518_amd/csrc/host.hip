@@ -621,8 +621,8 @@ static double prime_scale(const CycleCfg& c, int l) {
 // nu smoothing steps on level l; u / ualt are swapped so that u holds the result.
 // Gauss-Seidel (p1 = omega) runs the colours 0..7, or 7..0 when `post` (the
 // adjoint order, for the post-smoother), each colour as a weighted Jacobi step at
-// its nodes in place: no two of them share an element, so a node's neighbours are
-// all of other colours and nothing a sweep reads is written in it.
+// its nodes in place: no two of them are neighbours, so a node reads only itself of
+// what the sweep writes (EPI_GS).
 // primed: the zero start's first step is in u already.
 template <typename T>
 static void smooth(Hier& h, int l, const T* f, T*& u, T*& ualt, T* dvec, int nu, bool zero_start,
@@ -642,7 +642,7 @@ static void smooth(Hier& h, int l, const T* f, T*& u, T*& ualt, T* dvec, int nu,
         const int c = post ? 7 - k : k;
         if (d.col_off[c + 1] == d.col_off[c]) continue;
         const LevelView<T> v = colour_view<T>(h, l, c);
-        apply<T>(h, l, EPI_JACOBI, u, f, u, h.C, s, (T)p1, T(0), T(0), nullptr, &v);
+        apply<T>(h, l, EPI_GS, u, f, u, h.C, s, (T)p1, T(0), T(0), nullptr, &v);
       }
     return;
   }

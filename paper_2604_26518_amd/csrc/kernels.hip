@@ -64,7 +64,7 @@ __device__ __forceinline__ void epilogue_d(const EpiArgs<T>& e, size_t idx, T ac
     e.out[idx] = acc;
   } else if constexpr (EPI == EPI_RESID) {
     e.out[idx] = e.f[idx] - acc;
-  } else if constexpr (EPI == EPI_JACOBI) {
+  } else if constexpr (EPI == EPI_JACOBI || EPI == EPI_GS) {
     e.out[idx] = uself + e.omega * dinv * (e.f[idx] - acc);
   } else if constexpr (EPI == EPI_CHEB) {
     const T dn = e.rho1 * e.dvec_in[idx] + e.rho2 * dinv * (e.f[idx] - acc);
@@ -79,7 +79,7 @@ __device__ __forceinline__ void epilogue_d(const EpiArgs<T>& e, size_t idx, T ac
 
 template <int EPI>
 constexpr bool needs_dinv() {
-  return EPI == EPI_JACOBI || EPI == EPI_CHEB || EPI == EPI_CHEB0;
+  return EPI == EPI_JACOBI || EPI == EPI_GS || EPI == EPI_CHEB || EPI == EPI_CHEB0;
 }
 
 // Epilogue of node i for the CC cases c0, c0 + 1, .. and the D DOFs, with the
@@ -90,7 +90,7 @@ constexpr bool needs_dinv() {
 // store could not be moved above it, and each value would cost its own
 // round trip.  The arithmetic is that of epilogue_d.
 template <typename T, int EPI, int CC, int D>
-__device__ __forceinline__ void epilogue_node(const EpiArgs<T>& e, const T* __restrict__ u, size_t n, size_t i, int c0,
+__device__ __forceinline__ void epilogue_node(const EpiArgs<T>& e, sweep_input<T, EPI> u, size_t n, size_t i, int c0,
                                               const T* acc, const T* uself, const T* dv, const T* fpre = nullptr,
                                               const T* dpre = nullptr) {
   T fv[CC][D], dd[CC][D], us[CC][D], di[D];
@@ -119,7 +119,7 @@ __device__ __forceinline__ void epilogue_node(const EpiArgs<T>& e, const T* __re
         o[c][q] = a;
       } else if constexpr (EPI == EPI_RESID) {
         o[c][q] = fv[c][q] - a;
-      } else if constexpr (EPI == EPI_JACOBI) {
+      } else if constexpr (EPI == EPI_JACOBI || EPI == EPI_GS) {
         o[c][q] = us[c][q] + e.omega * di[q] * (fv[c][q] - a);
       } else if constexpr (EPI == EPI_CHEB) {
         dn[c][q] = e.rho1 * dd[c][q] + e.rho2 * di[q] * (fv[c][q] - a);
@@ -200,7 +200,7 @@ __device__ __forceinline__ void neighbour_ids(const int* __restrict__ map, int N
 // PRE: all 27 x D values of a case are loaded before the first FMA, which
 // keeps 27 gathers per wave in flight at the cost of registers (occupancy).
 template <typename T, int D, int EPI, int PRE>
-__device__ __forceinline__ void interior_plain(const LevelView<T>& L, int c0, int c1, const T* __restrict__ u,
+__device__ __forceinline__ void interior_plain(const LevelView<T>& L, int c0, int c1, sweep_input<T, EPI> u,
                                                const EpiArgs<T>& e, int t) {
   if (t >= L.n_int) return;
   const int i = L.interior[t];
@@ -244,7 +244,7 @@ __device__ __forceinline__ void interior_plain(const LevelView<T>& L, int c0, in
 }
 
 template <typename T, int D, int EPI, int PRE = 0>
-__global__ __launch_bounds__(kBlock) void k_apply_interior(LevelView<T> L, int C, const T* __restrict__ u, EpiArgs<T> e) {
+__global__ __launch_bounds__(kBlock) void k_apply_interior(LevelView<T> L, int C, sweep_input<T, EPI> u, EpiArgs<T> e) {
   interior_plain<T, D, EPI, PRE>(L, 0, C, u, e, block_index(L.xcd) * kBlock + (int)threadIdx.x);
 }
 
@@ -664,7 +664,7 @@ __global__ __launch_bounds__(kBlock) void k_apply_boundary_st(LevelView<T> L, co
 // of C cases, adjacent in the launch order: the rows of a node block run
 // together and share its neighbour-id rows and occupancy in L2.
 template <typename T, int D, int C, int EPI, int PRE>
-__device__ __forceinline__ void boundary_cls(const LevelView<T>& L, const T* __restrict__ u, const EpiArgs<T>& e, int t,
+__device__ __forceinline__ void boundary_cls(const LevelView<T>& L, sweep_input<T, EPI> u, const EpiArgs<T>& e, int t,
                                              int c0) {
   if (t >= L.n_bnd) return;
   const int i = L.boundary[t];
@@ -690,7 +690,7 @@ __device__ __forceinline__ void boundary_cls(const LevelView<T>& L, const T* __r
 #pragma unroll
   for (int j = 0; j < 27; ++j) {
     active |= (nb[j] >= 0 ? 1u : 0u) << j;
-    nb[j] = nb[j] >= 0 ? nb[j] : 0;
+    nb[j] = nb[j] >= 0 ? nb[j] : (EPI == EPI_GS ? i : 0);
   }
   T mk[8], mkn[8];
   if (L.oscale) {  // density hierarchy: the octant elements' stiffness scales (0 where inactive)
@@ -761,7 +761,7 @@ __device__ __forceinline__ void boundary_cls(const LevelView<T>& L, const T* __r
 }
 
 template <typename T, int D, int C, int EPI, int PRE = 0>
-__global__ __launch_bounds__(kBlock) void k_apply_boundary_cls(LevelView<T> L, const T* __restrict__ u, EpiArgs<T> e,
+__global__ __launch_bounds__(kBlock) void k_apply_boundary_cls(LevelView<T> L, sweep_input<T, EPI> u, EpiArgs<T> e,
                                                                int rows) {
   const int bi = block_index(L.xcd);
   boundary_cls<T, D, C, EPI, PRE>(L, u, e, (bi / rows) * kBlock + (int)threadIdx.x, (bi % rows) * C);
@@ -804,7 +804,7 @@ __device__ __forceinline__ Share level1_share(int xcd, unsigned nb, unsigned ni)
 // 3.0 with one.
 constexpr int kSplitInterior = 1 << 15;
 template <typename T, int D, int C, int EPI>
-__global__ __launch_bounds__(kBlock) void k_apply_lists(LevelView<T> L, const T* __restrict__ u, EpiArgs<T> e, int ic) {
+__global__ __launch_bounds__(kBlock) void k_apply_lists(LevelView<T> L, sweep_input<T, EPI> u, EpiArgs<T> e, int ic) {
   const unsigned nb = (unsigned)((L.n_bnd + kBlock - 1) / kBlock) * C;
   const unsigned rows = C / ic, ni = (unsigned)((L.n_int + kBlock - 1) / kBlock) * rows;
   const Share w = level1_share(L.xcd, nb, ni);
@@ -823,7 +823,7 @@ __global__ __launch_bounds__(kBlock) void k_apply_lists(LevelView<T> L, const T*
 // a scheduling barrier per neighbour keeps the compiler from hoisting the
 // loads of all 27 neighbours (27 x C x D live values would spill).
 template <typename T, int D, int C, int EPI>
-__global__ __launch_bounds__(kBlock) void k_apply_boundary_all(LevelView<T> L, const T* __restrict__ u, EpiArgs<T> e) {
+__global__ __launch_bounds__(kBlock) void k_apply_boundary_all(LevelView<T> L, sweep_input<T, EPI> u, EpiArgs<T> e) {
   const int t = block_index(L.xcd) * kBlock + threadIdx.x;
   if (t >= L.n_bnd) return;
   const int i = L.boundary[t];
@@ -860,8 +860,9 @@ __global__ __launch_bounds__(kBlock) void k_apply_boundary_all(LevelView<T> L, c
 #pragma unroll
     for (int q = 0; q < D; ++q) acc[c][q] = T(0);
   T vb[2][C][D];
+  const int absent = EPI == EPI_GS ? i : 0;  // where an absent neighbour's (unused) values are read
   {
-    const size_t id = nb[0] >= 0 ? nb[0] : 0;
+    const size_t id = nb[0] >= 0 ? nb[0] : absent;
 #pragma unroll
     for (int c = 0; c < C; ++c)
 #pragma unroll
@@ -871,7 +872,7 @@ __global__ __launch_bounds__(kBlock) void k_apply_boundary_all(LevelView<T> L, c
   for (int j = 0; j < 27; ++j) {
     const int cur = j & 1;
     if (j + 1 < 27) {
-      const size_t id = nb[j + 1] >= 0 ? nb[j + 1] : 0;
+      const size_t id = nb[j + 1] >= 0 ? nb[j + 1] : absent;
 #pragma unroll
       for (int c = 0; c < C; ++c)
 #pragma unroll
@@ -976,7 +977,7 @@ __global__ __launch_bounds__(kBlock) void k_apply_boundary(LevelView<T> L, int C
 // instructions.  An inactive element enters with weight 0 (its loads read a
 // valid matrix), an inactive neighbour with a zero block.
 template <typename T, int D, int CB, int KIND, int EPI, int BS, int NM = 0>
-__global__ __launch_bounds__(BS) void k_apply_coarse(LevelView<T> L, const T* __restrict__ u, EpiArgs<T> e) {
+__global__ __launch_bounds__(BS) void k_apply_coarse(LevelView<T> L, sweep_input<T, EPI> u, EpiArgs<T> e) {
   const int row = block_index(L.xcd) * BS + threadIdx.x;
   if (row >= (L.list ? L.n_list : L.n_n)) return;
   const int i = L.list ? L.list[row] : row;
@@ -1032,7 +1033,7 @@ __global__ __launch_bounds__(BS) void k_apply_coarse(LevelView<T> L, const T* __
 #pragma unroll
           for (int q2 = 0; q2 < D; ++q2) cj[q][q2] = fma(mk[k], Kk[k][q * M + m * D + q2], cj[q][q2]);
       }
-      const size_t id = nb[j] >= 0 ? nb[j] : 0;
+      const size_t id = nb[j] >= 0 ? nb[j] : (EPI == EPI_GS ? i : 0);
 #pragma unroll
       for (int c = 0; c < CB; ++c)
 #pragma unroll
@@ -2087,6 +2088,33 @@ static void apply_dispatch_kind(const LevelView<T>& L, int kind, const T* u, con
   GMT_LAUNCH_CHECK();
 }
 
+// One colour of a level, in place (EPI_GS): level 1 has its lists in variant 7, or the
+// boundary list alone in variant 5, 7 or 8 (density hierarchies).
+template <typename T, int D, int C>
+static void apply_dispatch_gs(const LevelView<T>& L, int kind, const T* u, const EpiArgs<T>& e, hipStream_t s) {
+  if (e.out != u) fail(GMT_E_STATE, "a colour is swept in place");
+  if (kind != KIND_SHARED) {
+    if ((L.cb == 1 || L.cb == 3) && C > 1)
+      launch_coarse<T, D, 1, EPI_GS>(L, kind, C, u, e, s);
+    else
+      launch_coarse<T, D, C, EPI_GS>(L, kind, 1, u, e, s);
+  } else if (L.n_int > 0 && L.n_bnd > 0) {
+    launch_lists<T, D, C, EPI_GS>(L, u, e, s);
+  } else if (L.n_int > 0) {
+    hipLaunchKernelGGL((k_apply_interior<T, D, EPI_GS, 1>), dim3(blocks_for(L.n_int)), dim3(kBlock), 0, s, L, C, u, e);
+  } else if (L.n_bnd > 0) {
+    const dim3 g(blocks_for(L.n_bnd) * C);
+    if (L.cb == 8)
+      hipLaunchKernelGGL((k_apply_boundary_all<T, D, C, EPI_GS>), dim3(blocks_for(L.n_bnd)), dim3(kBlock), 0, s, L, u,
+                         e);
+    else if (L.cb == 7)
+      hipLaunchKernelGGL((k_apply_boundary_cls<T, D, 1, EPI_GS, 1>), g, dim3(kBlock), 0, s, L, u, e, C);
+    else
+      hipLaunchKernelGGL((k_apply_boundary_cls<T, D, 1, EPI_GS>), g, dim3(kBlock), 0, s, L, u, e, C);
+  }
+  GMT_LAUNCH_CHECK();
+}
+
 template <typename T, int D, int C>
 static void apply_dispatch_epi(const LevelView<T>& L, int kind, int epi, const T* u, const EpiArgs<T>& e,
                                hipStream_t s) {
@@ -2102,6 +2130,12 @@ static void apply_dispatch_epi(const LevelView<T>& L, int kind, int epi, const T
 template <typename T>
 void launch_apply(const LevelView<T>& L, int kind, int D, int C, int epi, const T* u, const EpiArgs<T>& e,
                   hipStream_t s) {
+  if (epi == EPI_GS) {
+    if (D == 3 && C == 6) apply_dispatch_gs<T, 3, 6>(L, kind, u, e, s);
+    else if (D == 1 && C == 3) apply_dispatch_gs<T, 1, 3>(L, kind, u, e, s);
+    else fail(GMT_E_INVAL, "unsupported (d, c) = (%d, %d)", D, C);
+    return;
+  }
   if (D == 3 && C == 6) apply_dispatch_epi<T, 3, 6>(L, kind, epi, u, e, s);
   else if (D == 3 && C == 1) apply_dispatch_epi<T, 3, 1>(L, kind, epi, u, e, s);
   else if (D == 1 && C == 3) apply_dispatch_epi<T, 1, 3>(L, kind, epi, u, e, s);

@@ -82,7 +82,7 @@ __global__ __launch_bounds__(256) void k_stencil_build(int n, int N, int kind, c
 }
 
 template <typename T, int D, int CB, int EPI>
-__global__ __launch_bounds__(kBS) void k_apply_stencil(LevelView<T> L, const T* __restrict__ u, EpiArgs<T> e) {
+__global__ __launch_bounds__(kBS) void k_apply_stencil(LevelView<T> L, sweep_input<T, EPI> u, EpiArgs<T> e) {
   constexpr int DD = D * D;
   const int row = block_index(L.xcd) * kBS + threadIdx.x;
   if (row >= (L.list ? L.n_list : L.n_n)) return;
@@ -96,7 +96,7 @@ __global__ __launch_bounds__(kBS) void k_apply_stencil(LevelView<T> L, const T* 
   for (int g = 0; g < kGroups; ++g) ids[g] = nbr[(size_t)g * n + i];
   // own values and epilogue inputs: loaded with the first group
   T fv[CB][D], dd[CB][D], us[CB][D], di[D], acc[CB][D];
-  constexpr bool kDinv = EPI == EPI_JACOBI || EPI == EPI_CHEB || EPI == EPI_CHEB0;
+  constexpr bool kDinv = EPI == EPI_JACOBI || EPI == EPI_GS || EPI == EPI_CHEB || EPI == EPI_CHEB0;
 #pragma unroll
   for (int q = 0; q < D; ++q) di[q] = kDinv ? e.dinv[i * D + q] : T(0);
 #pragma unroll
@@ -141,7 +141,7 @@ __global__ __launch_bounds__(kBS) void k_apply_stencil(LevelView<T> L, const T* 
         o[c][q] = acc[c][q];
       } else if constexpr (EPI == EPI_RESID) {
         o[c][q] = fv[c][q] - acc[c][q];
-      } else if constexpr (EPI == EPI_JACOBI) {
+      } else if constexpr (EPI == EPI_JACOBI || EPI == EPI_GS) {
         o[c][q] = us[c][q] + e.omega * di[q] * (fv[c][q] - acc[c][q]);
       } else {
         dn[c][q] = e.rho2 * di[q] * (fv[c][q] - acc[c][q]);
@@ -170,6 +170,7 @@ void dispatch_epi(const LevelView<T>& L, int rows, int epi, const T* u, const Ep
     case EPI_KU: hipLaunchKernelGGL((k_apply_stencil<T, D, CB, EPI_KU>), g, dim3(kBS), 0, s, L, u, e); break;
     case EPI_RESID: hipLaunchKernelGGL((k_apply_stencil<T, D, CB, EPI_RESID>), g, dim3(kBS), 0, s, L, u, e); break;
     case EPI_JACOBI: hipLaunchKernelGGL((k_apply_stencil<T, D, CB, EPI_JACOBI>), g, dim3(kBS), 0, s, L, u, e); break;
+    case EPI_GS: hipLaunchKernelGGL((k_apply_stencil<T, D, CB, EPI_GS>), g, dim3(kBS), 0, s, L, u, e); break;
     case EPI_CHEB: hipLaunchKernelGGL((k_apply_stencil<T, D, CB, EPI_CHEB>), g, dim3(kBS), 0, s, L, u, e); break;
     default: hipLaunchKernelGGL((k_apply_stencil<T, D, CB, EPI_CHEB0>), g, dim3(kBS), 0, s, L, u, e); break;
   }

@@ -159,3 +159,56 @@ def test_transfers_around_the_split(N, L, phys):
             print(f"[transfers {N} {phys}] level {l} ({n} -> {nc}) {dt}: |err| / bound {e[0]:.3f} {e[1]:.3f}", flush=True)
             assert max(e) <= 1.0
     H.close()
+
+
+def _reach(lin, N, start, colours):
+    """Nodes (of the active node list `lin`) that a value at node `start` can reach in a Gauss-Seidel
+    pass over `colours`: a node takes up what its up to 27 active periodic neighbours hold."""
+    active = np.zeros(N ** 3, dtype=bool)
+    active[lin] = True
+    hit = np.zeros(N ** 3, dtype=bool)
+    hit[lin[start]] = True
+    z, y, x = np.meshgrid(*[np.arange(N)] * 3, indexing="ij")
+    colour = (x % 2 + 2 * (y % 2) + 4 * (z % 2)).reshape(-1)
+    for c in colours:
+        near = np.zeros((N, N, N), dtype=bool)
+        h = hit.reshape(N, N, N)
+        for dz in (-1, 0, 1):
+            for dy in (-1, 0, 1):
+                for dx in (-1, 0, 1):
+                    near |= np.roll(h, (dz, dy, dx), (0, 1, 2))
+        hit |= near.reshape(-1) & active & (colour == c)
+    return hit[lin]
+
+
+@pytest.mark.parametrize("value", [np.inf, np.nan])
+@pytest.mark.parametrize("cell", ["gyroid40", "gyroid40_th", "density32", "density32_th"])
+def test_gauss_seidel_reads_its_neighbours_only(cell, value, monkeypatch):
+    """A pass with a non-finite value at node 0 leaves every node that this value cannot reach as a pass
+    without it does, in every sweep variant (absent neighbours read nothing that the pass writes)."""
+    B = _gmt()
+    phys = "thermal" if cell.endswith("th") else "elastic"
+    if cell.startswith("density"):
+        rho = gyroid_sheet(32, 1, 0.3).astype(np.float64)
+        H = B.Hierarchy(None, 3, phys, density=rho, prune=1e-5)
+    else:
+        H = B.Hierarchy(gyroid_sheet(40, 3, 0.3), 4, phys)
+    H.solve(H.load_vector(), precision="f32", tol=1e-3)  # lays the assembled stencils out
+    for l in range(1, H.L):
+        lin = H.export_maps(l)["node_lin"].cpu().numpy()
+        N = H.N >> (l - 1)
+        far = torch.as_tensor(~_reach(lin, N, 0, range(8)), device=DEV)
+        assert far.any()
+        n = len(lin)
+        f = _t(random_vectors(n, H.c * H.d, 3).reshape(n, H.c, H.d))
+        u = _t(random_vectors(n, H.c * H.d, 4).reshape(n, H.c, H.d))
+        bad = u.clone()
+        bad[0] = value
+        for variant in (5, 7, 8) if l == 1 else (0, 1, 2, 3, 4, 5):
+            monkeypatch.setenv("GMT_FORCE_L1_VARIANT" if l == 1 else "GMT_FORCE_COARSE_VARIANT", str(variant))
+            for dt in (torch.float32, torch.float64):
+                want = H.smooth(f.to(dt), u.to(dt, copy=True), 1, "gs", 1.0, 0.0, level=l)
+                got = H.smooth(f.to(dt), bad.to(dt, copy=True), 1, "gs", 1.0, 0.0, level=l)
+                assert torch.isfinite(want).all()
+                assert torch.equal(got[far], want[far]), (l, variant, dt)
+    H.close()
