@@ -918,47 +918,66 @@ constexpr int kStencilTableNodes = 1 << 18;
 // entry points that return a cycle's own result or its gradient, which follow the
 // rounding of every coarse sweep (up to 1e-3 where coarse translations are weakly fixed).
 template <typename T>
-static void ensure_stencils(Hier& h, hipStream_t s) {
+static bool build_stencil(Hier& h, int l, hipStream_t s) {
   constexpr bool f32 = !std::is_same<T, double>::value;
-  if (!f32 && !h.density) return;
-  for (int l = 1; l + 1 < h.L; ++l) {
-    LevelData& d = h.lv[l];
-    if ((f32 ? (void*)d.stc32 : (void*)d.stc64) || d.n_n == 0) continue;
-    if (d.kind == KIND_TABLE && d.n_n >= kStencilTableNodes) continue;
-    bool& tried = f32 ? d.stried32 : d.stried64;
-    if (tried) continue;
+  LevelData& d = h.lv[l];
+  if (f32 ? (void*)d.stc32 : (void*)d.stc64) return true;
+  if ((!f32 && !h.density) || d.n_n == 0 || (d.kind == KIND_TABLE && d.n_n >= kStencilTableNodes)) return false;
+  bool& tried = f32 ? d.stried32 : d.stried64;
+  if (tried) return false;
+  T* stc = nullptr;
+  int* nbr = d.snbr;
+  try {
+    stc = h.alloc<T>(stencil_values(d.n_n, h.D));
+    if (!nbr) nbr = h.alloc<int>(stencil_ids(d.n_n));
+  } catch (const Failure& f) {
+    if (f.status != GMT_E_NOMEM) throw;
+  }
+  if (!stc || !nbr || (reinterpret_cast<uintptr_t>(stc) | reinterpret_cast<uintptr_t>(nbr)) % 16 != 0) {
+    // no room, or an allocator callback's memory that 16-byte reads cannot use: the
+    // sweeps keep the element matrices
     tried = true;
-    T* stc = nullptr;
-    int* nbr = d.snbr;
-    try {
-      stc = h.alloc<T>(stencil_values(d.n_n, h.D));
-      if (!nbr) nbr = h.alloc<int>(stencil_ids(d.n_n));
-    } catch (const Failure& f) {
-      if (f.status != GMT_E_NOMEM) throw;
-    }
-    if (!stc || !nbr || (reinterpret_cast<uintptr_t>(stc) | reinterpret_cast<uintptr_t>(nbr)) % 16 != 0) {
-      // no room, or an allocator callback's memory that 16-byte reads cannot use: the
-      // sweeps keep the element matrices
-      if (stc) h.release(stc);
-      if (nbr && nbr != d.snbr) h.release(nbr);
-      continue;
-    }
-    d.snbr = nbr;
-    launch_stencil_build<T>(d.n_n, d.N, h.D, d.kind, d.node_lin, d.node_map, d.elem_map, d.cmask,
-                            d.kind == KIND_TABLE ? h.table64 : d.Kel64, stc, d.snbr, s);
-    if constexpr (f32) d.stc32 = stc;
-    else d.stc64 = stc;
+    if (stc) h.release(stc);
+    if (nbr && nbr != d.snbr) h.release(nbr);
+    return false;
+  }
+  d.snbr = nbr;
+  launch_stencil_build<T>(d.n_n, d.N, h.D, d.kind, d.node_lin, d.node_map, d.elem_map, d.cmask,
+                          d.kind == KIND_TABLE ? h.table64 : d.Kel64, stc, d.snbr, s);
+  if constexpr (f32) d.stc32 = stc;
+  else d.stc64 = stc;
+  return true;
+}
+
+// Frees level l's stencils of precision T; no work that reads them may be queued.
+template <typename T>
+static void drop_stencil(Hier& h, int l) {
+  LevelData& d = h.lv[l];
+  if constexpr (std::is_same<T, double>::value) {
+    if (d.stc64) h.release(d.stc64);
+    d.stc64 = nullptr;
+    d.scb64 = 0;
+  } else {
+    if (d.stc32) h.release(d.stc32);
+    d.stc32 = nullptr;
+    d.scb32 = 0;
+  }
+  if (!d.stc32 && !d.stc64 && d.snbr) {
+    h.release(d.snbr);
+    d.snbr = nullptr;
   }
 }
 
-// Builds the stencils and takes, per level, the fastest of their sweeps if it beats the
-// tuned element sweep (timed beside it; choices cached like the launch shapes).  Called
-// with a solve's other buffers in place, which have the first claim on the memory.
+// Takes, per level, the fastest of the stencil sweeps if it beats the tuned element sweep
+// (timed beside it; choices cached like the launch shapes).  Stencils are laid out where
+// the choice is one of their sweeps or has to be timed, and kept only where it is one.
 template <typename T>
 static void tune_stencils(Hier& h, hipStream_t s) {
   constexpr bool f32 = !std::is_same<T, double>::value;
   if (tune_off()) return;
-  ensure_stencils<T>(h, s);
+  const int pinned = forced_coarse_variant();
+  if (pinned >= 0 && pinned < kStencilAll) return;  // tests: no stencil sweep would run or could be timed
+  const bool forced = pinned >= kStencilAll;        // tests: laid out whatever the choice
   h.ensure_work<T>();
   Work<T>& W = h.work<T>();
   hipEvent_t e0 = nullptr, e1 = nullptr;
@@ -967,18 +986,28 @@ static void tune_stencils(Hier& h, hipStream_t s) {
     bool& tuned = f32 ? d.stuned32 : d.stuned64;
     int& cb = f32 ? d.scb32 : d.scb64;
     int& xcd = f32 ? d.sxcd32 : d.sxcd64;
-    if (tuned || !(f32 ? (void*)d.stc32 : (void*)d.stc64)) continue;
-    tuned = true;
+    if (tuned) continue;
     std::vector<int> key = tune_key(h, d, f32);
     key.push_back(1);  // the stencil choice of the class
+    Shape pick{64, 0, 1};
+    bool known = false;
     {
       std::lock_guard<std::mutex> g(g_tune_mu);
       auto it = g_tune.find(key);
       if (it != g_tune.end()) {
-        cb = it->second.cb;
-        xcd = it->second.xcd;
-        continue;
+        pick = it->second;
+        known = true;
       }
+    }
+    if ((known && pick.cb == 0 && !forced) || !build_stencil<T>(h, l, s)) {
+      tuned = true;
+      continue;
+    }
+    tuned = true;
+    if (known) {
+      cb = pick.cb;
+      xcd = pick.xcd;
+      continue;
     }
     if (!e0) {
       GMT_HIP(hipEventCreate(&e0));
@@ -987,7 +1016,6 @@ static void tune_stencils(Hier& h, hipStream_t s) {
     launch_fill<T>(W.u[l], (size_t)d.n_n * h.Q, T(0), s);
     const bool keep = h.solving;
     h.solving = true;
-    Shape pick{64, 0, 1};
     float best = INFINITY;
     for (int c : {0, kStencilAll, kStencilOne, kStencilTwo}) {
       if (c == kStencilTwo && h.D != 3) continue;
@@ -1004,6 +1032,7 @@ static void tune_stencils(Hier& h, hipStream_t s) {
     h.solving = keep;
     cb = pick.cb;
     xcd = pick.xcd;
+    if (cb == 0 && !forced) drop_stencil<T>(h, l);  // (time_shape has waited for the sweeps)
     if (std::getenv("GMT_TIMING"))
       fprintf(stderr, "[gmt tune] level %d (%s, n_n %d) stencil: cb %d xcd %d, %.1f us\n", l + 1, f32 ? "f32" : "f64",
               d.n_n, cb, xcd, best * 1e3);
@@ -2240,9 +2269,16 @@ static void stage_out(Hier& h, int l, const T* src, void* dst, hipStream_t s) {
   launch_soa_to_aos<T, T>(src, (T*)dst, h.lv[l].n_n, h.C, h.D, s);
 }
 
+// tests: a pinned stencil sweep on a level whose solves take the element matrices
+template <typename T>
+static void forced_stencil(Hier& h, int l, hipStream_t s) {
+  if (l > 0 && l + 1 < h.L && forced_coarse_variant() >= kStencilAll) build_stencil<T>(h, l, s);
+}
+
 template <typename T>
 static void apply_api(Hier& h, int l, int epi, const void* d_u, const void* d_f, void* d_out, hipStream_t s) {
   h.ensure_io<T>(l);
+  forced_stencil<T>(h, l, s);
   Work<T>& W = h.work<T>();
   const T* u = stage_in<T>(h, l, d_u, W.io1[l], s);
   const T* f = d_f ? stage_in<T>(h, l, d_f, W.io2[l], s) : nullptr;
@@ -2281,6 +2317,7 @@ template <typename T>
 static void smooth_abi(Hier& h, int l, const void* d_f, void* d_u, int nu, int sm, double p1, double p2,
                        hipStream_t s) {
   h.ensure_io<T>(l);
+  forced_stencil<T>(h, l, s);
   Work<T>& W = h.work<T>();
   const T* f = stage_in<T>(h, l, d_f, W.io1[l], s);
   T* u = stage_in<T>(h, l, d_u, W.io2[l], s);
