@@ -246,7 +246,10 @@ gmt_status gmt_solve(gmt_hier_t h, const void* d_f, void* d_u, const gmt_solve_o
  * 4), each driving its own HIP stream, so small cells overlap on the GPU; each
  * cell's inner PCG replays captured hipGraph blocks when opts->graph is set.
  * All work buffers are allocated on the calling thread before the workers
- * start.  reports[i] / status[i] (either may be NULL) receive each cell's
+ * start, except those of a mixed-precision solve that goes on in FP64: they come
+ * from hipMalloc on the worker, or where that finds no room, from the allocator
+ * on the calling thread after the other cells, and that cell starts again.
+ * reports[i] / status[i] (either may be NULL) receive each cell's
  * outcome; the call returns the first non-OK status (GMT_E_NOCONV included)
  * or GMT_OK.  The caller's stream is synchronized first; the call returns when
  * every cell is done. */

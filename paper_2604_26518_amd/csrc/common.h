@@ -473,6 +473,7 @@ struct Hier {
   std::vector<void*> owned;      // from the caller's allocation callback
   std::vector<void*> owned_hip;  // from hipMalloc (no callback, or local_alloc)
   bool local_alloc = false;      // allocate with hipMalloc even when a callback is set
+  bool keep_stencils = false;    // an allocation that fails does not free the stencils
   void* nn = nullptr;  // learned-initializer state (nn.hip)
   // captured blocks of inner PCG iterations (1 and 4 iterations), per precision;
   // valid while `key` (cycle parameters and iterate buffer) is unchanged
@@ -482,9 +483,14 @@ struct Hier {
   };
   PcgGraphs g32, g64, gmx;  // FP32, FP64, FP64 Krylov with the FP32 V-cycle
   hipStream_t cap = nullptr;  // non-blocking stream used only to record the captures
-  void release_graphs();
+  void release_execs();   // the executable graphs
+  void release_graphs();  // and the stream
 
   void* raw_alloc(size_t bytes);
+  void* try_alloc(size_t bytes, hipError_t* err);  // nullptr where there is no room
+  // Frees the assembled stencils, which only save time (and are not laid out again), and the
+  // graphs that read them; false where there are none, or none that this thread may free.
+  bool release_stencils();
   void release(void* ptr);  // frees one buffer obtained from raw_alloc
   template <typename T>
   T* alloc(size_t n) {

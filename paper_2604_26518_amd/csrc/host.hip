@@ -51,22 +51,51 @@ static gmt_status guarded(F&& fn) {
 
 // ================================================================ allocation
 
-void* Hier::raw_alloc(size_t bytes) {
+// GMT_HIP_ALLOC_MAX=<bytes>: larger requests to hipMalloc find no room (tests).
+void* Hier::try_alloc(size_t bytes, hipError_t* err) {
   void* ptr = nullptr;
-  const bool callback = p.alloc && !local_alloc;
-  if (callback) {
+  *err = hipSuccess;
+  if (p.alloc && !local_alloc) {
     ptr = p.alloc(bytes, p.alloc_ctx);
-    if (!ptr) fail(GMT_E_NOMEM, "allocator callback returned NULL for %zu bytes", bytes);
-    owned.push_back(ptr);
-  } else {
-    hipError_t e = hipMalloc(&ptr, bytes);
-    if (e != hipSuccess || !ptr) {
-      (void)hipGetLastError();
-      fail(GMT_E_NOMEM, "hipMalloc(%zu) failed: %s", bytes, hipGetErrorString(e));
-    }
-    owned_hip.push_back(ptr);
+    if (ptr) owned.push_back(ptr);
+    return ptr;
   }
+  const char* e = std::getenv("GMT_HIP_ALLOC_MAX");
+  *err = e && *e && bytes > std::strtoull(e, nullptr, 10) ? hipErrorOutOfMemory : hipMalloc(&ptr, bytes);
+  if (*err != hipSuccess || !ptr) {
+    (void)hipGetLastError();
+    return nullptr;
+  }
+  owned_hip.push_back(ptr);
   return ptr;
+}
+
+void* Hier::raw_alloc(size_t bytes) {
+  hipError_t err;
+  void* ptr = try_alloc(bytes, &err);
+  if (!ptr && !keep_stencils && release_stencils()) ptr = try_alloc(bytes, &err);
+  if (ptr) return ptr;
+  if (p.alloc && !local_alloc) fail(GMT_E_NOMEM, "allocator callback returned NULL for %zu bytes", bytes);
+  fail(GMT_E_NOMEM, "hipMalloc(%zu) failed: %s", bytes, hipGetErrorString(err));
+}
+
+bool Hier::release_stencils() {
+  bool any = false;
+  for (const LevelData& d : lv) any = any || d.stc32 || d.stc64;
+  if (!any || (p.alloc && local_alloc)) return false;  // the callback is not for this thread
+  if (hipDeviceSynchronize() != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  release_execs();
+  for (LevelData& d : lv) {
+    if (d.stc32) release(d.stc32), d.stc32 = nullptr;
+    if (d.stc64) release(d.stc64), d.stc64 = nullptr;
+    if (d.snbr) release(d.snbr), d.snbr = nullptr;
+    d.scb32 = d.scb64 = 0;
+    d.stried32 = d.stried64 = true;
+  }
+  return true;
 }
 
 void Hier::release(void* q) {
@@ -83,12 +112,16 @@ void Hier::release(void* q) {
   }
 }
 
-void Hier::release_graphs() {
+void Hier::release_execs() {
   for (PcgGraphs* g : {&g32, &g64, &gmx}) {
     for (auto& e : g->exec)
       if (e) (void)hipGraphExecDestroy(e), e = nullptr;
     g->key.clear();
   }
+}
+
+void Hier::release_graphs() {
+  release_execs();
   if (cap) (void)hipStreamDestroy(cap), cap = nullptr;
 }
 
@@ -208,30 +241,23 @@ template <typename T>
 void Hier::ensure_work() {
   Work<T>& W = work<T>();
   if (W.ready) return;
-  W.f.assign(L, nullptr);
-  W.u.assign(L, nullptr);
-  W.io1.assign(L, nullptr);
-  W.io2.assign(L, nullptr);
-  W.io3.assign(L, nullptr);
-  W.ualt.assign(L, nullptr);
-  W.dvec.assign(L, nullptr);
-  W.r.assign(L, nullptr);
+  for (auto* v : {&W.f, &W.u, &W.io1, &W.io2, &W.io3, &W.ualt, &W.dvec, &W.r}) v->resize(L, nullptr);
+  // (a call that ran out of memory left the buffers before it in place)
+  auto need = [&](T*& q, size_t n) {
+    if (!q) q = alloc<T>(n);
+  };
   for (int l = 0; l < L; ++l) {
     const size_t n = (size_t)lv[l].n_n * Q;
     if (l > 0) {
-      W.f[l] = alloc<T>(n);
-      W.u[l] = alloc<T>(n);
+      need(W.f[l], n);
+      need(W.u[l], n);
     }
-    W.ualt[l] = alloc<T>(n);
-    W.dvec[l] = alloc<T>(n);
-    W.r[l] = alloc<T>(n);
+    need(W.ualt[l], n);
+    need(W.dvec[l], n);
+    need(W.r[l], n);
   }
   const size_t n0 = (size_t)lv[0].n_n * Q;
-  W.pr = alloc<T>(n0);
-  W.pz = alloc<T>(n0);
-  W.pp = alloc<T>(n0);
-  W.pq = alloc<T>(n0);
-  W.px = alloc<T>(n0);
+  for (T** q : {&W.pr, &W.pz, &W.pp, &W.pq, &W.px}) need(*q, n0);
   W.ready = true;
 }
 
@@ -239,11 +265,9 @@ template <typename T>
 void Hier::ensure_io(int l) {
   ensure_work<T>();
   Work<T>& W = work<T>();
-  if (W.io1[l]) return;
   const size_t n = (size_t)lv[l].n_n * Q;
-  W.io1[l] = alloc<T>(n);
-  W.io2[l] = alloc<T>(n);
-  W.io3[l] = alloc<T>(n);
+  for (T** q : {&W.io1[l], &W.io2[l], &W.io3[l]})
+    if (!*q) *q = alloc<T>(n);
 }
 
 template LevelView<float> Hier::view<float>(int) const;
@@ -927,12 +951,15 @@ static bool build_stencil(Hier& h, int l, hipStream_t s) {
   if (tried) return false;
   T* stc = nullptr;
   int* nbr = d.snbr;
+  h.keep_stencils = true;  // those of the other levels
   try {
     stc = h.alloc<T>(stencil_values(d.n_n, h.D));
     if (!nbr) nbr = h.alloc<int>(stencil_ids(d.n_n));
   } catch (const Failure& f) {
+    h.keep_stencils = false;
     if (f.status != GMT_E_NOMEM) throw;
   }
+  h.keep_stencils = false;
   if (!stc || !nbr || (reinterpret_cast<uintptr_t>(stc) | reinterpret_cast<uintptr_t>(nbr)) % 16 != 0) {
     // no room, or an allocator callback's memory that 16-byte reads cannot use: the
     // sweeps keep the element matrices
@@ -970,7 +997,8 @@ static void drop_stencil(Hier& h, int l) {
 
 // Takes, per level, the fastest of the stencil sweeps if it beats the tuned element sweep
 // (timed beside it; choices cached like the launch shapes).  Stencils are laid out where
-// the choice is one of their sweeps or has to be timed, and kept only where it is one.
+// the choice is one of their sweeps or has to be timed, and kept only where it is one; a
+// later buffer of the hierarchy that finds no room takes theirs (Hier::raw_alloc).
 template <typename T>
 static void tune_stencils(Hier& h, hipStream_t s) {
   constexpr bool f32 = !std::is_same<T, double>::value;
@@ -2536,12 +2564,11 @@ gmt_status gmt_solve_batch(gmt_hier_t const* hs, int32_t n, const void* const* d
       const double share = d0.n_n > 0 ? (double)d0.n_bnd / d0.n_n : 0.0;
       cost[i] = (double)d0.n_n * hs[i]->h.Q * std::exp(12.0 * share);
     }
-    std::vector<int> order(n);
+    std::vector<int> order(n);  // the cells still to solve
     for (int i = 0; i < n; ++i) order[i] = i;
     std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return cost[a] > cost[b]; });
     int dev = 0;
     GMT_HIP(hipGetDevice(&dev));
-    const int nw = std::max(1, std::min(n_workers > 0 ? n_workers : 4, std::max(n, 1)));
     std::atomic<int> next{0};
     auto worker = [&]() {
       hipStream_t ws = nullptr;
@@ -2551,7 +2578,7 @@ gmt_status gmt_solve_batch(gmt_hier_t const* hs, int32_t n, const void* const* d
       });
       for (;;) {
         const int k = next.fetch_add(1);
-        if (k >= n) break;
+        if (k >= (int)order.size()) break;
         const int i = order[k];
         if (ok != GMT_OK) {
           st[i] = ok;
@@ -2588,9 +2615,38 @@ gmt_status gmt_solve_batch(gmt_hier_t const* hs, int32_t n, const void* const* d
       }
       if (ws) (void)hipStreamDestroy(ws);
     };
-    std::vector<std::thread> pool;
-    for (int w = 0; w < nw; ++w) pool.emplace_back(worker);
-    for (auto& t : pool) t.join();
+    auto run = [&]() {
+      const int nw = std::max(1, std::min(n_workers > 0 ? n_workers : 4, (int)std::max(order.size(), (size_t)1)));
+      next = 0;
+      std::vector<std::thread> pool;
+      for (int w = 0; w < nw; ++w) pool.emplace_back(worker);
+      for (auto& t : pool) t.join();
+    };
+    run();
+    // Cells that found no room for the buffers of the FP64 recurrence get them on this
+    // thread, where the callback and the stencils of every cell can be used for them, and
+    // start again (their d_u is as the caller gave it).
+    std::vector<int> again;
+    for (int i : order)
+      if (st[i] == GMT_E_NOMEM) again.push_back(i);
+    if (!again.empty()) {
+      GMT_HIP(hipDeviceSynchronize());
+      order.clear();
+      for (int i : again) {
+        auto buffers = [&] {
+          scratch64(hs[i]->h, &hs[i]->h.s_x64);
+          hs[i]->h.ensure_work<double>();
+        };
+        gmt_status ok = guarded(buffers);
+        if (ok == GMT_E_NOMEM) {
+          bool freed = false;
+          for (int j = 0; j < n; ++j) freed |= hs[j]->h.release_stencils();
+          if (freed) ok = guarded(buffers);
+        }
+        if (ok == GMT_OK) order.push_back(i);
+      }
+      if (!order.empty()) run();
+    }
   });
   if (status)
     for (int i = 0; i < n; ++i) status[i] = st[i];

@@ -78,3 +78,68 @@ def test_no_stencils_where_no_sweep_takes_them(density, monkeypatch):
     sizes = {_stencil_bytes(H, l) for l in (2, 3)} | {2 * _stencil_bytes(H, l) - 16 for l in (2, 3)}
     assert not sizes & set(H._arena.made)
     H.close()
+
+
+class Budget(Recorder):
+    """No more than `limit` bytes live over all arenas (None: any number); `peak`: the most there were."""
+
+    limit = None
+    live_bytes = 0
+    peak = 0
+
+    def _alloc(self, nbytes, ctx):
+        if Budget.limit is not None and Budget.live_bytes + int(nbytes) > Budget.limit:
+            return None
+        ptr = super()._alloc(nbytes, ctx)
+        if ptr is not None:
+            Budget.live_bytes += int(nbytes)
+            Budget.peak = max(Budget.peak, Budget.live_bytes)
+        return ptr
+
+    def _release(self, ptr, ctx):
+        Budget.live_bytes -= self.size.get(ptr, 0)
+        super()._release(ptr, ctx)
+
+
+@pytest.fixture
+def budget(monkeypatch):
+    monkeypatch.setattr(B, "_TorchArena", Budget)
+    monkeypatch.setattr(Budget, "limit", None)
+    monkeypatch.setattr(Budget, "live_bytes", 0)
+    monkeypatch.setattr(Budget, "peak", 0)
+    return Budget
+
+
+def _run(batch, graph, limit=None):
+    """Mixed solves that go on with the FP64 recurrence after two FP32 iterations.  Returns the residuals,
+    whether every cell had stencils, and the most bytes that the solves had live."""
+    hs = [B.Hierarchy(gyroid_sheet(32, s, 0.3), 4, "elastic") for s in ((0, 1, 2) if batch else (0,))]
+    fs = [H.load_vector() for H in hs]
+    Budget.peak, Budget.limit = Budget.live_bytes, limit
+    if batch:
+        us, reps = B.solve_batch(hs, fs, tol=1e-8, precision="f32", n_workers=2, graph=graph)
+    else:
+        us, reps = zip(*[H.solve(f, tol=1e-8, precision="f32", graph=graph) for H, f in zip(hs, fs)])
+    peak, Budget.limit = Budget.peak, None
+    stencils = [any(_stencil_bytes(H, l) in H._arena.made for l in (2, 3)) for H in hs]
+    rel = [float(max(H.relative_residual(f, u))) for H, f, u in zip(hs, fs, us)]
+    assert all(r["converged"] for r in reps)
+    for H in hs:
+        H.close()
+    return max(rel), stencils, peak
+
+
+@pytest.mark.parametrize("graph", [False, True])
+@pytest.mark.parametrize("batch", [False, True])
+def test_stencils_make_room(batch, graph, budget, monkeypatch):
+    """Solves succeed in the memory that they take without stencils: the buffers of the FP64 recurrence
+    have the room of stencils laid out before.  The batch has no other memory than the callback's."""
+    monkeypatch.setenv("GMT_MAX_INNER32", "2")
+    if batch:
+        monkeypatch.setenv("GMT_HIP_ALLOC_MAX", "4096")
+    monkeypatch.setenv("GMT_FORCE_COARSE_VARIANT", "1")  # element matrices
+    rel, stencils, peak = _run(batch, graph)
+    assert rel <= 1e-8 and not any(stencils)
+    monkeypatch.setenv("GMT_FORCE_COARSE_VARIANT", "4")  # stencils, as long as they are held
+    rel, stencils, _ = _run(batch, graph, limit=peak)
+    assert rel <= 1e-8 and all(stencils)
