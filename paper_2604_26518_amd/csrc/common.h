@@ -508,6 +508,22 @@ struct Hier {
   void ensure_io(int l);  // staging buffers io1/io2/io3 of level l
 };
 
+// Hier::solving for a scope; an inner scope leaves it as it found it.
+struct Solving {
+  Hier& h;
+  const bool outer;
+  explicit Solving(Hier& hh) : h(hh), outer(hh.solving) { h.solving = true; }
+  ~Solving() { h.solving = outer; }
+};
+
+// Launch shape to try out in a scope: afterwards, also where a launch failed, it is what it was.
+struct Trial {
+  int &cb, &xcd;
+  const int cb0, xcd0;
+  Trial(int& c, int& x) : cb(c), xcd(x), cb0(c), xcd0(x) {}
+  ~Trial() { cb = cb0, xcd = xcd0; }
+};
+
 constexpr int kRedBlocks = 1024;
 
 // learned initializer (nn.hip)

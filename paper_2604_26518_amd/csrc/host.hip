@@ -449,12 +449,12 @@ static hipStream_t aux_stream(int k) {
   return v[(size_t)k % v.size()];
 }
 
-// Events (no timing) owned by a scope; destroyed when it ends.
+// Events owned by a scope; destroyed when it ends.
 struct EventSet {
   std::vector<hipEvent_t> ev;
-  hipEvent_t make() {
+  hipEvent_t make(unsigned flags = hipEventDisableTiming) {
     hipEvent_t e = nullptr;
-    GMT_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+    GMT_HIP(hipEventCreateWithFlags(&e, flags));
     ev.push_back(e);
     return e;
   }
@@ -1008,7 +1008,8 @@ static void tune_stencils(Hier& h, hipStream_t s) {
   const bool forced = pinned >= kStencilAll;        // tests: laid out whatever the choice
   h.ensure_work<T>();
   Work<T>& W = h.work<T>();
-  hipEvent_t e0 = nullptr, e1 = nullptr;
+  EventSet evs;
+  hipEvent_t ev[2] = {nullptr, nullptr};
   for (int l = 1; l + 1 < h.L; ++l) {
     LevelData& d = h.lv[l];
     bool& tuned = f32 ? d.stuned32 : d.stuned64;
@@ -1031,35 +1032,35 @@ static void tune_stencils(Hier& h, hipStream_t s) {
       tuned = true;
       continue;
     }
-    tuned = true;
     if (known) {
       cb = pick.cb;
       xcd = pick.xcd;
+      tuned = true;
       continue;
     }
-    if (!e0) {
-      GMT_HIP(hipEventCreate(&e0));
-      GMT_HIP(hipEventCreate(&e1));
-    }
+    if (!ev[0])
+      for (hipEvent_t& e : ev) e = evs.make(hipEventDefault);
     launch_fill<T>(W.u[l], (size_t)d.n_n * h.Q, T(0), s);
-    const bool keep = h.solving;
-    h.solving = true;
     float best = INFINITY;
-    for (int c : {0, kStencilAll, kStencilOne, kStencilTwo}) {
-      if (c == kStencilTwo && h.D != 3) continue;
-      for (int x = 1; x >= (c ? 0 : 1); --x) {
-        cb = c;
-        xcd = x;
-        const float ms = time_shape<T>(h, l, W.u[l], W.r[l], e0, e1, s);
-        if (ms < best) {
-          best = ms;
-          pick = {64, c, x};
+    {
+      const Solving scope(h);
+      const Trial trial(cb, xcd);
+      for (int c : {0, kStencilAll, kStencilOne, kStencilTwo}) {
+        if (c == kStencilTwo && h.D != 3) continue;
+        for (int x = 1; x >= (c ? 0 : 1); --x) {
+          cb = c;
+          xcd = x;
+          const float ms = time_shape<T>(h, l, W.u[l], W.r[l], ev[0], ev[1], s);
+          if (ms < best) {
+            best = ms;
+            pick = {64, c, x};
+          }
         }
       }
     }
-    h.solving = keep;
     cb = pick.cb;
     xcd = pick.xcd;
+    tuned = true;
     if (cb == 0 && !forced) drop_stencil<T>(h, l);  // (time_shape has waited for the sweeps)
     if (std::getenv("GMT_TIMING"))
       fprintf(stderr, "[gmt tune] level %d (%s, n_n %d) stencil: cb %d xcd %d, %.1f us\n", l + 1, f32 ? "f32" : "f64",
@@ -1067,8 +1068,6 @@ static void tune_stencils(Hier& h, hipStream_t s) {
     std::lock_guard<std::mutex> g(g_tune_mu);
     g_tune[key] = pick;
   }
-  if (e0) (void)hipEventDestroy(e0);
-  if (e1) (void)hipEventDestroy(e1);
 }
 
 static void host_dot(Hier& h, const double* dev, int n, double* out, hipStream_t s) {
@@ -1893,12 +1892,6 @@ static void borrow_f32_shape(Hier& h) {
   d.cb64 = d.cb32;
   d.xcd64 = d.xcd32;
 }
-
-struct Solving {  // Hier::solving for a scope
-  Hier& h;
-  explicit Solving(Hier& hh) : h(hh) { h.solving = true; }
-  ~Solving() { h.solving = false; }
-};
 
 static void solve(Hier& h, const double* f, double* u, const gmt_solve_opts* o, gmt_solve_report* rep,
                   hipStream_t s, gmt_status* st, bool u_zero = false) {
