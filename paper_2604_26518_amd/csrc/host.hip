@@ -426,9 +426,9 @@ static void mask_table(const Hier& h, const double Ps[8][8][8], std::vector<doub
 
 // ================================================================ coarsest level
 
-// Dense FP64 Cholesky of the pinned coarsest matrix and its explicit inverse.
 // Auxiliary streams for independent setup work of one hierarchy (the power
-// iterations of its levels), four per device, created on first use and kept
+// iterations of its coarse levels, level l on stream (l - 2) mod 4, and the
+// inversion of the coarsest operator), four per device, created on first use and kept
 // for the life of the process; default priority, non-blocking.  Work on them
 // is ordered against the caller's stream by events only, so hierarchies built
 // at the same time from several threads may share them safely.
@@ -1781,7 +1781,10 @@ static void build(Hier& h, const uint8_t* vox, hipStream_t s, const double* rho 
     hipEvent_t fork = evs.make(), coarse_done = evs.make();
     GMT_HIP(hipEventRecord(fork, s));
     {
-      // the coarsest operator is inverted beside the iterations
+      // The coarsest operator is inverted beside the iterations; from five levels on, those of
+      // one coarse level share its stream and follow it (which stream it takes makes no
+      // difference: build of a 112^3 cell, 1029 rows behind level 2 or before level 5, 4.25 and
+      // 4.39 ms)
       hipStream_t sc = aux_stream(h.L - 1);
       GMT_HIP(hipStreamWaitEvent(sc, fork, 0));
       const std::array<void*, 2> tmp = coarse_factor(h, sc, o + 56);
