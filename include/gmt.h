@@ -445,8 +445,10 @@ gmt_status gmt_vcycle_loss(gmt_hier_t h, const float* const* d_pred, const gmt_c
 /* Instrumentation (tracing/profiling): times `reps` Chebyshev sweeps of
  * level l (the fused K.u + smoother update, on internal FP32 or FP64 work
  * vectors, no layout staging) with HIP events recorded on the given stream and
- * returns the mean duration of one sweep in h_ms.  Level 1 sweeps launch two
- * kernels (all-solid interior nodes, boundary nodes).  Synchronizes the stream. */
+ * returns the mean duration of one sweep in h_ms.  It is the sweep that solves
+ * run: in the launch shape timed for them and, on the levels in between, from
+ * assembled stencils where they take those.  A level-1 sweep is one to three
+ * launches (interior and boundary nodes).  Synchronizes the stream. */
 gmt_status gmt_time_sweep(gmt_hier_t h, int32_t level, int32_t reps, int32_t dtype, double* h_ms,
                           void* stream);
 

@@ -2066,7 +2066,10 @@ const char* gmt_last_error(void) { return g_last_error.c_str(); }
 
 template <typename T>
 static double time_sweep(Hier& h, int l, int reps, hipStream_t s) {
-  autotune<T>(h, s);  // time the launch shape the solver uses
+  // the sweep that the solver runs: its launch shape, or a stencil where it takes one
+  autotune<T>(h, s);
+  if (l > 0) tune_stencils<T>(h, s);
+  const Solving scope(h);
   h.ensure_io<T>(l);
   Work<T>& W = h.work<T>();
   const size_t n = (size_t)h.lv[l].n_n * h.Q;

@@ -143,3 +143,13 @@ def test_stencils_make_room(batch, graph, budget, monkeypatch):
     monkeypatch.setenv("GMT_FORCE_COARSE_VARIANT", "4")  # stencils, as long as they are held
     rel, stencils, _ = _run(batch, graph, limit=peak)
     assert rel <= 1e-8 and all(stencils)
+
+
+def test_time_sweep_times_the_solvers_sweep(monkeypatch):
+    """On a coarse level that is the stencil sweep where solves take one: timing lays it out."""
+    monkeypatch.setattr(B, "_TorchArena", Recorder)
+    monkeypatch.setenv("GMT_FORCE_COARSE_VARIANT", "5")
+    H = B.Hierarchy(gyroid_sheet(32, 0, 0.3), 4, "elastic")
+    assert H.time_sweep(2, reps=3) > 0
+    assert _stencil_bytes(H, 2) in H._arena.size.values()
+    H.close()
