@@ -604,18 +604,24 @@ __global__ __launch_bounds__(D == 3 ? 288 : 256) void k_galerkin_sum(const int* 
 #pragma unroll
   for (int c = 0; c < 8; ++c) {
     if (fid[c] < 0) continue;
-    const double2 v = reinterpret_cast<const double2*>(terms + (size_t)row[c] * M * M)[t];
+    // pairs of values, for which the allocator's memory need not be aligned: one wide access
+    // each all the same
+    const double* v = terms + (size_t)row[c] * M * M + 2 * t;
+    const double v0 = v[0], v1 = v[1];
     if (fscale) {
       const double sc = fscale[fid[c]];
-      a0 = fma(sc, v.x, a0);
-      a1 = fma(sc, v.y, a1);
+      a0 = fma(sc, v0, a0);
+      a1 = fma(sc, v1, a1);
     } else {
-      a0 += v.x;
-      a1 += v.y;
+      a0 += v0;
+      a1 += v1;
     }
   }
-  reinterpret_cast<double2*>(out64 + (size_t)e * M * M)[t] = make_double2(a0, a1);
-  reinterpret_cast<float2*>(out32 + (size_t)e * M * M)[t] = make_float2((float)a0, (float)a1);
+  const size_t at = (size_t)e * M * M + 2 * t;
+  out64[at] = a0;
+  out64[at + 1] = a1;
+  out32[at] = (float)a0;
+  out32[at + 1] = (float)a1;
 }
 
 inline unsigned blocks_for(size_t n) { return (unsigned)((n + kBlock - 1) / kBlock); }
