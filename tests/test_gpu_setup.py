@@ -129,3 +129,34 @@ def test_component_count(N, L, fill):
             message = str(e)
         assert (f"form {want} node-connected components" in message) == (want != 1), (N, fill, seed, want, message)
         assert want != 1 or "components" not in message
+
+
+@pytest.mark.parametrize("rows", [2048, 2049])
+def test_coarsest_at_the_limit(rows):
+    """The largest matrix (64 full tiles) is inverted, one row more is refused."""
+    B = _gmt()
+    vox = np.zeros((16, 16, 16), dtype=np.uint8)
+    nodes = set()
+    for z, y, x in np.ndindex(12, 13, 13):  # voxel by voxel, each touching the ones before
+        corners = {(z + c // 4, y + c // 2 % 2, x + c % 2) for c in range(8)}
+        if len(nodes | corners) <= rows:
+            nodes |= corners
+            vox[z, y, x] = 1
+    assert len(nodes) == rows
+    if rows > 2048:
+        with pytest.raises(B.GmtError, match=f"{rows} DOFs") as ei:
+            B.Hierarchy(vox, 1, "thermal")
+        assert ei.value.status == B.GMT_E_INVAL
+        return
+    H = B.Hierarchy(vox, 1, "thermal")
+    assert H.n_n(1) == rows
+    f = np.random.default_rng(7).standard_normal((rows, H.c, H.d))
+    u = H.coarse_solve(torch.as_tensor(f, device=DEV)).cpu().numpy()
+    A = _pinned(H, 1)
+    w = np.linalg.eigvalsh(A)
+    ref = np.linalg.solve(A, f[1:, :, 0])
+    err = np.linalg.norm(u[1:, :, 0] - ref) / np.linalg.norm(ref)
+    bound = 4 * A.shape[0] * np.finfo(float).eps * w[-1] / w[0]
+    print(f"[rows {rows}] error {err:.1e} bound {bound:.1e}", flush=True)
+    assert np.all(u[0] == 0) and err <= bound
+    H.close()
