@@ -931,8 +931,10 @@ static void autotune(Hier& h, hipStream_t s) {
 
 // Level 2 gets assembled stencils below this many nodes only: its element matrices
 // are a 590 KB table, so where the stencils (1.1 KB a node) do not stay in the 256 MB
-// Infinity Cache they cost more bytes than they save (512^3: 4.7 GB a sweep).  The
-// deeper levels replace matrices of twice their size.
+// Infinity Cache they cost more bytes than they save (512^3: 4.7 GB a sweep).  FP32 elastic
+// sweep, us from the table / the stencils: 107 k nodes 37.9 / 26.6, 198 k 67.3 / 58.8, 329 k
+// 85.8 / 111.9, 743 k 182 / 258 (thermal, an eighth of the bytes: 743 k 40.1 / 36.8, 1.4 M 65.1 /
+// 87.4).  The deeper levels replace matrices of twice their size.
 constexpr int kStencilTableNodes = 1 << 18;
 
 // Assembled stencils of the smoothed coarse levels for the solver's sweeps (Hier::solving):

@@ -799,9 +799,11 @@ __device__ __forceinline__ Share level1_share(int xcd, unsigned nb, unsigned ni)
 // and larger elastic cells the staged interior (variant 9) in a launch of its own stays
 // ahead (54.7 + 51.4 us); the autotuner times both.
 // The interior takes all cases of a node in a thread (ids and D^-1 read once), or one
-// (ic = 1) where that would make fewer workgroups than half the CUs: 32^3 solve 5.6 ms
-// with all, 5.0 - 5.5 with one; colours of 160^3 (150 k nodes): cycle 2.7 ms with all,
-// 3.0 with one.
+// (ic = 1) where that would make fewer workgroups than half the CUs.  FP32 elastic sweep,
+// us with all / one: 5.0 k interior nodes 12.0 / 7.3, 22 k 18.9 / 14.0, 38 k 21.4 / 18.6,
+// 59 k 26.4 / 26.4, 124 k 44.1 / 46.0, 222 k 56.0 / 74.6 (FP64 22 k 38.3 / 21.9, 124 k 73.9 /
+// 73.0; thermal within 1 us up to 124 k); colours of 160^3 (150 k nodes): cycle 2.7 ms with
+// all, 3.0 with one.
 constexpr int kSplitInterior = 1 << 15;
 template <typename T, int D, int C, int EPI>
 __global__ __launch_bounds__(kBlock) void k_apply_lists(LevelView<T> L, sweep_input<T, EPI> u, EpiArgs<T> e, int ic) {
@@ -2162,7 +2164,10 @@ void launch_normalize(const T* src, size_t n, const double* nrm2, T* dst, hipStr
 
 // Transfers over fewer threads than this run one case per thread (six times the
 // threads and index lookups, a sixth of the chain): 18 k / 3.5 k nodes, restriction
-// 11 -> 5.6 us, prolongation 12 -> 4.7 us.
+// 11 -> 5.6 us, prolongation 12 -> 4.7 us.  What one case per thread gains on elastic levels,
+// FP32 / FP64 us: restriction to 17 k nodes 3.5 / 8.4, 30 k 3.0 / 4.4, 49 k -1.3 / -2.1, 74 k 0.8 /
+// 5.1, 107 k -4.5 / -3.4; prolongation to 44 k 1.6 / 2.7, 97 k 0.8 / 2.1, 183 k -0.6 / 1.1,
+// 308 k -2.3 / -0.5 (thermal: nothing below, a loss above).
 constexpr int kTransferSplit = 1 << 16;
 
 template <typename T>
