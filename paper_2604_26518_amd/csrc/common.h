@@ -429,6 +429,7 @@ struct Work {
 struct Hier {
   gmt_params p{};
   bool solving = false;  // inside gmt_solve / gmt_solve_batch: the coarse sweeps may use the assembled stencils
+  bool precise = false;  // see Precise
   int N = 0, L = 0, C = 0, D = 0, Q = 0;
   std::vector<LevelData> lv;
   double Ke[576] = {0};
@@ -448,6 +449,7 @@ struct Hier {
   double* kcls64 = nullptr;  // symmetry-class values of K_e
   float* kcls32 = nullptr;
   double* scls64 = nullptr;  // symmetry-class values of S
+  double *kcls64p = nullptr, *scls64p = nullptr;  // the same rounded once (Precise)
   float* scls32 = nullptr;
   double* fe64 = nullptr;
   double* table64 = nullptr;
@@ -514,6 +516,18 @@ struct Solving {
   const bool outer;
   explicit Solving(Hier& hh) : h(hh), outer(hh.solving) { h.solving = true; }
   ~Solving() { h.solving = outer; }
+};
+
+// Entry points that return an operator's own result: their FP64 level-1 sweeps take the
+// class values rounded once.  Error against extended precision of a 32^3 cell's residual,
+// relative to the sweep that reads K_e entry by entry (cb 0): elastic 0.92 - 1.0, thermal 0.33 -
+// 0.66; with the values of single entries 0.99 - 1.3 and 1.2 - 2.0.  Solves and cycles keep
+// the latter: CG on thin spinodals turns a last-bit change of a sweep into 1e-7 in the solution.
+struct Precise {
+  Hier& h;
+  const bool outer;
+  explicit Precise(Hier& hh) : h(hh), outer(hh.precise) { h.precise = true; }
+  ~Precise() { h.precise = outer; }
 };
 
 // Launch shape to try out in a scope: afterwards, also where a launch failed, it is what it was.

@@ -191,8 +191,8 @@ LevelView<T> Hier::view(int l) const {
   if constexpr (std::is_same<T, double>::value) {
     v.K = d.kind == KIND_SHARED ? Ke64 : (d.kind == KIND_TABLE ? table64 : d.Kel64);
     v.S = S64;
-    v.kcls = kcls64;
-    v.scls = scls64;
+    v.kcls = precise ? kcls64p : kcls64;
+    v.scls = precise ? scls64p : scls64;
     v.bs = d.bs64;
     v.xcd = d.xcd64;
     v.cb = d.cb64;
@@ -378,6 +378,37 @@ static void element_constants(Hier& h) {
   double fn = 0;
   for (int i = 0; i < M * C; ++i) fn += h.fe[i] * h.fe[i];
   h.fe_norm = std::sqrt(fn);
+}
+
+// K_e in extended precision: K[(a, i), (b, j)] is the mean over the 8 Gauss points of
+// lam g_ai g_bj + G (g_aj g_bi + delta_ij g_a . g_b), or kappa g_a . g_b.
+static std::vector<long double> element_matrix_extended(const Hier& h) {
+  typedef long double R;
+  const int D = h.D, M = 8 * D;
+  std::vector<R> K(M * M, 0);
+  const R off = 0.5L / std::sqrt(3.0L);
+  const R E = h.p.E, nu = h.p.nu, lam = E * nu / ((1 + nu) * (1 - 2 * nu)), G = E / (2 * (1 + nu));
+  for (int q = 0; q < 8; ++q) {
+    R g[8][3];  // shape-function gradients at the point
+    for (int a = 0; a < 8; ++a) {
+      R f[3];
+      for (int i = 0; i < 3; ++i) {
+        const R x = 0.5L + ((q >> i) & 1 ? off : -off);
+        f[i] = (a >> i) & 1 ? x : 1 - x;
+      }
+      for (int i = 0; i < 3; ++i) g[a][i] = ((a >> i) & 1 ? 1 : -1) * f[(i + 1) % 3] * f[(i + 2) % 3];
+    }
+    for (int a = 0; a < 8; ++a)
+      for (int b = 0; b < 8; ++b) {
+        const R dot = g[a][0] * g[b][0] + g[a][1] * g[b][1] + g[a][2] * g[b][2];
+        for (int i = 0; i < D; ++i)
+          for (int j = 0; j < D; ++j)
+            K[(a * D + i) * M + b * D + j] +=
+                0.125L * (D == 1 ? (R)h.p.kappa * dot
+                                 : lam * g[a][i] * g[b][j] + G * (g[a][j] * g[b][i] + (i == j ? dot : 0)));
+      }
+  }
+  return K;
 }
 
 // Ps[c][m][o]: weight of coarse-element corner o at corner m of child c
@@ -1624,13 +1655,18 @@ static void build(Hier& h, const uint8_t* vox, hipStream_t s, const double* rho 
   // assembled interior stencil of the shared K_e: S[j][d][d2] over the 27 offsets
   {
     std::vector<double> S((size_t)27 * D * D, 0.0);
+    const std::vector<long double> Kx = element_matrix_extended(h);
+    std::vector<long double> Sx(S.size(), 0.0L);
     for (int k = 0; k < 8; ++k) {
       const int a = 7 - k;
       for (int m = 0; m < 8; ++m) {
         const int j = ((k & 1) + (m & 1)) + 3 * (((k >> 1) & 1) + ((m >> 1) & 1)) +
                       9 * (((k >> 2) & 1) + ((m >> 2) & 1));
         for (int d = 0; d < D; ++d)
-          for (int d2 = 0; d2 < D; ++d2) S[(j * D + d) * D + d2] += h.Ke[(a * D + d) * M + m * D + d2];
+          for (int d2 = 0; d2 < D; ++d2) {
+            S[(j * D + d) * D + d2] += h.Ke[(a * D + d) * M + m * D + d2];
+            Sx[(j * D + d) * D + d2] += Kx[(a * D + d) * M + m * D + d2];
+          }
       }
     }
     double smax = 0;
@@ -1646,9 +1682,11 @@ static void build(Hier& h, const uint8_t* vox, hipStream_t s, const double* rho 
         }
     }
     // symmetry-class values of K_e (taken from block row 0, where the sign is
-    // +1), then every entry of K_e checked against its class value
+    // +1), then every entry of K_e checked against its class value.  kcp, scp: the class
+    // values rounded once (those of single entries of K_e and S carry the entries' own
+    // errors of a few ulp, which all entries of a class then share)
     const int NK = D == 1 ? 4 : 14;
-    std::vector<double> kc(NK, 0.0);
+    std::vector<double> kc(NK, 0.0), kcp(NK, 0.0);
     std::vector<char> have(NK, 0);
     double kmax = 0;
     for (int r = 0; r < M * M; ++r) kmax = std::max(kmax, std::fabs(h.Ke[r]));
@@ -1659,7 +1697,7 @@ static void build(Hier& h, const uint8_t* vox, hipStream_t s, const double* rho 
       for (int d = 0; d < D; ++d)
         for (int d2 = 0; d2 < D; ++d2) {
           const int c = cls(m, d, d2);
-          if (!have[c]) kc[c] = h.Ke[d * M + m * D + d2], have[c] = 1;
+          if (!have[c]) kc[c] = h.Ke[d * M + m * D + d2], kcp[c] = (double)Kx[d * M + m * D + d2], have[c] = 1;
         }
     for (int a = 0; a < 8; ++a)
       for (int m = 0; m < 8; ++m)
@@ -1667,12 +1705,13 @@ static void build(Hier& h, const uint8_t* vox, hipStream_t s, const double* rho 
           for (int d2 = 0; d2 < D; ++d2) {
             const bool neg = D == 1 ? kcls_negative<1>(a, d, d2) : kcls_negative<3>(a, d, d2);
             const double v = (neg ? -1.0 : 1.0) * h.Ke[(a * D + d) * M + m * D + d2];
-            if (std::fabs(v - kc[cls(a ^ m, d, d2)]) > 1e-12 * kmax)
+            if (std::fabs(v - kc[cls(a ^ m, d, d2)]) > 1e-12 * kmax ||
+                std::fabs(v - kcp[cls(a ^ m, d, d2)]) > 1e-12 * kmax)
               fail(GMT_E_STATE, "K_e entry (%d,%d,%d,%d) is not its symmetry-class value", a, m, d, d2);
           }
     // symmetry-class values of S, and every stencil entry checked against them
     const int NS = D == 1 ? 4 : 8;
-    std::vector<double> sc(NS, 0.0);
+    std::vector<double> sc(NS, 0.0), scp(NS, 0.0);
     std::vector<char> shave(NS, 0);
     auto scl = [&](int j, int d, int d2) {
       return D == 1 ? scls_index<1>(j, d, d2) : scls_index<3>(j, d, d2);
@@ -1691,8 +1730,9 @@ static void build(Hier& h, const uint8_t* vox, hipStream_t s, const double* rho 
             const double w = (sneg(j, d, d2) ? -1.0 : 1.0) * v;
             const int c = scl(j, d, d2);
             if (pass == 0) {
-              if (!shave[c]) sc[c] = w, shave[c] = 1;
-            } else if (std::fabs(w - sc[c]) > 1e-12 * smax) {
+              if (!shave[c])
+                sc[c] = w, scp[c] = (double)((sneg(j, d, d2) ? -1 : 1) * Sx[(j * D + d) * D + d2]), shave[c] = 1;
+            } else if (std::fabs(w - sc[c]) > 1e-12 * smax || std::fabs(w - scp[c]) > 1e-12 * smax) {
               fail(GMT_E_STATE, "stencil entry (%d,%d,%d) is not its symmetry-class value", j, d, d2);
             }
           }
@@ -1704,6 +1744,10 @@ static void build(Hier& h, const uint8_t* vox, hipStream_t s, const double* rho 
     h.kcls32 = h.alloc<float>(NK);
     GMT_HIP(hipMemcpyAsync(h.kcls64, kc.data(), NK * sizeof(double), hipMemcpyHostToDevice, s));
     launch_convert<double, float>(h.kcls64, h.kcls32, NK, s);
+    h.kcls64p = h.alloc<double>(NK);
+    h.scls64p = h.alloc<double>(NS);
+    GMT_HIP(hipMemcpyAsync(h.kcls64p, kcp.data(), NK * sizeof(double), hipMemcpyHostToDevice, s));
+    GMT_HIP(hipMemcpyAsync(h.scls64p, scp.data(), NS * sizeof(double), hipMemcpyHostToDevice, s));
     h.S64 = h.alloc<double>(S.size());
     h.S32 = h.alloc<float>(S.size());
     GMT_HIP(hipMemcpyAsync(h.S64, S.data(), S.size() * sizeof(double), hipMemcpyHostToDevice, s));
@@ -1863,7 +1907,8 @@ static void build(Hier& h, const uint8_t* vox, hipStream_t s, const double* rho 
   // per boundary thread.  Fastest or level with the fastest on every shape timed:
   // residual of 8.7 M nodes, 6 cases: FP64 2.78 ms (cb 7: 3.55, cb 0: 4.35), FP32 1.84
   // (2.20, 2.70); of 14.5 k nodes: FP64 36 us (44, 88), FP32 27 us (27, 65); density
-  // K.u at 64^3: FP64 91 us (cb 7: 107), FP32 53 us (61).
+  // K.u at 64^3: FP64 91 us (cb 7: 107), FP32 53 us (61).  Its boundary coefficients are
+  // class values where cb 0 reads K_e: these entry points take them rounded once (Precise).
   h.lv[0].cb32 = h.lv[0].cb64 = h.density ? 8 : 9;
   GMT_HIP(hipStreamSynchronize(s));
   for (void* b : pw) h.release(b);
@@ -2311,6 +2356,7 @@ static void apply_api(Hier& h, int l, int epi, const void* d_u, const void* d_f,
   Work<T>& W = h.work<T>();
   const T* u = stage_in<T>(h, l, d_u, W.io1[l], s);
   const T* f = d_f ? stage_in<T>(h, l, d_f, W.io2[l], s) : nullptr;
+  const Precise scope(h);
   apply<T>(h, l, epi, u, f, W.io3[l], h.C, s);
   stage_out<T>(h, l, W.io3[l], d_out, s);
 }
@@ -2351,6 +2397,7 @@ static void smooth_abi(Hier& h, int l, const void* d_f, void* d_u, int nu, int s
   const T* f = stage_in<T>(h, l, d_f, W.io1[l], s);
   T* u = stage_in<T>(h, l, d_u, W.io2[l], s);
   T* alt = W.io3[l];
+  const Precise scope(h);
   smooth<T>(h, l, f, u, alt, W.dvec[l], nu, false, sm, p1, p2, s, sm == GMT_SMOOTH_GS && p2 != 0.0);
   stage_out<T>(h, l, u, d_u, s);
 }
@@ -2680,6 +2727,7 @@ gmt_status gmt_relative_residual(gmt_hier_t H, const void* d_f, const void* d_u,
     hipStream_t s = S(stream);
     const double* f = to_soa64(h, d_f, dtype, &h.s_x64, s);
     const double* u = to_soa64(h, d_u, dtype, &h.s_t64, s);
+    const Precise scope(h);
     rel_residual64(h, f, u, scratch64(h, &h.s_r64), h_rel, nullptr, s);
   });
 }
@@ -2694,6 +2742,7 @@ gmt_status gmt_homogenize(gmt_hier_t H, const void* d_u, int32_t dtype, double* 
     const int n = h.lv[0].n_n, C = h.C;
     const double* u = to_soa64(h, d_u, dtype, &h.s_t64, s);
     double* y = scratch64(h, &h.s_r64);
+    const Precise scope(h);
     apply<double>(h, 0, EPI_KU, u, nullptr, y, C, s);
     double* A = h.red_out + 96;
     double* B = h.red_out + 160;
