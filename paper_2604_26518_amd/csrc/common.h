@@ -429,7 +429,8 @@ struct Work {
 struct Hier {
   gmt_params p{};
   bool solving = false;  // inside gmt_solve / gmt_solve_batch: the coarse sweeps may use the assembled stencils
-  bool precise = false;  // see Precise
+  bool default64 = true;  // level 1's FP64 launch shape is the build's, not timed
+  bool precise = false;   // see Precise
   int N = 0, L = 0, C = 0, D = 0, Q = 0;
   std::vector<LevelData> lv;
   double Ke[576] = {0};
@@ -518,15 +519,17 @@ struct Solving {
   ~Solving() { h.solving = outer; }
 };
 
-// Entry points that return an operator's own result: their FP64 level-1 sweeps take the
-// class values rounded once.  Error against extended precision of a 32^3 cell's residual,
-// relative to the sweep that reads K_e entry by entry (cb 0): elastic 0.92 - 1.0, thermal 0.33 -
-// 0.66; with the values of single entries 0.99 - 1.3 and 1.2 - 2.0.  Solves and cycles keep
-// the latter: CG on thin spinodals turns a last-bit change of a sweep into 1e-7 in the solution.
+// Entry points that return an operator's own result: until a solve or cycle has chosen the
+// FP64 shape of level 1, their sweeps of it take the class values rounded once.  Error against
+// extended precision of a 32^3 cell's residual, relative to the sweep that reads K_e entry by
+// entry (cb 0): elastic 0.92 - 1.0, thermal 0.33 - 0.66; with the values of single entries 0.99 -
+// 1.3 and 1.2 - 2.0.  Solves and cycles, and the entry points after them, keep the latter: CG
+// on thin spinodals turns a last-bit change of a sweep into 1e-7 in the solution, and C_H
+// cancels the energies of the same sums.
 struct Precise {
   Hier& h;
   const bool outer;
-  explicit Precise(Hier& hh) : h(hh), outer(hh.precise) { h.precise = true; }
+  explicit Precise(Hier& hh) : h(hh), outer(hh.precise) { h.precise = h.default64; }
   ~Precise() { h.precise = outer; }
 };
 

@@ -900,6 +900,7 @@ static void autotune(Hier& h, hipStream_t s) {
     if (tuned) continue;
     tuned = true;
     if (off || d.n_n == 0) continue;
+    if (l == 0 && !f32) h.default64 = false;
     const std::vector<int> key = tune_key(h, d, f32);
     {
       std::lock_guard<std::mutex> g(g_tune_mu);
@@ -1908,7 +1909,7 @@ static void build(Hier& h, const uint8_t* vox, hipStream_t s, const double* rho 
   // residual of 8.7 M nodes, 6 cases: FP64 2.78 ms (cb 7: 3.55, cb 0: 4.35), FP32 1.84
   // (2.20, 2.70); of 14.5 k nodes: FP64 36 us (44, 88), FP32 27 us (27, 65); density
   // K.u at 64^3: FP64 91 us (cb 7: 107), FP32 53 us (61).  Its boundary coefficients are
-  // class values where cb 0 reads K_e: these entry points take them rounded once (Precise).
+  // class values where cb 0 reads K_e: the entry points take them rounded once (Precise).
   h.lv[0].cb32 = h.lv[0].cb64 = h.density ? 8 : 9;
   GMT_HIP(hipStreamSynchronize(s));
   for (void* b : pw) h.release(b);
@@ -1938,6 +1939,7 @@ constexpr int kInnerMixed = 100;
 static void borrow_f32_shape(Hier& h) {
   LevelData& d = h.lv[0];
   if (d.tuned64 || !d.tuned32) return;
+  h.default64 = false;
   d.bs64 = d.bs32;
   d.cb64 = d.cb32;
   d.xcd64 = d.xcd32;
