@@ -50,7 +50,7 @@ COPY_BYTES = 512 << 20
 # kernel reports null until it is profiled again.
 SWEEP_TRAFFIC_BYTES = {
     # profiles/level1_chebyshev_sweep_gyroid512_hbm_traffic.txt
-    ("gyroid512_seed30001", 9, "b53cd5b5f18eca48"): (22_693_662 + 5_187_202) * 1024,
+    ("gyroid512_seed30001", 9, "231d77f4a8794efe"): (22_680_387 + 5_187_178) * 1024,
 }
 SWEEP_KERNELS = {
     0: "k_apply_interior_nc + k_apply_boundary_st",
